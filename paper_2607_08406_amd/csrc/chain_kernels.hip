@@ -336,7 +336,7 @@ hipError_t launch_chain(const NetDev& net, const mca_cand* cands, const Aux* aux
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const dim3 grid((unsigned)nchain, commit ? 1u : (unsigned)K);
-  if (net.C <= 10)
+  if (net.C == 10)
     hipLaunchKernelGGL(k_chain<10>, grid, dim3(kChainThreads), 0, s, net, cands, aux, rows, rda,
                        cnt, partial, nchain, k_mode, st);
   else

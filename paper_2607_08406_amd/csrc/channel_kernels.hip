@@ -404,7 +404,7 @@ hipError_t launch_channel(const NetDev& net, const mca_channel* ch, const Aux* a
                           const double* dL, hipStream_t s) {
   const bool commit = k_mode != -2;
   const dim3 grid((unsigned)ntiles, commit ? 1u : (unsigned)K);
-  hipError_t e = (net.C <= 10)
+  hipError_t e = (net.C == 10)
                      ? launch_width<10>(net, grid, ch, aux, partial, ntiles, k_mode, st, s)
                      : launch_width<kCMax>(net, grid, ch, aux, partial, ntiles, k_mode, st, s);
   if (e != hipSuccess || !commit) return e;

@@ -358,7 +358,7 @@ hipError_t launch_norm(const NetDev& net, const NormDev& nd, const mca_cand* can
                        DevState* st, const double* dL, hipStream_t s) {
   const bool commit = k_mode != -2;
   const dim3 grid((unsigned)ntiles, commit ? 1u : (unsigned)K);
-  hipError_t e = (net.C <= 10)
+  hipError_t e = (net.C == 10)
                      ? launch_norm_width<10>(net, nd, grid, cands, aux, partial, ntiles, k_mode, st, s)
                      : launch_norm_width<kCMax>(net, nd, grid, cands, aux, partial, ntiles, k_mode, st, s);
   if (e != hipSuccess || !commit) return e;

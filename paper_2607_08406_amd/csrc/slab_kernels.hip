@@ -560,7 +560,7 @@ __global__ void k_transpose(const float* src, int rows, int cols, float* dst) {
     if (c0 + c < cols && r0 + tx < rows) dst[(int64_t)(c0 + c) * rows + r0 + tx] = tile[tx][c];
 }
 
-int slab_tile(int C) { return C <= 10 ? SlabTile<10>::T : SlabTile<kCMax>::T; }
+int slab_tile(int C) { return C == 10 ? SlabTile<10>::T : SlabTile<kCMax>::T; }
 
 hipError_t launch_propose_columns(const NetDev& net, const DevState* st, int K, mca_cand* cands,
                                  Aux* aux, const uint64_t* fmask, uint64_t* cmask,
@@ -586,7 +586,7 @@ hipError_t launch_slab(const NetDev& net, const mca_cand* cands, const Aux* aux,
     hipLaunchKernelGGL(kernel, dim3(nblk), dim3(kSlabThreads), 0, s, net, cands, aux, K, cols,
                        nnz, partial, nblk, k_mode, st, dL, columns ? 1 : 0);
   };
-  const bool small = net.C <= 10;
+  const bool small = net.C == 10;  // the ten-class kernels take exactly ten
   if (net.act == MCA_ACT_TANH)
     small ? go(k_slab<10, MCA_ACT_TANH>) : go(k_slab<kCMax, MCA_ACT_TANH>);
   else if (net.act == MCA_ACT_RELU)
