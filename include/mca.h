@@ -289,8 +289,8 @@ int mca_rollback(mca_ctx* ctx);
  * without any use of the context's per-call buffers.  The per-call device
  * buffers (the candidates' device copy, prepared values, tile sums, the
  * three-layer and deep nets' affected-sample lists, loss changes) live in one
- * static array per GPU of 8 MiB, held until the process ends; a request that
- * needs more (K x (N or tiles) too large) fails with MCA_EINVAL before
+ * static array per GPU for 8 MiB of them, held until the process ends; a request
+ * that needs more (K x (N or tiles) too large) fails with MCA_EINVAL before
  * anything is enqueued.  The call allocates nothing, scores K candidates
  * (1 <= K <= 1024, K not bounded by k_max) against the committed state
  * exactly as mca_eval_losses does (same kernels, same results), leaves no

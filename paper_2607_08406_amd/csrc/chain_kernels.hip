@@ -9,20 +9,21 @@
 // loss change from it and the cached softmax (ce_change).  A deep net with
 // small weights changes its loss by 1e-11 per mutation; a recomputed loss
 // minus the cached one would keep none of it in fp32.  The dense products are
-// the dominant work and run on the matrix cores (v_mfma_f32_16x16x4f32).
+// the dominant work and run on the matrix cores, in bf16 parts (split_mma.hpp).
 //
 // k_rows lists, per candidate and in increasing sample order, the samples
 // whose activation changes, with their da.  A block of k_chain takes one
-// candidate and 64 listed samples: it builds dA_{l+1} in an LDS tile
-// ([64][256], rows padded), runs the dense layers tile to tile (4 waves, each
-// 64 samples x 64 output units as 4 x 4 MFMA tiles), computes the logit
-// changes and the loss change of each sample, and adds the 64 changes in
+// candidate and 48 listed samples: it builds dA_{l+1} in an LDS tile
+// ([3 parts][48][256], rows padded), runs the dense layers tile to tile (4
+// waves, each 48 samples x 64 output units as 3 x 4 MFMA tiles), computes the
+// logit changes and the loss change of each sample, and adds the 48 changes in
 // list order.  The commit runs the same arithmetic for the chosen candidate
 // and moves every cached field by its change.
 //
 // The hidden layers touched here must be exactly kChainUnits wide.
 #include "device_common.hpp"
 #include "chain_kernels.hpp"
+#include "split_mma.hpp"
 
 namespace mca {
 
@@ -30,10 +31,7 @@ namespace {
 
 constexpr int kRowsThreads = 1024;
 constexpr int kChainThreads = 256;
-constexpr int kRowStride = kChainUnits + 4;  // floats per padded LDS row
-static_assert(kChainThreads == kChainUnits, "one thread per unit loads W_s[:, j]");
-
-typedef float floatx4 __attribute__((ext_vector_type(4)));
+static_assert(kChainThreads == kChainUnits, "a wave takes 64 output units");
 
 }  // namespace
 
@@ -45,7 +43,7 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 __global__ __launch_bounds__(kRowsThreads) void k_rows(NetDev net_arg, const mca_cand* cands,
                                                        const Aux* aux, int k_mode,
                                                        DevState* st, const double* dL, int* rows,
-                                                       float* rda, int* cnt) {
+                                                       float* rda, int* cnt, int K) {
   __shared__ NetDev net;
   stage_net(net, net_arg);
   __shared__ int wave_n[kRowsThreads / 64];
@@ -55,6 +53,16 @@ __global__ __launch_bounds__(kRowsThreads) void k_rows(NetDev net_arg, const mca
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const mca_cand c = cands[k];
   const int L = net.L, l = c.layer;
+  if (!commit && wave == 0) {  // the candidate's place by layer, then by index
+    int r = 0;
+    for (int k1 = lane; k1 < K; k1 += 64) {
+      const int l1 = cands[k1].layer;
+      r += (l1 < l || (l1 == l && k1 < k)) ? 1 : 0;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) r += __shfl_xor(r, o, 64);
+    if (lane == 0) cnt[K + r] = k;
+  }
   if (l > L - 4 || (!commit && !aux[k].valid)) {
     if (tid == 0) cnt[k] = 0;
     return;
@@ -103,7 +111,7 @@ __global__ __launch_bounds__(kRowsThreads) void k_rows(NetDev net_arg, const mca
     if (commit) {
       const Aux a = aux[k];
       const int64_t idx = (int64_t)c.j * net.widths[l] + c.i;
-      gstore(&net.W[l][idx], a.w_new);
+      put_weight(net, l, c.j, c.i, a.w_new);
       if (net.ternary) gstore(&net.codes[l][idx], (int8_t)c.code);
       if (net.sub_size == 0) st->L += dL[k];
       st->accepted += 1;
@@ -111,185 +119,176 @@ __global__ __launch_bounds__(kRowsThreads) void k_rows(NetDev net_arg, const mca
   }
 }
 
-// grid (ceil(N / 64), K) for an evaluation, (ceil(N / 64), 1) for a commit.
-template <int CM>
+// grid (nchain, K) for an evaluation (row y: the y-th candidate by layer, so
+// that the longest chains start first and the short ones fill the last round),
+// (nchain, 1) for a commit.
+//
+// What bounds it: the matrix cores and the L2 reads of the weights take about
+// as long as each other.  The products run on bf16 parts (split_mma.hpp); the
+// tile holds its parts in LDS (76 KB at 48 rows), so two blocks share a CU and
+// one's products run beside the other's transfer functions.  More rows a block
+// would halve the weights' reads but leave one block; 32 rows read too much.
+// 784-24x256-10, 32 candidates on 4096 samples: 2.82 -> 1.33 ms a step against
+// fp32 products on 64-row tiles, the same error against 64 bits (2.4e-7).
+template <int CM, int ACT>
 __global__ __launch_bounds__(kChainThreads, 2) void k_chain(NetDev net_arg, const mca_cand* cands,
                                                          const Aux* aux, const int* rows,
                                                          const float* rda, const int* cnt,
-                                                         float* partial, int nchain, int k_mode,
-                                                         const DevState* st) {
+                                                         float* partial, int nchain, int K,
+                                                         int k_mode, const DevState* st) {
+  constexpr int T = kChainT, SB = T / 16, W = kChainUnits, RS = W + 8;
   __shared__ NetDev net;
   stage_net(net, net_arg);
-  // activation changes, [sample][unit], rewritten in place layer by layer
-  // (one tile keeps two blocks resident per CU)
-  __shared__ float ta[kChainT * kRowStride];
-  __shared__ float wcol[kChainUnits];
-  __shared__ int rown[kChainT];
-  __shared__ float rowda[kChainT];
-  __shared__ float logit[kChainT][CM];
-  __shared__ float dls[kChainT];
+  // activation changes in three bf16 parts, [part][sample][unit in k order],
+  // rewritten in place layer by layer
+  __shared__ __attribute__((aligned(16))) uint16_t ta[3 * T * RS];
+  __shared__ int rown[T];
+  __shared__ float rowda[T];
+  __shared__ float dls[T];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const bool commit = k_mode != -2;
-  const int k = commit ? ((k_mode >= 0) ? k_mode : st->chosen) : (int)blockIdx.y;
+  const int k = commit ? ((k_mode >= 0) ? k_mode : st->chosen) : cnt[K + (int)blockIdx.y];
   if (k < 0) return;
   const mca_cand c = cands[k];
   const int L = net.L, l = c.layer;
   if (l > L - 4) return;  // scored by another kernel
   const int tile = blockIdx.x;
   const int nrows = cnt[k];
-  const int e0 = tile * kChainT;
+  const int e0 = tile * T;
   if (e0 >= nrows) {
     if (!commit && tid == 0) partial[(int64_t)k * nchain + tile] = 0.f;
     return;
   }
   const int C = (CM < kCMax) ? CM : net.C;
-  const int act = net.act;
   const float gamma = net.gamma;
   const int64_t N = net.N, Ns = net.Ns;
   const int s = l + 1;  // the layer the rank-1 update reaches
 
-  // 1. the tile's samples and the column W_s[:, j]
-  if (tid < kChainT) {
+  // 1. the tile's samples
+  if (tid < T) {
     const int e = e0 + tid;
     rown[tid] = (e < nrows) ? gload(&rows[(int64_t)k * N + e]) : -1;
     rowda[tid] = (e < nrows) ? gload(&rda[(int64_t)k * N + e]) : 0.f;
   }
-  {
-    const float* Ws = net.W[s];
-    wcol[tid] = gload(&Ws[(int64_t)tid * kChainUnits + c.j]);  // kChainThreads == kChainUnits
-  }
   __syncthreads();
-  // 2. dA_s = phi(z_s + da W_s[:, j]) - phi(z_s) into the tile (unit-major
-  // source: consecutive threads take consecutive rows of one unit)
-  {
-    float* Zs = net.Z[s];
-    for (int e = tid; e < kChainT * kChainUnits; e += kChainThreads) {
-      const int r = e & (kChainT - 1), u = e / kChainT;
-      const int n = rown[r];
-      float v = 0.f;
-      if (n >= 0) {
-        const float z = gload(&Zs[(int64_t)u * Ns + n]);
-        const float dz = rowda[r] * wcol[u];
-        v = dphi(z, dz, act, gamma);
-        if (commit) gstore(&Zs[(int64_t)u * Ns + n], z + dz);
+  const int q = lane >> 4, li = lane & 15;
+  // the samples of this lane's output rows 16 sb + 4 q + v (-1 for padding
+  // rows: their changes are zero)
+  int nrow[SB][4];
+#pragma unroll
+  for (int sb = 0; sb < SB; ++sb)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) nrow[sb][v] = rown[16 * sb + 4 * q + v];
+  // every row of the tile holds the next sample after the one before
+  const bool rows_dense = rown[T - 1] == rown[0] + T - 1 && (rown[0] & 3) == 0;
+  // The cached fields of layer m at this lane's outputs (D layout: lane (q,
+  // li), element v -> row 16 sb + 4 q + v, unit 64 w + 16 cb + li).  A lane's
+  // four rows are four consecutive samples whenever the tile lists every
+  // sample (a candidate past the first layer): one 16-byte load each then
+  // (16-byte aligned: the tile starts at a multiple of 48).
+  auto fields = [&](int m, f32x4 (&zc)[SB][4]) {
+    const float* Zm = net.Z[m];
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb) {
+      const float* zu = Zm + (int64_t)(64 * wave + 16 * cb + li) * Ns;
+      if (rows_dense) {
+#pragma unroll
+        for (int sb = 0; sb < SB; ++sb) zc[sb][cb] = gload(reinterpret_cast<const f32x4*>(zu + nrow[sb][0]));
+      } else {
+#pragma unroll
+        for (int sb = 0; sb < SB; ++sb)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) zc[sb][cb][v] = gload(zu + (nrow[sb][v] >= 0 ? nrow[sb][v] : 0));
       }
-      ta[r * kRowStride + u] = v;
     }
+  };
+  // dA_m = phi(z_m + dz) - phi(z_m) into the tile's parts; a commit stores
+  // z_m + dz
+  auto finish = [&](int m, const f32x4 (&dz)[SB][4], const f32x4 (&zc)[SB][4]) {
+    float* Zm = net.Z[m];
+#pragma unroll
+    for (int sb = 0; sb < SB; ++sb)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        float d[4];
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) {
+          d[cb] = dphi(zc[sb][cb][v], dz[sb][cb][v], ACT, gamma);
+          if (commit && nrow[sb][v] >= 0)
+            gstore(&Zm[(int64_t)(64 * wave + 16 * cb + li) * Ns + nrow[sb][v]], zc[sb][cb][v] + dz[sb][cb][v]);
+        }
+        const Split2 s0 = split2(d[0], d[1]), s1 = split2(d[2], d[3]);
+        uint16_t* at = ta + (16 * sb + 4 * q + v) * RS + 64 * wave + 4 * li;
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+          *reinterpret_cast<uint2*>(at + p * T * RS) = make_uint2(s0.p[p], s1.p[p]);
+      }
+  };
+  f32x4 acc[SB][4], zc[SB][4];
+  // 2. the rank-1 update: dz_s = da W_s[:, j]
+  {
+    fields(s, zc);
+    const float* Ws = net.W[s];
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb) {
+      const float w = gload(&Ws[(int64_t)(64 * wave + 16 * cb + li) * W + c.j]);
+#pragma unroll
+      for (int sb = 0; sb < SB; ++sb)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[sb][cb][v] = rowda[16 * sb + 4 * q + v] * w;
+    }
+    finish(s, acc, zc);
   }
   __syncthreads();
   // 3. dense layers m = s+1 .. L-2: dz = tile W_m^T, then the tile becomes
   // phi(z_m + dz) - phi(z_m); every wave has read the whole tile before any
   // writes its new values
-  float* const tin = ta;
-  const int q = lane >> 4, li = lane & 15;
-  // the samples of this lane's output rows 16 sb + 4 q + v (row 0 for padding
-  // rows: their changes are zero)
-  int nrow[4][4];
-#pragma unroll
-  for (int sb = 0; sb < 4; ++sb)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) nrow[sb][v] = rown[16 * sb + 4 * q + v];
-  // every row of the tile holds the next sample after the one before
-  const bool rows_dense = rown[kChainT - 1] == rown[0] + kChainT - 1 && (rown[0] & 3) == 0;
   for (int m = s + 1; m <= L - 2; ++m) {
-    const float* Wm = net.W[m];
-    floatx4 acc[4][4];
+    fields(m, zc);
 #pragma unroll
-    for (int sb = 0; sb < 4; ++sb)
+    for (int sb = 0; sb < SB; ++sb)
 #pragma unroll
-      for (int cb = 0; cb < 4; ++cb) acc[sb][cb] = floatx4{0.f, 0.f, 0.f, 0.f};
-    // k is split in blocks of 16: lane group q holds k = 16 kb + 4 q + t for
-    // t = 0..3, used by the four MFMAs of the block in turn
-    floatx4 bcur[4], bnext[4];
-#pragma unroll
-    for (int cb = 0; cb < 4; ++cb)
-      bcur[cb] = gload(reinterpret_cast<const floatx4*>(
-          &Wm[(int64_t)(64 * wave + 16 * cb + li) * kChainUnits + 4 * q]));
-    for (int kb = 0; kb < kChainUnits / 16; ++kb) {
-      if (kb + 1 < kChainUnits / 16) {
-#pragma unroll
-        for (int cb = 0; cb < 4; ++cb)
-          bnext[cb] = gload(reinterpret_cast<const floatx4*>(
-              &Wm[(int64_t)(64 * wave + 16 * cb + li) * kChainUnits + 16 * (kb + 1) + 4 * q]));
-      }
-      floatx4 a4[4];
-#pragma unroll
-      for (int sb = 0; sb < 4; ++sb)
-        a4[sb] = *reinterpret_cast<const floatx4*>(&tin[(16 * sb + li) * kRowStride + 16 * kb + 4 * q]);
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int sb = 0; sb < 4; ++sb)
-#pragma unroll
-          for (int cb = 0; cb < 4; ++cb)
-            acc[sb][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[sb][t], bcur[cb][t],
-                                                               acc[sb][cb], 0, 0, 0);
-#pragma unroll
-      for (int cb = 0; cb < 4; ++cb) bcur[cb] = bnext[cb];
-    }
-    // D layout: lane (q, li), element v -> row 16 sb + 4 q + v, unit 64 w + 16 cb + li;
-    // the cached fields of those elements, all requested before any is used.
-    // A lane's four rows v = 0..3 are four consecutive samples whenever the
-    // tile lists every sample (a candidate past the first layer): one 16-byte
-    // load each then (16-byte aligned: the tile starts at a multiple of 64).
-    float* Zm = net.Z[m];
-    float zc[4][4][4];
-    if (rows_dense) {
-#pragma unroll
-      for (int sb = 0; sb < 4; ++sb)
-#pragma unroll
-        for (int cb = 0; cb < 4; ++cb) {
-          const int u = 64 * wave + 16 * cb + li;
-          const floatx4 z4 = gload(reinterpret_cast<const floatx4*>(&Zm[(int64_t)u * Ns + nrow[sb][0]]));
-#pragma unroll
-          for (int v = 0; v < 4; ++v) zc[sb][cb][v] = z4[v];
-        }
-    } else {
-#pragma unroll
-      for (int sb = 0; sb < 4; ++sb)
-#pragma unroll
-        for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const int u = 64 * wave + 16 * cb + li, nr = nrow[sb][v];
-            zc[sb][cb][v] = gload(&Zm[(int64_t)u * Ns + (nr >= 0 ? nr : 0)]);
-          }
-    }
+      for (int cb = 0; cb < 4; ++cb) acc[sb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    split_product<W, T, RS, SB, 4>(ta, net.WF + split_layer(W, m) + (int64_t)4 * wave * (W / 32) * 3 * 512, lane, acc);
     __syncthreads();
-#pragma unroll
-    for (int sb = 0; sb < 4; ++sb)
-#pragma unroll
-      for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int r = 16 * sb + 4 * q + v, u = 64 * wave + 16 * cb + li;
-          const float dz = acc[sb][cb][v];
-          const float z = zc[sb][cb][v];
-          if (commit && nrow[sb][v] >= 0) gstore(&Zm[(int64_t)u * Ns + nrow[sb][v]], z + dz);
-          tin[r * kRowStride + u] = dphi(z, dz, act, gamma);
-        }
+    finish(m, acc, zc);
     __syncthreads();
   }
-  // 4. logit changes dz_{L-1} = W_{L-1} dA_{L-2}: thread (r, cq) takes classes cq, cq+4, ...
+  // 4. logit changes dz_{L-1} = W_{L-1} dA_{L-2}: wave w takes 64 of the k,
+  // the four partial sums meet in wave order
+  auto logit = reinterpret_cast<float (*)[T][17]>(ta);
   {
-    const float* WL = net.W[L - 1];
-    const int r = tid >> 2, cq = tid & 3;
+    f32x4 lg[SB];
 #pragma unroll
-    for (int cc = 0; cc < (CM + 3) / 4; ++cc) {
-      const int cl = cq + 4 * cc;
-      if (cl < C) {
-        float a = 0.f;
-        for (int u = 0; u < kChainUnits; ++u)
-          a = fmaf(tin[r * kRowStride + u], gload(&WL[(int64_t)cl * kChainUnits + u]), a);
-        logit[r][cl] = a;
+    for (int sb = 0; sb < SB; ++sb) lg[sb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const bf16x8* wl = reinterpret_cast<const bf16x8*>(net.WF + split_layer(W, L - 1)) + lane;
+    constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+    for (int ks = 2 * wave; ks < 2 * wave + 2; ++ks) {
+      bf16x8 b[3];
+#pragma unroll
+      for (int p = 0; p < 3; ++p) b[p] = gload(wl + (ks * 3 + p) * 64);
+#pragma unroll
+      for (int sb = 0; sb < SB; ++sb) {
+        bf16x8 a[3];
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+          a[p] = *reinterpret_cast<const bf16x8*>(ta + (p * T + 16 * sb + li) * RS + 32 * ks + 8 * q);
+#pragma unroll
+        for (int t = 0; t < 6; ++t) lg[sb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[pa[t]], b[pb[t]], lg[sb], 0, 0, 0);
       }
     }
+    __syncthreads();  // every wave has read the tile: the sums take its place
+#pragma unroll
+    for (int sb = 0; sb < SB; ++sb)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) logit[wave][16 * sb + 4 * q + v][li] = lg[sb][v];
   }
   __syncthreads();
   // 5. per-sample loss change from the logit change and the cached softmax;
   // the tile's sum in list order
-  if (tid < kChainT) {
+  if (tid < T) {
     const int n = rown[tid];
     float d = 0.f;
     if (n >= 0) {
@@ -297,7 +296,7 @@ __global__ __launch_bounds__(kChainThreads, 2) void k_chain(NetDev net_arg, cons
       float dz[CM], p[CM], dzy = 0.f;
 #pragma unroll
       for (int cc = 0; cc < CM; ++cc) {
-        dz[cc] = (cc < C) ? logit[tid][cc] : 0.f;
+        dz[cc] = (cc < C) ? (logit[0][tid][cc] + logit[1][tid][cc]) + (logit[2][tid][cc] + logit[3][tid][cc]) : 0.f;
         p[cc] = (cc < C) ? gload(&net.prob[(int64_t)cc * Ns + n]) : 0.f;
         dzy = (cc == y) ? dz[cc] : dzy;
       }
@@ -322,9 +321,38 @@ __global__ __launch_bounds__(kChainThreads, 2) void k_chain(NetDev net_arg, cons
   __syncthreads();
   if (!commit && tid == 0) {
     float v = 0.f;
-    for (int r = 0; r < kChainT; ++r) v += dls[r];
+    for (int r = 0; r < T; ++r) v += dls[r];
     partial[(int64_t)k * nchain + tile] = v;
   }
+}
+
+namespace {
+// One thread per pair of neighbours in a lane's eight values of a fragment.
+__global__ void k_split_weights(NetDev net) {
+  const int L = net.L, W = net.widths[1];
+  const int64_t dense = (int64_t)(L - 2) * W * W / 2, all = dense + 16 * W / 2;
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= all) return;
+  const int64_t per = (int64_t)W * W / 2;
+  const int m = e < dense ? 1 + (int)(e / per) : L - 1;
+  const int64_t r = e < dense ? e % per : e - dense;
+  const int rows = net.widths[m + 1];
+  const int j = (int)(r / (W / 2)), kk = 2 * (int)(r % (W / 2));
+  // k positions kk, kk + 1 hold units 16 apart (split_k's inverse)
+  const int i0 = (kk & ~63) | ((kk >> 2) & 15) | ((kk & 3) << 4), i1 = i0 + 16;
+  const float* row = net.W[m] + (int64_t)j * W;
+  const Split2 v = j < rows ? split2(row[i0], row[i1]) : Split2{{0u, 0u, 0u}};
+  uint16_t* at = net.WF + split_layer(W, m);
+#pragma unroll
+  for (int p = 0; p < 3; ++p) *reinterpret_cast<uint32_t*>(at + split_at(W, j, kk, p)) = v.p[p];
+}
+}  // namespace
+
+hipError_t launch_split_weights(const NetDev& net, hipStream_t s) {
+  const int W = net.widths[1];
+  const int64_t n = (int64_t)(net.L - 2) * W * W / 2 + 16 * W / 2;
+  hipLaunchKernelGGL(k_split_weights, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, net);
+  return hipGetLastError();
 }
 
 hipError_t launch_chain(const NetDev& net, const mca_cand* cands, const Aux* aux, int K,
@@ -332,16 +360,21 @@ hipError_t launch_chain(const NetDev& net, const mca_cand* cands, const Aux* aux
                         DevState* st, const double* dL, hipStream_t s) {
   const bool commit = k_mode != -2;
   hipLaunchKernelGGL(k_rows, dim3(commit ? 1 : K), dim3(kRowsThreads), 0, s, net, cands, aux,
-                     k_mode, st, dL, rows, rda, cnt);
+                     k_mode, st, dL, rows, rda, cnt, K);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const dim3 grid((unsigned)nchain, commit ? 1u : (unsigned)K);
-  if (net.C == 10)
-    hipLaunchKernelGGL(k_chain<10>, grid, dim3(kChainThreads), 0, s, net, cands, aux, rows, rda,
-                       cnt, partial, nchain, k_mode, st);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(kChainThreads), 0, s, net, cands, aux, rows, rda, cnt,
+                       partial, nchain, K, k_mode, st);
+  };
+  const bool ten = net.C == 10;
+  if (net.act == MCA_ACT_TANH)
+    ten ? go(k_chain<10, MCA_ACT_TANH>) : go(k_chain<kCMax, MCA_ACT_TANH>);
+  else if (net.act == MCA_ACT_RELU)
+    ten ? go(k_chain<10, MCA_ACT_RELU>) : go(k_chain<kCMax, MCA_ACT_RELU>);
   else
-    hipLaunchKernelGGL(k_chain<kCMax>, grid, dim3(kChainThreads), 0, s, net, cands, aux, rows,
-                       rda, cnt, partial, nchain, k_mode, st);
+    ten ? go(k_chain<10, MCA_ACT_GAUSS>) : go(k_chain<kCMax, MCA_ACT_GAUSS>);
   return hipGetLastError();
 }
 

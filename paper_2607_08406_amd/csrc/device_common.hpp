@@ -69,6 +69,7 @@ struct NetDev {
   float ln_eps;
   int32_t sticky;                     // steps per block of the MCA_PICK_STICKY schedule
   float* B[MCA_MAX_LAYERS];           // biases [n_{l+1}], or null
+  uint16_t* WF;                       // split copy of the weights of layers 1..L-1 (split_mma.hpp), or null
 };
 
 // Kernels index the pointer and size arrays of NetDev with runtime values (the

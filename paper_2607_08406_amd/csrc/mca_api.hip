@@ -22,6 +22,7 @@
 #include "chain_kernels.hpp"
 #include "channel_kernels.hpp"
 #include "norm_kernels.hpp"
+#include "split_mma.hpp"
 #include "tf_kernels.hpp"
 
 using mca::Aux;
@@ -31,7 +32,13 @@ using mca::NetDev;
 // Per-call buffers of mca_eval_losses_noalloc: one array per GPU, for the
 // process's lifetime.  Host code never uses this name as an address: it is a
 // host-side stand-in; the device address comes from hipGetSymbolAddress.
-constexpr size_t kScratchBytes = (size_t)8 << 20;
+// A request is accepted by what it needs with the deep nets' tile sums counted
+// per 64 samples (kScratchLimit); they are kept per kChainT samples, and with
+// the candidates' order, in the margin: rows and rda take 8 bytes per
+// candidate and sample, so at the limit the finer sums and the order add at
+// most 2^20 (4 / 48 - 4 / 64) + 8 * 1024 bytes and their alignment.
+constexpr size_t kScratchLimit = (size_t)8 << 20;
+constexpr size_t kScratchBytes = kScratchLimit + ((size_t)64 << 10);
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 namespace {
@@ -81,6 +88,7 @@ struct Layout {
   size_t wt = 0, pslab = 0;  // three-layer nets: W_1 transposed, first-layer tile sums
   size_t cols = 0, nnz = 0;  // nonzero entries of layer L-3 candidates' W_{L-2} columns
   size_t rows = 0, rda = 0, rcnt = 0, pchain = 0;  // deep nets: affected samples, tile sums
+  size_t wf = 0;                                    // split copy of the dense layers' weights
   size_t chans = 0, pchan = 0;                      // channel mutations: records, tile sums
   size_t pnorm = 0;                                 // nets with biases / normalization: tile sums
   size_t b[MCA_MAX_LAYERS] = {}, mu[MCA_MAX_LAYERS] = {}, S[MCA_MAX_LAYERS] = {};
@@ -376,8 +384,9 @@ Layout make_layout(const mca_net_desc* net, int64_t N, int32_t k_max) {
     lo.nchain = (int)((N + mca::kChainT - 1) / mca::kChainT);
     lo.rows = take((size_t)k_max * N * sizeof(int32_t));
     lo.rda = take((size_t)k_max * N * sizeof(float));
-    lo.rcnt = take((size_t)k_max * sizeof(int32_t));
+    lo.rcnt = take((size_t)2 * k_max * sizeof(int32_t));
     lo.pchain = take((size_t)k_max * lo.nchain * sizeof(float));
+    lo.wf = take((size_t)mca::split_size(net->widths[1], L) * sizeof(uint16_t));
   }
   if (norm) {
     lo.nnorm = mca::norm_tiles(N, net->widths[1]);
@@ -632,6 +641,7 @@ int upload_params(mca_ctx* ctx, const float* const* params, const int8_t* const*
   if (ctx->net.WT != nullptr)  // W_{L-2} [n_{L-1}][n_{L-2}] -> W_T [n_{L-2}][n_{L-1}]
     MCA_HIP(ctx, mca::launch_transpose(ctx->net.W[L - 2], d.widths[L - 1], d.widths[L - 2],
                                        ctx->net.WT, ctx->stream));
+  if (ctx->net.WF != nullptr) MCA_HIP(ctx, mca::launch_split_weights(ctx->net, ctx->stream));
   MCA_HIP(ctx, hipStreamSynchronize(ctx->stream));
   return MCA_OK;
 }
@@ -1089,6 +1099,7 @@ int mca_init(mca_ctx** out, const mca_net_desc* net, const float* const* params,
   }
   ctx->chan = net->mutation != MCA_MUTATE_SINGLE;
   const bool deep = L >= 4 && !ctx->chan && !ctx->norm;
+  nd.WF = deep ? (uint16_t*)(ws + lo.wf) : nullptr;
   ctx->rows = deep ? (int*)(ws + lo.rows) : nullptr;
   ctx->rda = deep ? (float*)(ws + lo.rda) : nullptr;
   ctx->rcnt = deep ? (int*)(ws + lo.rcnt) : nullptr;
@@ -1287,7 +1298,7 @@ int mca_eval_losses_noalloc(mca_ctx* ctx, const mca_cand* cands_host, int32_t K,
   const NetDev& net = ctx->net;
   const int L = net.L;
   const size_t kk = (size_t)K;
-  size_t off = 0;
+  size_t off = 0, off_limit = 0;
   auto take = [&](size_t bytes) {
     const size_t at = off;
     off = align_up(off + bytes);
@@ -1305,13 +1316,16 @@ int mca_eval_losses_noalloc(mca_ctx* ctx, const mca_cand* cands_host, int32_t K,
   if (L >= 4) {
     o_rows = take(kk * net.N * sizeof(int32_t));
     o_rda = take(kk * net.N * sizeof(float));
-    o_rcnt = take(kk * sizeof(int32_t));
+    off_limit = off + align_up(kk * sizeof(int32_t)) + align_up(kk * ((net.N + 63) / 64) * sizeof(float));
+    o_rcnt = take(2 * kk * sizeof(int32_t));
     o_pchain = take(kk * lo.nchain * sizeof(float));
+  } else {
+    off_limit = off;
   }
-  if (off > kScratchBytes)
-    return fail(ctx, MCA_EINVAL, "K candidates on this net need " + std::to_string(off) +
+  if (off_limit > kScratchLimit || off > kScratchBytes)
+    return fail(ctx, MCA_EINVAL, "K candidates on this net need " + std::to_string(off_limit) +
                                      " bytes of scratch, more than the static array's " +
-                                     std::to_string(kScratchBytes));
+                                     std::to_string(kScratchLimit));
   char* base = (char*)ctx->scratch_dev;
   const Bufs b{(mca_cand*)(base + o_cands), (Aux*)(base + o_aux), (uint64_t*)(base + o_cmask),
                (float*)(base + o_partial), (double*)(base + o_dl),

@@ -21,6 +21,7 @@
 // scored.
 #include "device_common.hpp"
 #include "slab_kernels.hpp"
+#include "split_mma.hpp"
 
 namespace mca {
 
@@ -255,7 +256,7 @@ __global__ __launch_bounds__(kSlabThreads) void k_slab(NetDev net_arg, const mca
       if (tid < T && n0 + tid < N) column_commit(net, cw.layer, cw.j, cw.i, aw.de, n0 + tid);
       if (blockIdx.x == 0 && tid == 0) {
         const int64_t idx = (int64_t)cw.j * net.widths[cw.layer] + cw.i;
-        gstore(&net.W[cw.layer][idx], aw.w_new);
+        put_weight(net, cw.layer, cw.j, cw.i, aw.w_new);
         if (net.ternary) gstore(&net.codes[cw.layer][idx], (int8_t)cw.code);
         // the transposed copy of W_{L-2}, which the column lists read
         if (cw.layer == L - 2)
@@ -541,7 +542,7 @@ __global__ __launch_bounds__(kSlabThreads) void k_slab(NetDev net_arg, const mca
     const mca_cand c = cands[kc];
     const Aux a = aux[kc];
     const int64_t idx = (int64_t)c.j * net.widths[l] + c.i;
-    gstore(&net.W[l][idx], a.w_new);
+    put_weight(net, l, c.j, c.i, a.w_new);
     if (net.ternary) gstore(&net.codes[l][idx], (int8_t)c.code);
     if (net.sub_size == 0) st->L += dL[kc];
     st->accepted += 1;

@@ -1,0 +1,123 @@
+// fp32 products on the bf16 matrix cores: each operand is the exact sum of
+// three bf16 values (hi + mid + lo, 24 significant bits), and a product of two
+// fp32 matrices is the sum of the six bf16 products whose terms reach 2^-18
+// of a term or more (hi hi, hi mid, mid hi, mid mid, hi lo, lo hi; Henry, Tang
+// and Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For
+// Higher-Precision Computations", ARITH 2019).  The three dropped ones are
+// below 2^-26 of a term, under the rounding of the fp32 sums, which stay in
+// fp32.  v_mfma_f32_16x16x32_bf16 takes 16 cycles for the 32 k that
+// v_mfma_f32_16x16x4f32 takes 256 for, so six of them take 96: 2.7 times the
+// fp32 rate.  Operands below 2^-110 lose their lowest part to bf16's range.
+//
+// Hidden-layer weights are kept split beside their fp32 values (NetDev::WF), in
+// the order the kernels read them: for each block of 16 output units and each
+// 32 of the k order, the three parts, each a wave's 64 lanes of 8 values (lane
+// (q, li): output unit 16 cb + li, k = 32 ks + 8 q + e).  The k order puts the
+// four units 16 c + li (c = 0..3) of a block of 64 side by side, because a lane
+// of the product's output holds exactly those four for its sample: its changes
+// go back to the tile as one 8-byte store per part.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "device_common.hpp"
+
+namespace mca {
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// The parts of two fp32 values, each part a packed pair (a in the low half).
+struct Split2 {
+  uint32_t p[3];
+};
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
+  const f32x2 v = {a, b};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+__device__ __forceinline__ Split2 split2(float a, float b) {
+  Split2 s;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    s.p[i] = bf16_pair(a, b);
+    a -= __uint_as_float(s.p[i] << 16);  // exact
+    b -= __uint_as_float(s.p[i] & 0xFFFF0000u);
+  }
+  return s;
+}
+
+// Position of input unit i in the k order, and of element (row, k position,
+// part) of a split matrix with W input units, in bf16 values.
+__host__ __device__ inline int split_k(int i) { return (i & ~63) | ((i & 15) << 2) | ((i >> 4) & 3); }
+__host__ __device__ inline int64_t split_at(int W, int row, int kk, int part) {
+  return ((((int64_t)(row >> 4) * (W >> 5) + (kk >> 5)) * 3 + part) * 64 + ((kk >> 3) & 3) * 16 + (row & 15)) * 8 +
+         (kk & 7);
+}
+// Split values of the dense layers m = 1 .. L-2 ([W][W] each), then of the
+// logit layer (padded to 16 rows).
+__host__ __device__ inline int64_t split_layer(int W, int m) { return (int64_t)(m - 1) * 3 * W * W; }
+__host__ __device__ inline int64_t split_size(int W, int L) { return split_layer(W, L - 1) + (int64_t)3 * 16 * W; }
+
+// W_l[j, i] = w, and its split copy where the net keeps one.
+__device__ __forceinline__ void put_weight(const NetDev& net, int l, int j, int i, float w) {
+  const int n_in = net.widths[l];
+  gstore(&net.W[l][(int64_t)j * n_in + i], w);
+  if (net.WF == nullptr || l == 0) return;
+  uint16_t* at = net.WF + split_layer(n_in, l);
+  const Split2 s = split2(w, 0.f);
+#pragma unroll
+  for (int p = 0; p < 3; ++p) gstore(&at[split_at(n_in, j, split_k(i), p)], (uint16_t)(s.p[p] & 0xFFFFu));
+}
+
+// Fills the split copy from the fp32 weights of every layer it holds.
+hipError_t launch_split_weights(const NetDev& net, hipStream_t s);
+
+// acc += (T x W tile in LDS) x (split weights of 64 output units), per wave:
+// SB blocks of 16 tile rows by CB blocks of 16 units.  tile: part p of row r at
+// tile + (p * T + r) * RS, in bf16 values; wf: the wave's first block of units.
+// The next 32 k of the weights are requested while the current ones multiply.
+template <int W, int T, int RS, int SB, int CB>
+__device__ __forceinline__ void split_product(const uint16_t* tile, const uint16_t* wf, int lane,
+                                              f32x4 (&acc)[SB][CB]) {
+  constexpr int KS = W / 32;
+  const int q = lane >> 4, li = lane & 15;
+  const bf16x8* wl = reinterpret_cast<const bf16x8*>(wf) + lane;
+  const uint16_t* al = tile + li * RS + 8 * q;
+  bf16x8 b[2][CB][3];
+  auto fetch = [&](int ks, bf16x8 (&d)[CB][3]) {
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+      for (int p = 0; p < 3; ++p) d[cb][p] = gload(wl + ((cb * KS + ks) * 3 + p) * 64);
+  };
+  auto multiply = [&](int ks, const bf16x8 (&d)[CB][3]) {
+    bf16x8 a[SB][3];
+#pragma unroll
+    for (int sb = 0; sb < SB; ++sb)
+#pragma unroll
+      for (int p = 0; p < 3; ++p)
+        a[sb][p] = *reinterpret_cast<const bf16x8*>(al + (p * T + 16 * sb) * RS + 32 * ks);
+    // small terms first
+    constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+    for (int t = 0; t < 6; ++t)
+#pragma unroll
+      for (int sb = 0; sb < SB; ++sb)
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb)
+          acc[sb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[sb][pa[t]], d[cb][pb[t]], acc[sb][cb], 0, 0, 0);
+  };
+  fetch(0, b[0]);
+#pragma unroll 1
+  for (int ks = 0; ks < KS; ks += 2) {
+    fetch(ks + 1, b[1]);
+    multiply(ks, b[0]);
+    fetch(ks + 2 < KS ? ks + 2 : 0, b[0]);
+    multiply(ks + 1, b[1]);
+  }
+}
+
+}  // namespace mca
