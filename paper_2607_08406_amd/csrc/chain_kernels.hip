@@ -21,6 +21,8 @@
 // and moves every cached field by its change.
 //
 // The hidden layers touched here must be exactly kChainUnits wide.
+#include <type_traits>
+
 #include "device_common.hpp"
 #include "chain_kernels.hpp"
 #include "split_mma.hpp"
@@ -31,6 +33,7 @@ namespace {
 
 constexpr int kRowsThreads = 1024;
 constexpr int kChainThreads = 256;
+constexpr int kCommitT = 16;  // listed samples per block of a commit
 static_assert(kChainThreads == kChainUnits, "a wave takes 64 output units");
 
 }  // namespace
@@ -130,13 +133,20 @@ __global__ __launch_bounds__(kRowsThreads) void k_rows(NetDev net_arg, const mca
 // would halve the weights' reads but leave one block; 32 rows read too much.
 // 784-24x256-10, 32 candidates on 4096 samples: 2.82 -> 1.33 ms a step against
 // fp32 products on 64-row tiles, the same error against 64 bits (2.4e-7).
-template <int CM, int ACT>
-__global__ __launch_bounds__(kChainThreads, 2) void k_chain(NetDev net_arg, const mca_cand* cands,
+//
+// T: rows of a block.  A commit has one candidate's rows: its time is the
+// latency of one tile's layers one after another, all blocks at the same layer
+// at once, so that every read of the weights is the first in its L2.  It takes
+// 16 rows (4096 samples: a tile for every CU) and requests a whole layer ahead
+// (its one block a CU has the registers).  Each row's sums are the same bits
+// at every T.  784-24x256-10 on 4096 samples: 199 -> 96 us a commit on average.
+template <int CM, int ACT, int T>
+__global__ __launch_bounds__(kChainThreads, T == kCommitT ? 1 : 2) void k_chain(NetDev net_arg, const mca_cand* cands,
                                                          const Aux* aux, const int* rows,
                                                          const float* rda, const int* cnt,
                                                          float* partial, int nchain, int K,
                                                          int k_mode, const DevState* st) {
-  constexpr int T = kChainT, SB = T / 16, W = kChainUnits, RS = W + 8;
+  constexpr int SB = T / 16, W = kChainUnits, RS = W + 8;
   __shared__ NetDev net;
   stage_net(net, net_arg);
   // activation changes in three bf16 parts, [part][sample][unit in k order],
@@ -186,7 +196,7 @@ __global__ __launch_bounds__(kChainThreads, 2) void k_chain(NetDev net_arg, cons
   // li), element v -> row 16 sb + 4 q + v, unit 64 w + 16 cb + li).  A lane's
   // four rows are four consecutive samples whenever the tile lists every
   // sample (a candidate past the first layer): one 16-byte load each then
-  // (16-byte aligned: the tile starts at a multiple of 48).
+  // (16-byte aligned: the tile starts at a multiple of 16).
   auto fields = [&](int m, f32x4 (&zc)[SB][4]) {
     const float* Zm = net.Z[m];
 #pragma unroll
@@ -226,6 +236,15 @@ __global__ __launch_bounds__(kChainThreads, 2) void k_chain(NetDev net_arg, cons
       }
   };
   f32x4 acc[SB][4], zc[SB][4];
+  // the split weights of the wave's 64 output units of layer m (s + 1 <= L - 2)
+  auto weights = [&](int m) { return net.WF + split_layer(W, m) + (int64_t)4 * wave * (W / 32) * 3 * 512; };
+  constexpr bool kAhead = T == kCommitT;
+  bf16x8 held[kAhead ? W / 32 : 1][4][3];
+  (void)held;
+  if constexpr (kAhead) {
+#pragma unroll
+    for (int ks = 0; ks < W / 32; ++ks) fetch_weights<W>(weights(s + 1), lane, ks, held[ks]);
+  }
   // 2. the rank-1 update: dz_s = da W_s[:, j]
   {
     fields(s, zc);
@@ -250,7 +269,10 @@ __global__ __launch_bounds__(kChainThreads, 2) void k_chain(NetDev net_arg, cons
     for (int sb = 0; sb < SB; ++sb)
 #pragma unroll
       for (int cb = 0; cb < 4; ++cb) acc[sb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    split_product<W, T, RS, SB, 4>(ta, net.WF + split_layer(W, m) + (int64_t)4 * wave * (W / 32) * 3 * 512, lane, acc);
+    if constexpr (kAhead)
+      split_product_ahead<W, T, RS>(ta, weights(m < L - 2 ? m + 1 : m), held, lane, acc);
+    else
+      split_product<W, T, RS>(ta, weights(m), lane, acc);
     __syncthreads();
     finish(m, acc, zc);
     __syncthreads();
@@ -363,18 +385,24 @@ hipError_t launch_chain(const NetDev& net, const mca_cand* cands, const Aux* aux
                      k_mode, st, dL, rows, rda, cnt, K);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const dim3 grid((unsigned)nchain, commit ? 1u : (unsigned)K);
-  auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, grid, dim3(kChainThreads), 0, s, net, cands, aux, rows, rda, cnt,
-                       partial, nchain, K, k_mode, st);
+  auto go = [&](auto kernel, int64_t tiles) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)tiles, commit ? 1u : (unsigned)K), dim3(kChainThreads), 0, s,
+                       net, cands, aux, rows, rda, cnt, partial, nchain, K, k_mode, st);
   };
-  const bool ten = net.C == 10;
-  if (net.act == MCA_ACT_TANH)
-    ten ? go(k_chain<10, MCA_ACT_TANH>) : go(k_chain<kCMax, MCA_ACT_TANH>);
-  else if (net.act == MCA_ACT_RELU)
-    ten ? go(k_chain<10, MCA_ACT_RELU>) : go(k_chain<kCMax, MCA_ACT_RELU>);
-  else
-    ten ? go(k_chain<10, MCA_ACT_GAUSS>) : go(k_chain<kCMax, MCA_ACT_GAUSS>);
+  auto pick = [&](auto cm, auto act) {
+    constexpr int CM = decltype(cm)::value, ACT = decltype(act)::value;
+    if (commit)
+      go(k_chain<CM, ACT, kCommitT>, (net.N + kCommitT - 1) / kCommitT);
+    else
+      go(k_chain<CM, ACT, kChainT>, nchain);
+  };
+  auto by_act = [&](auto cm) {
+    if (net.act == MCA_ACT_TANH) pick(cm, std::integral_constant<int, MCA_ACT_TANH>{});
+    else if (net.act == MCA_ACT_RELU) pick(cm, std::integral_constant<int, MCA_ACT_RELU>{});
+    else pick(cm, std::integral_constant<int, MCA_ACT_GAUSS>{});
+  };
+  if (net.C == 10) by_act(std::integral_constant<int, 10>{});
+  else by_act(std::integral_constant<int, kCMax>{});
   return hipGetLastError();
 }
 

@@ -75,48 +75,64 @@ __device__ __forceinline__ void put_weight(const NetDev& net, int l, int j, int 
 // Fills the split copy from the fp32 weights of every layer it holds.
 hipError_t launch_split_weights(const NetDev& net, hipStream_t s);
 
-// acc += (T x W tile in LDS) x (split weights of 64 output units), per wave:
-// SB blocks of 16 tile rows by CB blocks of 16 units.  tile: part p of row r at
-// tile + (p * T + r) * RS, in bf16 values; wf: the wave's first block of units.
-// The next 32 k of the weights are requested while the current ones multiply.
+// The 32 k of step ks of the weights of a wave's CB blocks of 16 output units.
+template <int W, int CB>
+__device__ __forceinline__ void fetch_weights(const uint16_t* wf, int lane, int ks, bf16x8 (&d)[CB][3]) {
+  const bf16x8* wl = reinterpret_cast<const bf16x8*>(wf) + lane;
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+    for (int p = 0; p < 3; ++p) d[cb][p] = gload(wl + ((cb * (W / 32) + ks) * 3 + p) * 64);
+}
+
+// acc += rows 16 sb + li of the tile (part p of row r at tile + (p * T + r) *
+// RS, in bf16 values) times the weights b, over step ks; small terms first.
+template <int T, int RS, int SB, int CB>
+__device__ __forceinline__ void multiply_step(const uint16_t* tile, int lane, int ks, const bf16x8 (&b)[CB][3],
+                                              f32x4 (&acc)[SB][CB]) {
+  const uint16_t* al = tile + (lane & 15) * RS + 8 * (lane >> 4) + 32 * ks;
+  bf16x8 a[SB][3];
+#pragma unroll
+  for (int sb = 0; sb < SB; ++sb)
+#pragma unroll
+    for (int p = 0; p < 3; ++p) a[sb][p] = *reinterpret_cast<const bf16x8*>(al + (p * T + 16 * sb) * RS);
+  constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+  for (int t = 0; t < 6; ++t)
+#pragma unroll
+    for (int sb = 0; sb < SB; ++sb)
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb)
+        acc[sb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[sb][pa[t]], b[cb][pb[t]], acc[sb][cb], 0, 0, 0);
+}
+
+// acc += (T x W tile) x (weights wf of the wave's 16 CB output units), the
+// next step's weights requested while the current ones multiply.
 template <int W, int T, int RS, int SB, int CB>
 __device__ __forceinline__ void split_product(const uint16_t* tile, const uint16_t* wf, int lane,
                                               f32x4 (&acc)[SB][CB]) {
   constexpr int KS = W / 32;
-  const int q = lane >> 4, li = lane & 15;
-  const bf16x8* wl = reinterpret_cast<const bf16x8*>(wf) + lane;
-  const uint16_t* al = tile + li * RS + 8 * q;
-  bf16x8 b[2][CB][3];
-  auto fetch = [&](int ks, bf16x8 (&d)[CB][3]) {
-#pragma unroll
-    for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-      for (int p = 0; p < 3; ++p) d[cb][p] = gload(wl + ((cb * KS + ks) * 3 + p) * 64);
-  };
-  auto multiply = [&](int ks, const bf16x8 (&d)[CB][3]) {
-    bf16x8 a[SB][3];
-#pragma unroll
-    for (int sb = 0; sb < SB; ++sb)
-#pragma unroll
-      for (int p = 0; p < 3; ++p)
-        a[sb][p] = *reinterpret_cast<const bf16x8*>(al + (p * T + 16 * sb) * RS + 32 * ks);
-    // small terms first
-    constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
-#pragma unroll
-    for (int t = 0; t < 6; ++t)
-#pragma unroll
-      for (int sb = 0; sb < SB; ++sb)
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb)
-          acc[sb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[sb][pa[t]], d[cb][pb[t]], acc[sb][cb], 0, 0, 0);
-  };
-  fetch(0, b[0]);
+  bf16x8 b0[CB][3], b1[CB][3];
+  fetch_weights<W>(wf, lane, 0, b0);
 #pragma unroll 1
   for (int ks = 0; ks < KS; ks += 2) {
-    fetch(ks + 1, b[1]);
-    multiply(ks, b[0]);
-    fetch(ks + 2 < KS ? ks + 2 : 0, b[0]);
-    multiply(ks + 1, b[1]);
+    fetch_weights<W>(wf, lane, ks + 1, b1);
+    multiply_step<T, RS>(tile, lane, ks, b0, acc);
+    fetch_weights<W>(wf, lane, ks + 2 < KS ? ks + 2 : 0, b0);
+    multiply_step<T, RS>(tile, lane, ks + 1, b1, acc);
+  }
+}
+
+// The same with a whole layer's weights in registers: b holds wf's on entry,
+// and those of `next` are requested step by step in their place.
+template <int W, int T, int RS, int SB, int CB>
+__device__ __forceinline__ void split_product_ahead(const uint16_t* tile, const uint16_t* next,
+                                                    bf16x8 (&b)[W / 32][CB][3], int lane,
+                                                    f32x4 (&acc)[SB][CB]) {
+#pragma unroll
+  for (int ks = 0; ks < W / 32; ++ks) {
+    multiply_step<T, RS>(tile, lane, ks, b[ks], acc);
+    fetch_weights<W>(next, lane, ks, b[ks]);
   }
 }
 
