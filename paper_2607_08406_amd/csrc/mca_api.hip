@@ -391,6 +391,10 @@ Layout make_layout(const mca_net_desc* net, int64_t N, int32_t k_max) {
   if (norm) {
     lo.nnorm = mca::norm_tiles(N, net->widths[1]);
     lo.pnorm = take((size_t)k_max * lo.nnorm * sizeof(float));
+    lo.rows = take((size_t)k_max * N * sizeof(int32_t));
+    lo.rda = take((size_t)k_max * N * sizeof(float));
+    lo.rcnt = take((size_t)2 * k_max * sizeof(int32_t));
+    lo.wf = take((size_t)mca::split_size(net->widths[1], L) * sizeof(uint16_t));
   }
   if (net->mutation != MCA_MUTATE_SINGLE) {
     lo.nchan = mca::channel_tiles(N, net->widths[1]);
@@ -741,7 +745,8 @@ hipError_t prepare_dev(mca_ctx* ctx, int K) { return prepare_into(ctx, ctx_bufs(
 // `listed`: the layer L-3 column lists came with the proposal.
 hipError_t eval_into(mca_ctx* ctx, const NetDev& net, const Bufs& b, int K, bool listed = false) {
   if (ctx->norm)
-    return mca::launch_norm(net, ctx->nd, b.cands, b.aux, K, ctx->pnorm, ctx->lo.nnorm, -2,
+    return mca::launch_norm(net, ctx->nd, b.cands, b.aux, K, ctx->rows, ctx->rda, ctx->rcnt, ctx->pnorm,
+                            ctx->lo.nnorm, -2,
                             ctx->st, b.dl, ctx->stream);
   if (ctx->chan)
     return mca::launch_channel(net, ctx->chans, b.aux, K, ctx->pchan, ctx->lo.nchan, -2,
@@ -811,7 +816,8 @@ hipError_t select_all(mca_ctx* ctx, const NetDev& net, int K, bool do_select, in
 // kernel applies only the candidates of the layers it scores.
 hipError_t commit_all(mca_ctx* ctx, const NetDev& net, int k, int K) {
   if (ctx->norm)
-    return mca::launch_norm(net, ctx->nd, ctx->cands, ctx->aux, 0, ctx->pnorm, ctx->lo.nnorm, k,
+    return mca::launch_norm(net, ctx->nd, ctx->cands, ctx->aux, 0, ctx->rows, ctx->rda, ctx->rcnt,
+                            ctx->pnorm, ctx->lo.nnorm, k,
                             ctx->st, ctx->dl, ctx->stream);
   if (ctx->chan)
     return mca::launch_channel(net, ctx->chans, ctx->aux, 0, ctx->pchan, ctx->lo.nchan, k,
@@ -1099,10 +1105,11 @@ int mca_init(mca_ctx** out, const mca_net_desc* net, const float* const* params,
   }
   ctx->chan = net->mutation != MCA_MUTATE_SINGLE;
   const bool deep = L >= 4 && !ctx->chan && !ctx->norm;
-  nd.WF = deep ? (uint16_t*)(ws + lo.wf) : nullptr;
-  ctx->rows = deep ? (int*)(ws + lo.rows) : nullptr;
-  ctx->rda = deep ? (float*)(ws + lo.rda) : nullptr;
-  ctx->rcnt = deep ? (int*)(ws + lo.rcnt) : nullptr;
+  const bool listed = deep || ctx->norm;  // kernels that list the samples a candidate moves
+  nd.WF = listed ? (uint16_t*)(ws + lo.wf) : nullptr;
+  ctx->rows = listed ? (int*)(ws + lo.rows) : nullptr;
+  ctx->rda = listed ? (float*)(ws + lo.rda) : nullptr;
+  ctx->rcnt = listed ? (int*)(ws + lo.rcnt) : nullptr;
   ctx->pchain = deep ? (float*)(ws + lo.pchain) : nullptr;
   ctx->chans = ctx->chan ? (mca_channel*)(ws + lo.chans) : nullptr;
   ctx->pchan = ctx->chan ? (float*)(ws + lo.pchan) : nullptr;

@@ -12,30 +12,22 @@
 //   values; then da = phi(h + dh) - phi(h) (dphi), and the next field's change
 //   W_m da on the matrix cores (v_mfma_f32_16x16x4f32); the logits' change
 //   gives each sample's loss change with the cached softmax (ce_change).
-// A block takes T = 16384 / W consecutive samples of one candidate and keeps
-// their changes in an LDS tile [T][W + 4]; the normalization pass gives each
-// sample TPR = 256 / T threads (64 units each) and adds across them with a
-// fixed butterfly.  The commit runs the same arithmetic, stores the moved
-// fields and recomputes each moved sample's statistics from them; a second
-// kernel then writes the parameter.
-#include "device_common.hpp"
+// k_norm_rows lists, per candidate and in sample order, the samples the change
+// moves (a first-layer weight's input is zero on most: about 81 % of the images)
+// with the size of their move; a block of k_norm takes a tile of them
+// (dense_tile.hpp).  The row sums of the normalization add the lanes that hold
+// a row by a fixed butterfly, then the waves in order.  A net without
+// normalization starts at layer l+1, with the rank-1 term of the one moved
+// unit.  The commit runs the same arithmetic, stores the moved fields and
+// recomputes each moved sample's statistics from them.
+#include <type_traits>
+
+#include "dense_tile.hpp"
 #include "norm_kernels.hpp"
 
 namespace mca {
 
 namespace {
-
-constexpr int kNThreads = 256;
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-
-// Sum over the TPR consecutive lanes of a row group (a butterfly: the same
-// bits in every lane of the group).
-template <int TPR>
-__device__ __forceinline__ float group_sum(float v) {
-#pragma unroll
-  for (int o = 1; o < TPR; o <<= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
 
 __device__ __forceinline__ float inv_sqrt(float s) { return 1.0f / sqrtf(s); }
 
@@ -48,239 +40,282 @@ __device__ __forceinline__ float hidden_act(const NetDev& net, const NormDev& nd
   return act_fn(h, net.act, net.gamma);
 }
 
-// The activation change of hidden layer m from its field change dz (in the
-// tile, replaced in place): thread (r, p) takes units p + TPR x of row r.
-// A commit also stores the moved fields and, for a normalized layer, the
-// moved samples' new statistics.
-template <int W>
-__device__ void norm_pass(const NetDev& net, const NormDev& nd, int m, float* ta, int64_t n0,
-                          bool commit) {
-  constexpr int T = 16384 / W, RS = W + 4, TPR = kNThreads / T, UPT = W / TPR;
-  const int tid = threadIdx.x, r = tid / TPR, p = tid % TPR;
-  const int64_t n = n0 + r, Ns = net.Ns;
-  const bool live = n < net.N;  // rows past N read the padding and stay zero
-  float* Zm = net.Z[m];
-  float* row = ta + r * RS + p;  // this thread's units: row[TPR x], field z at zrow[TPR x Ns]
-  const float* zrow = Zm + (int64_t)p * Ns + n;
-  const int64_t zstep = (int64_t)TPR * Ns;
-  const int act = net.act;
-  const float gamma = net.gamma;
-  float new_mu = 0.f, new_S = 0.f;
-  // the moved rows (every pass below reads the fields again: they stay in cache)
-  float sa = 0.f;
-#pragma unroll 8
-  for (int x = 0; x < UPT; ++x) sa += fabsf(row[TPR * x]);
-  const bool moved = live && group_sum<TPR>(sa) != 0.f;  // the same in every lane of the row
-  if (net.ln && commit && moved) {
-    // a commit: the moved sample's statistics from its new fields z + dz
-    // (taken before the fields are overwritten)
-    float s = 0.f;
-#pragma unroll 8
-    for (int x = 0; x < UPT; ++x) s += gload(&zrow[zstep * x]) + row[TPR * x];
-    const float mu1 = group_sum<TPR>(s) * (1.0f / W);
-    float v = 0.f;
-#pragma unroll 8
-    for (int x = 0; x < UPT; ++x) {
-      const float c = (gload(&zrow[zstep * x]) + row[TPR * x]) - mu1;
-      v += c * c;
-    }
-    const float S1 = group_sum<TPR>(v) * (1.0f / W) + net.ln_eps;
-    if (p == 0) {
-      // stored after this sample's evaluation below has read the old ones
-      new_mu = mu1;
-      new_S = S1;
-    }
+}  // namespace
+
+// Block k (eval) or the committed candidate: the samples it moves, with the
+// change of the one field (normalized nets, logit-layer parameters) or
+// activation (a hidden unit without normalization) it enters by; cnt[k] their
+// number, cnt[K + r] the candidate that is r-th by layer.  An evaluation lists
+// the step's minibatch only.  A commit also stores the moved field where the
+// tile kernel starts past it, the parameter and the state.
+__global__ __launch_bounds__(kListThreads) void k_norm_rows(NetDev net_arg, NormDev nd, const mca_cand* cands,
+                                                            const Aux* aux, int k_mode, DevState* st,
+                                                            const double* dL, int* rows, float* vals,
+                                                            int* cnt, int K) {
+  __shared__ NetDev net;
+  stage_net(net, net_arg);
+  const bool commit = k_mode != -2;
+  const int k = commit ? ((k_mode >= 0) ? k_mode : st->chosen) : (int)blockIdx.x;
+  if (k < 0) return;
+  const mca_cand c = cands[k];
+  const int L = net.L, l = c.layer;
+  if (!commit && threadIdx.x < 64) {
+    const int r = layer_rank(cands, K, k, l);
+    if (threadIdx.x == 0) cnt[K + r] = k;
   }
-  if (net.ln) {
-    float s1 = 0.f;
-#pragma unroll 8
-    for (int x = 0; x < UPT; ++x) s1 += row[TPR * x];
-    const float dmu = group_sum<TPR>(s1) * (1.0f / W);
-    const float mu = gload(&nd.MU[m][n]), S = gload(&nd.S[m][n]);
-    float s2 = 0.f;
-#pragma unroll 8
-    for (int x = 0; x < UPT; ++x) {
-      const float c = gload(&zrow[zstep * x]) - mu, e = row[TPR * x] - dmu;
-      s2 += e * (c + c + e);
+  if (!commit && !aux[k].valid) {  // rejected unevaluated: selection gives +inf
+    if (threadIdx.x == 0) cnt[k] = 0;
+    return;
+  }
+  const float de = aux[k].de;
+  const int64_t N = net.N, Ns = net.Ns;
+  const bool is_bias = c.i == net.widths[l];
+  const bool unit = !net.ln && l < L - 1;  // lists the unit's activation change
+  float* zrow = net.Z[l] + (int64_t)c.j * Ns;
+  const int64_t sub0 = subset_start(net, commit ? 0 : st->t);
+  const int n_rows = list_rows(N, rows + (int64_t)k * N, vals + (int64_t)k * N, [&](int64_t n, bool in) {
+    const float x = is_bias ? 1.0f
+                            : (l == 0 ? gload(&net.XT[(int64_t)c.i * Ns + n]) : hidden_act(net, nd, l - 1, c.i, n));
+    float v = de * x;
+    if (unit) {
+      const float z = gload(&zrow[n]);
+      if (commit && in && v != 0.f) gstore(&zrow[n], z + v);
+      v = dphi(z, v, net.act, net.gamma);
     }
-    const float dS = group_sum<TPR>(s2) * (1.0f / W);
-    const float q0 = sqrtf(S), q1 = sqrtf(S + dS);
-    const float rs = 1.0f / q0, rs1 = 1.0f / q1;
-    const float f = ((dS * rs) * rs1) / (q0 + q1);
-#pragma unroll 4
-    for (int x = 0; x < UPT; ++x) {
-      const float z = gload(&zrow[zstep * x]), d = row[TPR * x];
-      const float c = z - mu, e = d - dmu;
-      const float dh = e * rs1 - c * f;
-      row[TPR * x] = moved ? dphi(c * rs, dh, act, gamma) : 0.f;
-      if (commit && moved) gstore(&Zm[(int64_t)(p + TPR * x) * Ns + n], z + d);
-    }
-    if (commit && moved && p == 0) {
-      gstore(&nd.MU[m][n], new_mu);
-      gstore(&nd.S[m][n], new_S);
-    }
-  } else {
-#pragma unroll 4
-    for (int x = 0; x < UPT; ++x) {
-      const float z = gload(&zrow[zstep * x]), d = row[TPR * x];
-      row[TPR * x] = moved ? dphi(z, d, act, gamma) : 0.f;
-      if (commit && moved) gstore(&Zm[(int64_t)(p + TPR * x) * Ns + n], z + d);
+    return (commit || in_subset(net, sub0, n)) ? v : 0.f;
+  });
+  if (threadIdx.x == 0) {
+    cnt[k] = n_rows;
+    if (commit) {
+      const float w = aux[k].w_new;
+      if (is_bias) gstore(&net.B[l][c.j], w);
+      else put_weight(net, l, c.j, c.i, w);
+      if (net.sub_size == 0) st->L += dL[k];  // a minibatch's change is not the loss's
+      st->accepted += 1;
     }
   }
 }
 
-}  // namespace
-
-// grid (ntiles, K) for an evaluation, (ntiles, 1) for a commit.
-template <int CM, int W>
-__global__ __launch_bounds__(kNThreads, (W >= 1024) ? 1 : 2) void k_norm(
-    NetDev net_arg, NormDev nd, const mca_cand* cands, const Aux* aux, float* partial,
-    int ntiles, int k_mode, DevState* st) {
-  constexpr int T = 16384 / W, SB = T / 16, UW = W / 4, CB = UW / 16, RS = W + 4;
-  constexpr int TPR = kNThreads / T;
-  static_assert(SB * CB == 16, "sixteen accumulator tiles per wave");
+// grid (ntiles, K) for an evaluation (row y: the y-th candidate by layer),
+// (ntiles, 1) for a commit.
+template <int W, int ACT, bool LN, bool commit>
+__global__ __launch_bounds__((Dense<W, commit>::threads), (Dense<W, commit>::blocks_per_cu)) void k_norm(
+    NetDev net_arg, NormDev nd, const mca_cand* cands, const int* rows, const float* vals,
+    const int* cnt, float* partial, int ntiles, int K, int k_mode, const DevState* st) {
+  typedef Dense<W, commit> D;
+  constexpr int T = D::T, SB = D::SB, H = D::H, NW = D::NW, RS = D::RS;
   __shared__ NetDev net;
   stage_net(net, net_arg);
-  __shared__ __attribute__((aligned(16))) float ta[T * RS];
-  __shared__ float incol[T];
-  __shared__ float logit[T][CM];
-  __shared__ float dls[T];
+  __shared__ __attribute__((aligned(16))) uint16_t ta[3 * T * RS];
+  __shared__ int rown[T];
+  __shared__ float rowv[T];
+  __shared__ __attribute__((aligned(16))) float red[2][NW][T];  // row sums by wave
+  __shared__ __attribute__((aligned(16))) float4 rowc[T];       // dmu, 1/sqrt S, 1/sqrt S', f
+  __shared__ float rowmu[T], dls[T];
+  auto logit = reinterpret_cast<float (*)[T][17]>(ta);
+  static_assert(sizeof(float) * NW * T * 17 <= sizeof(ta), "the logits' sums take the tile's place");
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const bool commit = k_mode != -2;
-  const int k = commit ? ((k_mode >= 0) ? k_mode : st->chosen) : (int)blockIdx.y;
+  const int tid = threadIdx.x;
+  const int k = commit ? ((k_mode >= 0) ? k_mode : st->chosen) : cnt[K + (int)blockIdx.y];
   if (k < 0) return;
-  const int tile = blockIdx.x;
-  if (!commit && !aux[k].valid) {  // rejected unevaluated: selection gives +inf
-    if (tid == 0) partial[(int64_t)k * ntiles + tile] = 0.f;
+  const int tile = blockIdx.x, n_rows = cnt[k], e0 = tile * T;
+  if (e0 >= n_rows) {
+    if (!commit && tid == 0) partial[(int64_t)k * ntiles + tile] = 0.f;
     return;
   }
   const mca_cand c = cands[k];
-  const float de = aux[k].de;
   const int L = net.L, l = c.layer;
-  const int C = (CM < kCMax) ? CM : net.C;
+  const float gamma = net.gamma;
   const int64_t N = net.N, Ns = net.Ns;
-  const int64_t n0 = (int64_t)tile * T;
-  const bool is_bias = c.i == net.widths[l];
-
-  // 1. the changed parameter's input on each sample (1 for a bias)
   if (tid < T) {
-    const int64_t n = n0 + tid;
-    float x = 0.f;
-    if (n < N)
-      x = is_bias ? 1.0f
-                  : (l == 0 ? gload(&net.XT[(int64_t)c.i * Ns + n]) : hidden_act(net, nd, l - 1, c.i, n));
-    incol[tid] = x;
+    const int e = e0 + tid;
+    rown[tid] = (e < n_rows) ? gload(&rows[(int64_t)k * N + e]) : -1;
+    rowv[tid] = (e < n_rows) ? gload(&vals[(int64_t)k * N + e]) : 0.f;
   }
   __syncthreads();
-  const int r4 = tid / TPR, cq = tid % TPR;  // logits: thread (row, class group)
+  D t;
+  t.init(rown);
   if (l == L - 1) {
     // a logit-layer parameter: only logit j moves
-#pragma unroll
-    for (int c0 = 0; c0 < CM; c0 += TPR) {
-      const int cl = c0 + cq;
-      if (cl < C) logit[r4][cl] = (cl == c.j) ? de * incol[r4] : 0.f;
-    }
+    for (int e = tid; e < T * 16; e += D::threads) logit[0][e >> 4][e & 15] = ((e & 15) == c.j) ? rowv[e >> 4] : 0.f;
   } else {
-    // 2. field change of layer l: column j
-    for (int e = tid; e < T * W; e += kNThreads) {
-      const int r = e / W, u = e - r * W;
-      ta[r * RS + u] = (u == c.j) ? de * incol[r] : 0.f;
-    }
-    __syncthreads();
-    norm_pass<W>(net, nd, l, ta, n0, commit);
-    __syncthreads();
-    // 3. dense layers m = l+1 .. L-2
-    const int q = lane >> 4, li = lane & 15;
-    for (int m = l + 1; m <= L - 2; ++m) {
-      const float* Wm = net.W[m];
-      floatx4 acc[SB][CB];
+    typename D::Acc acc, zc;
+    // sum of x over the units of each of this lane's rows
+    int slot = 0;
+    auto row_sums = [&](auto&& x, float (&out)[SB][4]) {
 #pragma unroll
       for (int sb = 0; sb < SB; ++sb)
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb) acc[sb][cb] = floatx4{0.f, 0.f, 0.f, 0.f};
-      floatx4 bcur[CB], bnext[CB];
+        for (int v = 0; v < 4; ++v) {
+          float s = 0.f;
 #pragma unroll
-      for (int cb = 0; cb < CB; ++cb)
-        bcur[cb] = gload(reinterpret_cast<const floatx4*>(&Wm[(int64_t)(UW * wave + 16 * cb + li) * W + 4 * q]));
-      for (int kb = 0; kb < W / 16; ++kb) {
-        if (kb + 1 < W / 16) {
+          for (int h = 0; h < H; ++h)
 #pragma unroll
-          for (int cb = 0; cb < CB; ++cb)
-            bnext[cb] = gload(reinterpret_cast<const floatx4*>(
-                &Wm[(int64_t)(UW * wave + 16 * cb + li) * W + 16 * (kb + 1) + 4 * q]));
+            for (int cb = 0; cb < 4; ++cb) s += x(h, sb, cb, v);
+          s = lanes16_sum(s);
+          if (t.li == 0) red[slot][t.wave][16 * sb + 4 * t.q + v] = s;
         }
-        floatx4 a4[SB];
+      __syncthreads();
 #pragma unroll
-        for (int sb = 0; sb < SB; ++sb)
-          a4[sb] = *reinterpret_cast<const floatx4*>(&ta[(16 * sb + li) * RS + 16 * kb + 4 * q]);
+      for (int sb = 0; sb < SB; ++sb) {
+        f32x4 s = *reinterpret_cast<const f32x4*>(&red[slot][0][16 * sb + 4 * t.q]);
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
+        for (int w = 1; w < NW; ++w) s += *reinterpret_cast<const f32x4*>(&red[slot][w][16 * sb + 4 * t.q]);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) out[sb][v] = s[v];
+      }
+      slot ^= 1;  // the other buffer next: no wave still reads it two sums later
+    };
+    // the layer's changes from its field's change acc, into the tile; `read`:
+    // other waves may still read the tile
+    auto finish = [&](int m, bool read) {
+      if constexpr (LN) {
+        float mu1 = 0.f, S1 = 0.f;
+        bool moved = false;
+        if (commit) {
+          // the moved samples' statistics from their new fields
+          float s[SB][4], m1[SB][4], v1[SB][4];
+          row_sums([&](int h, int sb, int cb, int v) { return fabsf(acc[h][sb][cb][v]); }, s);
+          row_sums([&](int h, int sb, int cb, int v) { return zc[h][sb][cb][v] + acc[h][sb][cb][v]; }, m1);
 #pragma unroll
           for (int sb = 0; sb < SB; ++sb)
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
-              acc[sb][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[sb][t], bcur[cb][t], acc[sb][cb], 0, 0, 0);
+            for (int v = 0; v < 4; ++v) m1[sb][v] *= 1.0f / W;
+          row_sums([&](int h, int sb, int cb, int v) {
+            const float d = (zc[h][sb][cb][v] + acc[h][sb][cb][v]) - m1[sb][v];
+            return d * d;
+          }, v1);
+          if (t.wave == 0 && t.li < 4)  // lane (q, v): row 4 q + v of each block of 16
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb) bcur[cb] = bnext[cb];
+            for (int sb = 0; sb < SB; ++sb)
+#pragma unroll
+              for (int v = 0; v < 4; ++v)
+                if (v == t.li && t.nrow[sb][v] >= 0 && s[sb][v] != 0.f) {
+                  rowc[16 * sb + 4 * t.q + v] = make_float4(m1[sb][v], v1[sb][v] * (1.0f / W) + net.ln_eps, 1.f, 0.f);
+                } else if (v == t.li) {
+                  rowc[16 * sb + 4 * t.q + v] = make_float4(0.f, 0.f, 0.f, 0.f);
+                }
+          __syncthreads();
+          if (tid < T) {
+            mu1 = rowc[tid].x;
+            S1 = rowc[tid].y;
+            moved = rowc[tid].z != 0.f;
+          }
+        }
+        float S = 1.f;
+        if (tid < T) {
+          const int n = rown[tid] >= 0 ? rown[tid] : 0;
+          rowmu[tid] = gload(&nd.MU[m][n]);
+          S = gload(&nd.S[m][n]);
+        }
+        float dmu[SB][4], dS[SB][4];
+        row_sums([&](int h, int sb, int cb, int v) { return acc[h][sb][cb][v]; }, dmu);  // (rowmu with its barrier)
+        float mu[SB][4];
+#pragma unroll
+        for (int sb = 0; sb < SB; ++sb)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            dmu[sb][v] *= 1.0f / W;
+            mu[sb][v] = rowmu[16 * sb + 4 * t.q + v];
+          }
+        row_sums([&](int h, int sb, int cb, int v) {
+          const float c1 = zc[h][sb][cb][v] - mu[sb][v], e = acc[h][sb][cb][v] - dmu[sb][v];
+          return e * (c1 + c1 + e);
+        }, dS);
+        // the row's factors by one thread a row
+        if (t.wave == 0 && t.li == 0)
+#pragma unroll
+          for (int sb = 0; sb < SB; ++sb)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) dls[16 * sb + 4 * t.q + v] = dS[sb][v] * (1.0f / W);
+        __syncthreads();
+        if (tid < T) {
+          const float d = dls[tid];
+          const float q0 = sqrtf(S), q1 = sqrtf(S + d);
+          const float rs = 1.0f / q0, rs1 = 1.0f / q1;
+          rowc[tid] = make_float4(rs, rs1, ((d * rs) * rs1) / (q0 + q1), 0.f);
+          if (commit && moved) {
+            gstore(&nd.MU[m][rown[tid]], mu1);
+            gstore(&nd.S[m][rown[tid]], S1);
+          }
+        }
+        __syncthreads();
+        if (commit) t.store_fields(net.Z[m], Ns, zc, acc);
+#pragma unroll
+        for (int sb = 0; sb < SB; ++sb)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const float4 r = rowc[16 * sb + 4 * t.q + v];
+#pragma unroll
+            for (int h = 0; h < H; ++h)
+#pragma unroll
+              for (int cb = 0; cb < 4; ++cb) {
+                const float c1 = zc[h][sb][cb][v] - mu[sb][v], e = acc[h][sb][cb][v] - dmu[sb][v];
+                acc[h][sb][cb][v] = dphi(c1 * r.x, e * r.y - c1 * r.z, ACT, gamma);
+              }
+          }
+      } else {
+        if (commit) t.store_fields(net.Z[m], Ns, zc, acc);
+#pragma unroll
+        for (int h = 0; h < H; ++h)
+#pragma unroll
+          for (int sb = 0; sb < SB; ++sb)
+#pragma unroll
+            for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+              for (int v = 0; v < 4; ++v) acc[h][sb][cb][v] = dphi(zc[h][sb][cb][v], acc[h][sb][cb][v], ACT, gamma);
+        if (read) __syncthreads();  // every wave has read the tile
       }
-      __syncthreads();  // every wave has read the tile
+      t.write_tile(ta, acc);
+      __syncthreads();
+    };
+    // 1. the first layer: the one moved field (normalized), or the rank-1 term
+    // of the moved unit in the next layer
+    const int s = LN ? l : l + 1;
+    if (LN || s <= L - 2) {
+      t.fields(net.Z[s], Ns, zc);
+#pragma unroll
+      for (int h = 0; h < H; ++h)
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) {
+          const int u = t.unit(h, cb);
+          const float w = LN ? (u == c.j ? 1.0f : 0.f) : gload(&net.W[s][(int64_t)u * W + c.j]);
+#pragma unroll
+          for (int sb = 0; sb < SB; ++sb)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[h][sb][cb][v] = rowv[16 * sb + 4 * t.q + v] * w;
+        }
+      finish(s, false);
+      // 2. dense layers
+      for (int m = s + 1; m <= L - 2; ++m) {
+        t.fields(net.Z[m], Ns, zc);
+        t.product(net, m, ta, acc);
+        finish(m, true);
+      }
+      // 3. the logits: the last hidden layer's change through W_{L-1}
+      f32x4 lg[SB][1];
+      t.logit_part(net, ta, lg);
+      __syncthreads();  // every wave has read the tile: the sums take its place
 #pragma unroll
       for (int sb = 0; sb < SB; ++sb)
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-          for (int v = 0; v < 4; ++v)
-            ta[(16 * sb + 4 * q + v) * RS + UW * wave + 16 * cb + li] = acc[sb][cb][v];
-      __syncthreads();
-      norm_pass<W>(net, nd, m, ta, n0, commit);
-      __syncthreads();
-    }
-    // 4. logit changes: the last hidden layer's change through W_{L-1}
-    const float* WL = net.W[L - 1];
-#pragma unroll
-    for (int c0 = 0; c0 < CM; c0 += TPR) {
-      const int cl = c0 + cq;
-      if (cl < C) {
-        float a = 0.f;
-        for (int u = 0; u < W; ++u) a = fmaf(ta[r4 * RS + u], gload(&WL[(int64_t)cl * W + u]), a);
-        logit[r4][cl] = a;
+        for (int v = 0; v < 4; ++v) logit[t.wave][16 * sb + 4 * t.q + v][t.li] = lg[sb][0][v];
+    } else {
+      // a unit of the last hidden layer without normalization: rank-1 logits
+      const float* WL = net.W[L - 1];
+      for (int e = tid; e < T * 16; e += D::threads) {
+        const int r = e >> 4, cl = e & 15;
+        logit[0][r][cl] = cl < net.C ? rowv[r] * gload(&WL[(int64_t)cl * W + c.j]) : 0.f;
       }
     }
   }
   __syncthreads();
-  // 5. per-sample loss change from the logit change and the cached softmax
-  // (an evaluation counts the step's minibatch only); the tile's sum in row order
+  // 4. each sample's loss change; the tile's sum in row order
+  const bool one = l == L - 1 || (!LN && l == L - 2);
   if (tid < T) {
-    const int64_t n = n0 + tid;
-    float d = 0.f;
-    if (n < N) {
-      const int y = gload(&net.y[n]);
-      float dz[CM], pr[CM], dzy = 0.f;
-#pragma unroll
-      for (int cc = 0; cc < CM; ++cc) {
-        dz[cc] = (cc < C) ? logit[tid][cc] : 0.f;
-        pr[cc] = (cc < C) ? gload(&net.prob[(int64_t)cc * Ns + n]) : 0.f;
-        dzy = (cc == y) ? dz[cc] : dzy;
-      }
-      d = ce_change<CM>(pr, dz, C, dzy);
-      if (!commit && !in_subset(net, subset_start(net, st->t), n)) d = 0.f;
-      if (commit) {
-        float* ZL = net.Z[L - 1];
-        float z[CM], pn[CM];
-#pragma unroll
-        for (int cc = 0; cc < CM; ++cc) z[cc] = (cc < C) ? gload(&ZL[(int64_t)cc * Ns + n]) + dz[cc] : 0.f;
-        const float ln = softmax_ce<CM>(z, C, y, pn);
-#pragma unroll
-        for (int cc = 0; cc < CM; ++cc)
-          if (cc < C) {
-            gstore(&ZL[(int64_t)cc * Ns + n], z[cc]);
-            gstore(&net.prob[(int64_t)cc * Ns + n], pn[cc]);
-          }
-        gstore(&net.ell[n], ln);
-      }
-    }
-    dls[tid] = d;
+    const int n = rown[tid];
+    dls[tid] = n < 0 ? 0.f : (one ? sample_change<1, T>(net, n, logit, tid, commit)
+                                  : sample_change<NW, T>(net, n, logit, tid, commit));
   }
   __syncthreads();
   if (!commit && tid == 0) {
@@ -290,18 +325,9 @@ __global__ __launch_bounds__(kNThreads, (W >= 1024) ? 1 : 2) void k_norm(
   }
 }
 
-// After the field commit: the new parameter (weight or bias), the committed
-// loss (a minibatch's change is not the loss's) and the count.
-__global__ void k_norm_param(NetDev net, const mca_cand* cands, const Aux* aux, int k_mode,
-                             DevState* st, const double* dL) {
-  const int k = (k_mode >= 0) ? k_mode : st->chosen;
-  if (k < 0 || threadIdx.x != 0) return;
-  const mca_cand c = cands[k];
-  const float w = aux[k].w_new;
-  if (c.i == net.widths[c.layer]) net.B[c.layer][c.j] = w;
-  else net.W[c.layer][(int64_t)c.j * net.widths[c.layer] + c.i] = w;
-  if (net.sub_size == 0) st->L += dL[k];
-  st->accepted += 1;
+int norm_tiles(int64_t n_samples, int w) {
+  const int T = w == 256 ? Dense<256, false>::T : (w == 512 ? Dense<512, false>::T : Dense<1024, false>::T);
+  return (int)((n_samples + T - 1) / T);
 }
 
 // Statistics of hidden layer l, one thread per sample, units in order.
@@ -328,42 +354,39 @@ hipError_t launch_norm_stats(const NetDev& net, const NormDev& nd, int l, hipStr
   return hipGetLastError();
 }
 
-namespace {
-template <int CM>
-hipError_t launch_norm_width(const NetDev& net, const NormDev& nd, dim3 grid,
-                             const mca_cand* cands, const Aux* aux, float* partial, int ntiles,
-                             int k_mode, DevState* st, hipStream_t s) {
-  switch (net.widths[1]) {
-    case 256:
-      hipLaunchKernelGGL((k_norm<CM, 256>), grid, dim3(kNThreads), 0, s, net, nd, cands, aux,
-                         partial, ntiles, k_mode, st);
-      break;
-    case 512:
-      hipLaunchKernelGGL((k_norm<CM, 512>), grid, dim3(kNThreads), 0, s, net, nd, cands, aux,
-                         partial, ntiles, k_mode, st);
-      break;
-    case 1024:
-      hipLaunchKernelGGL((k_norm<CM, 1024>), grid, dim3(kNThreads), 0, s, net, nd, cands, aux,
-                         partial, ntiles, k_mode, st);
-      break;
-    default:
-      return hipErrorInvalidValue;  // the context's validation admits no other width
-  }
-  return hipGetLastError();
-}
-}  // namespace
-
 hipError_t launch_norm(const NetDev& net, const NormDev& nd, const mca_cand* cands,
-                       const Aux* aux, int K, float* partial, int ntiles, int k_mode,
-                       DevState* st, const double* dL, hipStream_t s) {
+                       const Aux* aux, int K, int* rows, float* vals, int* cnt, float* partial,
+                       int ntiles, int k_mode, DevState* st, const double* dL, hipStream_t s) {
   const bool commit = k_mode != -2;
-  const dim3 grid((unsigned)ntiles, commit ? 1u : (unsigned)K);
-  hipError_t e = (net.C == 10)
-                     ? launch_norm_width<10>(net, nd, grid, cands, aux, partial, ntiles, k_mode, st, s)
-                     : launch_norm_width<kCMax>(net, nd, grid, cands, aux, partial, ntiles, k_mode, st, s);
-  if (e != hipSuccess || !commit) return e;
-  hipLaunchKernelGGL(k_norm_param, dim3(1), dim3(64), 0, s, net, cands, aux, k_mode, st, dL);
-  return hipGetLastError();
+  hipLaunchKernelGGL(k_norm_rows, dim3(commit ? 1 : K), dim3(kListThreads), 0, s, net, nd, cands, aux,
+                     k_mode, st, dL, rows, vals, cnt, K);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  constexpr int kCommitT = 16;
+  const dim3 grid(commit ? (unsigned)((net.N + kCommitT - 1) / kCommitT) : (unsigned)ntiles,
+                  commit ? 1u : (unsigned)K);
+  auto go = [&](auto w, auto act) {
+    constexpr int W = decltype(w)::value, ACT = decltype(act)::value;
+    static_assert(Dense<W, true>::T == kCommitT, "a commit's grid");
+    auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, grid, dim3(Dense<W, false>::threads), 0, s, net, nd, cands, rows, vals, cnt,
+                         partial, ntiles, K, k_mode, st);
+    };
+    if (net.ln) commit ? launch(k_norm<W, ACT, true, true>) : launch(k_norm<W, ACT, true, false>);
+    else commit ? launch(k_norm<W, ACT, false, true>) : launch(k_norm<W, ACT, false, false>);
+    return hipGetLastError();
+  };
+  auto by_act = [&](auto w) {
+    if (net.act == MCA_ACT_TANH) return go(w, std::integral_constant<int, MCA_ACT_TANH>{});
+    if (net.act == MCA_ACT_RELU) return go(w, std::integral_constant<int, MCA_ACT_RELU>{});
+    return go(w, std::integral_constant<int, MCA_ACT_GAUSS>{});
+  };
+  switch (net.widths[1]) {
+    case 256: return by_act(std::integral_constant<int, 256>{});
+    case 512: return by_act(std::integral_constant<int, 512>{});
+    case 1024: return by_act(std::integral_constant<int, 1024>{});
+    default: return hipErrorInvalidValue;  // the context's validation admits no other width
+  }
 }
 
 }  // namespace mca
