@@ -91,6 +91,7 @@ struct Layout {
   size_t wf = 0;                                    // split copy of the dense layers' weights
   size_t chans = 0, pchan = 0;                      // channel mutations: records, tile sums
   size_t pnorm = 0;                                 // nets with biases / normalization: tile sums
+  size_t aug[MCA_MAX_LAYERS] = {};  // the augmented matrices as the host has them
   size_t b[MCA_MAX_LAYERS] = {}, mu[MCA_MAX_LAYERS] = {}, S[MCA_MAX_LAYERS] = {};
   int nchain = 0, nchan = 0, nnorm = 0;
   int nslab = 0;
@@ -349,7 +350,10 @@ Layout make_layout(const mca_net_desc* net, int64_t N, int32_t k_max) {
   lo.xt = take((size_t)net->widths[0] * lo.Ns * sizeof(float));
   for (int l = 0; l < L; ++l) lo.w[l] = take((size_t)net->widths[l + 1] * net->widths[l] * sizeof(float));
   if (net->biases)
-    for (int l = 0; l < L; ++l) lo.b[l] = take((size_t)net->widths[l + 1] * sizeof(float));
+    for (int l = 0; l < L; ++l) {
+      lo.b[l] = take((size_t)net->widths[l + 1] * sizeof(float));
+      lo.aug[l] = take((size_t)net->widths[l + 1] * (net->widths[l] + 1) * sizeof(float));
+    }
   if (net->layer_norm)
     for (int l = 0; l + 1 < L; ++l) {
       lo.mu[l] = take(lo.Ns * sizeof(float));
@@ -448,6 +452,7 @@ struct mca_ctx {
   bool norm = false;             // biases and / or normalized hidden fields (Sec. 2.1)
   mca::NormDev nd{};             // normalization statistics
   float* pnorm = nullptr;        // tile sums of the dense evaluation
+  float* aug[MCA_MAX_LAYERS] = {};  // biased nets: the augmented matrices on their way to or from the host
   double* dl = nullptr;
   double* bsum = nullptr;
   DevState* st = nullptr;
@@ -632,11 +637,10 @@ int upload_params(mca_ctx* ctx, const float* const* params, const int8_t* const*
   for (int l = 0; l < L; ++l) {
     const size_t n = (size_t)d.widths[l + 1] * d.widths[l];
     if (d.biases) {  // the augmented matrix [n_{l+1}][n_l + 1]: weights, then the bias column
-      const size_t w = (size_t)d.widths[l], rows = (size_t)d.widths[l + 1];
-      MCA_HIP(ctx, hipMemcpy2DAsync(ctx->net.W[l], w * sizeof(float), params[l], (w + 1) * sizeof(float),
-                                    w * sizeof(float), rows, hipMemcpyHostToDevice, ctx->stream));
-      MCA_HIP(ctx, hipMemcpy2DAsync(ctx->net.B[l], sizeof(float), params[l] + w, (w + 1) * sizeof(float),
-                                    sizeof(float), rows, hipMemcpyHostToDevice, ctx->stream));
+      const size_t all = (size_t)d.widths[l + 1] * (d.widths[l] + 1);
+      MCA_HIP(ctx, hipMemcpyAsync(ctx->aug[l], params[l], all * sizeof(float), hipMemcpyHostToDevice, ctx->stream));
+      MCA_HIP(ctx, mca::launch_augment(ctx->aug[l], ctx->net.W[l], ctx->net.B[l], d.widths[l + 1], d.widths[l],
+                                       true, ctx->stream));
       continue;
     }
     MCA_HIP(ctx, hipMemcpyAsync(ctx->net.W[l], params[l], n * sizeof(float), hipMemcpyHostToDevice, ctx->stream));
@@ -1078,6 +1082,7 @@ int mca_init(mca_ctx** out, const mca_net_desc* net, const float* const* params,
     nd.offs[l] = off;
     off += (int64_t)net->widths[l + 1] * (net->widths[l] + net->biases);
     nd.B[l] = net->biases ? (float*)(ws + lo.b[l]) : nullptr;
+    ctx->aug[l] = net->biases ? (float*)(ws + lo.aug[l]) : nullptr;
     nd.scales[l] = net->scales[l];
     nd.W[l] = (float*)(ws + lo.w[l]);
     nd.codes[l] = nd.ternary ? (int8_t*)(ws + lo.codes[l]) : nullptr;
@@ -1551,11 +1556,10 @@ int mca_get_params(mca_ctx* ctx, float* const* params_out, int8_t* const* codes_
     const size_t n = (size_t)d.widths[l + 1] * d.widths[l];
     if (params_out[l] == nullptr) return fail(ctx, MCA_EINVAL, "a params_out pointer is NULL");
     if (d.biases) {
-      const size_t w = (size_t)d.widths[l], rows = (size_t)d.widths[l + 1];
-      MCA_HIP(ctx, hipMemcpy2DAsync(params_out[l], (w + 1) * sizeof(float), ctx->net.W[l], w * sizeof(float),
-                                    w * sizeof(float), rows, hipMemcpyDeviceToHost, ctx->stream));
-      MCA_HIP(ctx, hipMemcpy2DAsync(params_out[l] + w, (w + 1) * sizeof(float), ctx->net.B[l], sizeof(float),
-                                    sizeof(float), rows, hipMemcpyDeviceToHost, ctx->stream));
+      const size_t all = (size_t)d.widths[l + 1] * (d.widths[l] + 1);
+      MCA_HIP(ctx, mca::launch_augment(ctx->aug[l], ctx->net.W[l], ctx->net.B[l], d.widths[l + 1], d.widths[l],
+                                       false, ctx->stream));
+      MCA_HIP(ctx, hipMemcpyAsync(params_out[l], ctx->aug[l], all * sizeof(float), hipMemcpyDeviceToHost, ctx->stream));
       continue;
     }
     MCA_HIP(ctx, hipMemcpyAsync(params_out[l], ctx->net.W[l], n * sizeof(float), hipMemcpyDeviceToHost, ctx->stream));

@@ -21,6 +21,9 @@ int norm_tiles(int64_t n_samples, int w);
 
 // MU[l], S[l] of hidden layer l from the cached fields Z[l].
 hipError_t launch_norm_stats(const NetDev& net, const NormDev& nd, int l, hipStream_t s);
+// aug [rows][n + 1] = each row of W [rows][n] followed by its bias, or
+// (to_net) W and B from aug.
+hipError_t launch_augment(float* aug, float* W, float* B, int rows, int n, bool to_net, hipStream_t s);
 // k_mode -2: partial[k * ntiles + tile] for every candidate k < K; -1: commit
 // st->chosen (nothing when -1); >= 0: commit that candidate.  A commit moves
 // every cached field and statistic and writes the parameter, the loss and
