@@ -9,23 +9,33 @@
 //    (W'_m a' - W_m a = W_m (a' - a) + (w'_m - w_m) a'[u_m]);
 //  - the logits' change gives each sample's loss change with the cached
 //    softmax (ce_change).
-// Every sample can change (the later path weights reach every sample whose
-// activation at the path unit is non-zero), so a block takes T consecutive
-// samples of one channel, keeps their activation changes in an LDS tile
-// [T][W + 4] (T = 16384 / W: 64, 32 or 16 rows, 66 KB), runs the dense layers
-// on the matrix cores (v_mfma_f32_16x16x4f32, four waves of W / 4 output
-// units each), and sums its T loss changes in row order.  The commit runs the
-// same arithmetic for the chosen channel and moves every cached field by its
-// change; a second kernel then writes the path's weights.
-#include "device_common.hpp"
+//
+// Most of that is one unit at a time.  Where the first unit's activation does not
+// change (its input is zero on four of five samples of an image, or a ReLU unit
+// stays off), the second field moves at the path's unit alone, by its own
+// weight's change; if that unit's activation does not change either, so does the
+// third, and so on.  k_channel_rows walks every sample along the path up to the
+// layer f that first receives a changed activation: layer f moves by the rank-1
+// term of that one unit, and only the layers after it need dense products.
+// Samples whose walk reaches the logits are done there (a rank-1 logit change);
+// the others are listed, those of f = 1 first, and blocks of k_channel take tiles
+// of T of them (dense_tile.hpp).  On 784-1024x3-10 with ReLU a tenth of the
+// samples need the dense layer, a fifth a rank-1 second layer: 16 channels on 8192
+// samples, with the products on bf16 parts, 5.4 -> 0.61 ms.
+// The commit runs the same arithmetic for the chosen channel and moves every
+// cached field by its change; a last kernel writes the path's weights.
+#include <type_traits>
+
+#include "dense_tile.hpp"
 #include "channel_kernels.hpp"
 
 namespace mca {
 
 namespace {
 
-constexpr int kChThreads = 256;
-typedef float floatx4 __attribute__((ext_vector_type(4)));
+// Blocks of k_channel per unit of residency: one a CU, and a second round's worth
+// so that a slow one is not waited for.
+constexpr int kChannelBlocks = 512;
 
 // The channel of draw (t, k): 2L + 1 words of the Philox blocks at counters
 // (t, k, 2 + b, 0), four words per block, in order.
@@ -102,243 +112,353 @@ __global__ void k_channel_prepare(NetDev net_arg, const mca_channel* chans, int 
   cands[k] = placeholder();
 }
 
-// grid (ntiles, K) for an evaluation, (ntiles, 1) for a commit.
-template <int CM, int W>
-__global__ __launch_bounds__(kChThreads, (W >= 1024) ? 1 : 2) void k_channel(
-    NetDev net_arg, const mca_channel* chans, const Aux* aux, float* partial, int ntiles,
-    int k_mode, DevState* st) {
-  constexpr int T = 16384 / W;        // samples of the block
-  constexpr int SB = T / 16;          // 16-row blocks of the tile
-  constexpr int UW = W / 4;           // output units per wave
-  constexpr int CB = UW / 16;         // 16-unit blocks per wave
-  constexpr int RS = W + 4;           // floats per padded LDS row
-  constexpr int TPR = kChThreads / T; // threads per row for the logits
-  static_assert(SB * CB == 16, "sixteen accumulator tiles per wave");
+// The path and the increments fl32(w' - w) of its weights (committed weights: a
+// commit writes the new ones only after the field kernels).  By every thread.
+__device__ __forceinline__ void load_path(const NetDev& net, const mca_channel& ch, int* units, float* de) {
+  const int tid = threadIdx.x;
+  if (tid <= net.L) units[tid] = ch.units[tid];
+  __syncthreads();
+  if (tid < net.L) {
+    const float wo = net.W[tid][(int64_t)units[tid + 1] * net.widths[tid] + units[tid]];
+    de[tid] = ch.w_new[tid] - wo;
+  }
+  __syncthreads();
+}
+
+// Block k (eval) or the committed channel: every sample's walk along the path.
+// Samples that break off at layer f <= L-2 are listed in sample order, f = 1 from
+// the front of the channel's part of the lists, later ones from its back: the
+// sample, the changed activation entering layer f, the path unit's new one, f.
+// The others' loss changes are summed here: partial[k * nchan + nchan - 1].
+// An evaluation's last block then adds up the tiles of all lists (those of f = 1
+// first): lists.first[e], e <= 2 K.  A commit stores the walked fields.
+__global__ __launch_bounds__(kListThreads) void k_channel_rows(NetDev net_arg, const mca_channel* chans,
+                                                               const Aux* aux, ChannelLists lists, float* partial,
+                                                               int nchan, int T, int K, int k_mode, DevState* st) {
   __shared__ NetDev net;
   stage_net(net, net_arg);
-  // activation changes [sample][unit], rewritten in place layer by layer
-  __shared__ __attribute__((aligned(16))) float ta[T * RS];
-  __shared__ float wcol[W];
-  __shared__ float apath[2][T];  // new activation of the path unit feeding the next layer
-  __shared__ float da0[T];       // activation change of the first layer's path unit
-  __shared__ float logit[T][CM];
-  __shared__ float dls[T];
   __shared__ int units[MCA_MAX_LAYERS + 1];
   __shared__ float de[MCA_MAX_LAYERS];
-
+  __shared__ int counts[2][64];  // [list][u][wave]
+  __shared__ double sums[kListThreads / 64];
+  __shared__ int last;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const bool commit = k_mode != -2;
-  const int k = commit ? ((k_mode >= 0) ? k_mode : st->chosen) : (int)blockIdx.y;
-  if (k < 0) return;
-  const int tile = blockIdx.x;
-  if (!commit && !aux[k].valid) {  // rejected unevaluated: selection gives +inf
-    if (tid == 0) partial[(int64_t)k * ntiles + tile] = 0.f;
+  const int k = commit ? ((k_mode >= 0) ? k_mode : st->chosen) : (int)blockIdx.x;
+  if (k < 0) {
+    if (tid == 0) lists.first[0] = lists.first[1] = lists.first[2] = 0;
     return;
   }
-  const int L = net.L;
-  const int C = (CM < kCMax) ? CM : net.C;
-  const int act = net.act;
+  const int L = net.L, C = net.C, act = net.act;
   const float gamma = net.gamma;
   const int64_t N = net.N, Ns = net.Ns;
-  const int64_t n0 = (int64_t)tile * T;
-
-  // 0. the path and the increments fl32(w' - w) of its weights (committed
-  // weights: a commit writes the new ones only after this kernel)
-  if (tid <= L) units[tid] = chans[k].units[tid];
-  if (tid < T) apath[0][tid] = apath[1][tid] = 0.f;
-  __syncthreads();
-  if (tid < L) {
-    const float wo = net.W[tid][(int64_t)units[tid + 1] * net.widths[tid] + units[tid]];
-    de[tid] = chans[k].w_new[tid] - wo;
-  }
-  __syncthreads();
-
-  // 1. the first field's path column
-  if (tid < T) {
-    const int64_t n = n0 + tid;
-    float d = 0.f, ap = 0.f;
-    if (n < N) {
-      const float x = gload(&net.XT[(int64_t)units[0] * Ns + n]);
-      float* zp = &net.Z[0][(int64_t)units[1] * Ns + n];
-      const float z = gload(zp);
-      const float dz = de[0] * x;
-      if (L > 1) {
-        d = dphi(z, dz, act, gamma);
-        ap = act_fn(z + dz, act, gamma);
-        if (commit) gstore(zp, z + dz);
-      } else {
-        d = dz;  // a one-layer net: the field is a logit (moved at step 5)
-      }
-    }
-    da0[tid] = d;
-    apath[0][tid] = ap;
-  }
-  // 2. the second layer: rank-1 through W_1[:, u_1] plus the path weight's change
-  int cur = 0;  // apath buffer of the layer feeding the next product
-  if (L >= 2) {
-    const int n_out = net.widths[2];
-    for (int u = tid; u < n_out; u += kChThreads)
-      wcol[u] = gload(&net.W[1][(int64_t)u * net.widths[1] + units[1]]);
-    __syncthreads();
-    if (L >= 3) {
-      const int j2 = units[2];
-      float* Z1 = net.Z[1];
-      for (int e = tid; e < T * W; e += kChThreads) {
-        const int r = e % T, u = e / T;
-        const int64_t n = n0 + r;
-        float v = 0.f;
-        if (n < N) {
-          float dz = da0[r] * wcol[u];
-          if (u == j2) dz = fmaf(de[1], apath[0][r], dz);
-          const float z = gload(&Z1[(int64_t)u * Ns + n]);
-          v = dphi(z, dz, act, gamma);
-          if (u == j2) apath[1][r] = act_fn(z + dz, act, gamma);
-          if (commit) gstore(&Z1[(int64_t)u * Ns + n], z + dz);
+  const bool scored = commit || aux[k].valid;  // rejected unevaluated: selection gives +inf
+  int base[2] = {0, 0};
+  double sum = 0.0;
+  if (!commit)
+    for (int t = tid; t < nchan; t += kListThreads) partial[(int64_t)k * nchan + t] = 0.f;
+  if (scored) {
+    load_path(net, chans[k], units, de);
+    for (int64_t n0 = 0; n0 < N; n0 += kListU * kListThreads) {
+      int64_t ns[kListU];
+      float d[kListU], ap[kListU];  // the last walked unit's change and new activation
+      int f[kListU];                // the layer they enter
+      {
+        float* z0 = net.Z[0] + (int64_t)units[1] * Ns;
+        float x[kListU], z[kListU];
+#pragma unroll
+        for (int u = 0; u < kListU; ++u) {
+          const int64_t n = n0 + u * kListThreads + tid;
+          ns[u] = n < N ? n : N - 1;
+          x[u] = gload(&net.XT[(int64_t)units[0] * Ns + ns[u]]);
+          z[u] = gload(&z0[ns[u]]);
         }
-        ta[r * RS + u] = v;
+#pragma unroll
+        for (int u = 0; u < kListU; ++u) {
+          const float dz = de[0] * x[u];
+          d[u] = dphi(z[u], dz, act, gamma);
+          ap[u] = act_fn(z[u] + dz, act, gamma);
+          f[u] = 1;
+          if (commit && dz != 0.f && n0 + u * kListThreads + tid < N) gstore(&z0[ns[u]], z[u] + dz);
+        }
       }
-      cur = 1;
+      for (int m = 1; m <= L - 2; ++m) {
+        float* zm = net.Z[m] + (int64_t)units[m + 1] * Ns;
+        float z[kListU];
+#pragma unroll
+        for (int u = 0; u < kListU; ++u) z[u] = gload(&zm[ns[u]]);
+#pragma unroll
+        for (int u = 0; u < kListU; ++u) {
+          if (f[u] == m && d[u] == 0.f) {
+            const float dz = de[m] * ap[u];
+            d[u] = dphi(z[u], dz, act, gamma);
+            ap[u] = act_fn(z[u] + dz, act, gamma);
+            f[u] = m + 1;
+            if (commit && dz != 0.f && n0 + u * kListThreads + tid < N) gstore(&zm[ns[u]], z[u] + dz);
+          }
+        }
+      }
+      uint64_t b[2][kListU];
+#pragma unroll
+      for (int u = 0; u < kListU; ++u) {
+        const bool in = n0 + u * kListThreads + tid < N;
+        b[0][u] = __ballot(in && f[u] <= L - 2 && f[u] == 1);
+        b[1][u] = __ballot(in && f[u] <= L - 2 && f[u] > 1);
+        if (lane < 2) counts[lane][u * (kListThreads / 64) + wave] = (int)__popcll(lane ? b[1][u] : b[0][u]);
+        if (in && f[u] == L - 1) {
+          // a rank-1 change of the logits
+          const float* WL = net.W[L - 1] + units[L - 1];
+          const float dp = de[L - 1] * ap[u];
+          if (d[u] != 0.f || dp != 0.f) {
+            const int64_t n = ns[u];
+            const int y = gload(&net.y[n]), cls = units[L];
+            float dz[kCMax], p[kCMax], dzy = 0.f;
+#pragma unroll
+            for (int c = 0; c < kCMax; ++c) {
+              dz[c] = 0.f;
+              p[c] = (c < C) ? gload(&net.prob[(int64_t)c * Ns + n]) : 0.f;
+              if (c < C) {
+                dz[c] = d[u] * gload(&WL[(int64_t)c * net.widths[L - 1]]);
+                if (c == cls) dz[c] = fmaf(de[L - 1], ap[u], dz[c]);
+              }
+              dzy = (c == y) ? dz[c] : dzy;
+            }
+            sum += (double)ce_change<kCMax>(p, dz, C, dzy);
+            if (commit) {
+              float* ZL = net.Z[L - 1];
+              float z[kCMax], pn[kCMax];
+#pragma unroll
+              for (int c = 0; c < kCMax; ++c) z[c] = (c < C) ? gload(&ZL[(int64_t)c * Ns + n]) + dz[c] : 0.f;
+              const float ln = softmax_ce<kCMax>(z, C, y, pn);
+#pragma unroll
+              for (int c = 0; c < kCMax; ++c)
+                if (c < C) {
+                  gstore(&ZL[(int64_t)c * Ns + n], z[c]);
+                  gstore(&net.prob[(int64_t)c * Ns + n], pn[c]);
+                }
+              gstore(&net.ell[n], ln);
+            }
+          }
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        const int mine = counts[g][lane];
+        int incl = mine;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const int w = __shfl_up(incl, o, 64);
+          if (lane >= o) incl += w;
+        }
+#pragma unroll
+        for (int u = 0; u < kListU; ++u) {
+          const int off = base[g] + __shfl(incl - mine, u * (kListThreads / 64) + wave, 64);
+          if ((b[g][u] >> lane) & 1ull) {
+            const int64_t e = off + (int)__popcll(b[g][u] & ((1ull << lane) - 1ull));
+            const int64_t at = (int64_t)k * N + (g == 0 ? e : N - 1 - e);
+            gstore(&lists.rows[at], (int)ns[u]);
+            gstore(&lists.d[at], d[u]);
+            gstore(&lists.ap[at], ap[u]);
+            gstore(&lists.f[at], f[u]);
+          }
+        }
+        base[g] += __shfl(incl, 63, 64);
+      }
+      __syncthreads();
+    }
+  }
+  if (!commit && scored) {
+    // the walked samples' sum: lanes by a butterfly, waves in order
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    if (lane == 0) sums[wave] = sum;
+    __syncthreads();
+    if (tid == 0) {
+      double s = 0.0;
+      for (int w = 0; w < kListThreads / 64; ++w) s += sums[w];
+      partial[(int64_t)k * nchan + nchan - 1] = (float)s;
+    }
+  }
+  // the tiles of every list, in order (a commit: of its channel's two)
+  const int nl = commit ? 1 : K;
+  if (tid == 0) {
+    __hip_atomic_store(&lists.cnt[commit ? 0 : k], base[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&lists.cnt[commit ? 1 : K + k], base[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __threadfence();
+    last = commit || atomicAdd(&st->list_done, 1u) == gridDim.x - 1;
+  }
+  __syncthreads();
+  if (!last || wave != 0) return;
+  __threadfence();
+  int total = 0;
+  for (int e0 = 0; e0 < 2 * nl; e0 += 64) {
+    const int e = e0 + lane;
+    const int c = e < 2 * nl ? __hip_atomic_load(&lists.cnt[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+    const int tiles = (c + T - 1) / T;
+    int incl = tiles;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int w = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += w;
+    }
+    if (e < 2 * nl) lists.first[e + 1] = total + incl;
+    total += __shfl(incl, 63, 64);
+  }
+  if (lane == 0) {
+    lists.first[0] = 0;
+    st->list_done = 0u;
+  }
+}
+
+// Tiles of the lists, shared out to the grid's blocks in list order.
+template <int W, int ACT, bool commit>
+__global__ __launch_bounds__((Dense<W, commit>::threads), (Dense<W, commit>::blocks_per_cu)) void k_channel(
+    NetDev net_arg, const mca_channel* chans, ChannelLists lists, float* partial, int nchan, int K,
+    int k_mode, const DevState* st) {
+  typedef Dense<W, commit> D;
+  constexpr int T = D::T, SB = D::SB, H = D::H, NW = D::NW, RS = D::RS;
+  const int nl = commit ? 1 : K;
+  if ((int)blockIdx.x >= lists.first[2 * nl]) return;
+  __shared__ NetDev net;
+  stage_net(net, net_arg);
+  __shared__ __attribute__((aligned(16))) uint16_t ta[3 * T * RS];
+  __shared__ int rown[T], rowf[T];
+  __shared__ float rowd[T], rowa[T], dls[T];
+  __shared__ int units[MCA_MAX_LAYERS + 1];
+  __shared__ float de[MCA_MAX_LAYERS];
+  __shared__ int item[2];
+  auto logit = reinterpret_cast<float (*)[T][17]>(ta);
+  static_assert(sizeof(float) * NW * T * 17 <= sizeof(ta), "the logits' sums take the tile's place");
+  const int tid = threadIdx.x, L = net.L;
+  const float gamma = net.gamma;
+  const int64_t N = net.N, Ns = net.Ns;
+  const int total = lists.first[2 * nl];
+  for (int w = blockIdx.x; w < total; w += gridDim.x) {
+    __syncthreads();  // the last item's rows and sums are read
+    if (tid < 64) {   // the list of item w: the first whose end lies past it
+      for (int e0 = 0; e0 < 2 * nl; e0 += 64) {
+        const int e = e0 + tid;
+        const uint64_t past = __ballot(e < 2 * nl && lists.first[e + 1] > w);
+        if (past != 0ull) {
+          if (tid == 0) {
+            const int e1 = e0 + (int)__ffsll((unsigned long long)past) - 1;
+            item[0] = e1;
+            item[1] = w - lists.first[e1];
+          }
+          break;
+        }
+      }
     }
     __syncthreads();
-  }
-  // 3. dense layers m = 2 .. L-2: dz = tile W_m^T plus the path change at
-  // u_{m+1}; the tile becomes phi(z_m + dz) - phi(z_m) once every wave has
-  // read it
-  const int q = lane >> 4, li = lane & 15;
-  for (int m = 2; m <= L - 2; ++m) {
-    const float* Wm = net.W[m];
-    const int jn = units[m + 1];
-    floatx4 acc[SB][CB];
+    const int e1 = item[0], tile = item[1];
+    const bool front = e1 < nl;
+    const int k = commit ? ((k_mode >= 0) ? k_mode : st->chosen) : (front ? e1 : e1 - nl);
+    const int n_rows = lists.cnt[e1];
+    load_path(net, chans[k], units, de);
+    if (tid < T) {
+      const int e = tile * T + tid;
+      const bool in = e < n_rows;
+      const int64_t at = (int64_t)k * N + (front ? (in ? e : 0) : N - 1 - (in ? e : 0));
+      rown[tid] = in ? gload(&lists.rows[at]) : -1;
+      rowd[tid] = in ? gload(&lists.d[at]) : 0.f;
+      rowa[tid] = in ? gload(&lists.ap[at]) : 0.f;
+      rowf[tid] = in ? gload(&lists.f[at]) : L;
+    }
+    __syncthreads();
+    D t;
+    t.init(rown);
+    int m0 = front ? 1 : L;
+    if (!front)
+      for (int r = 0; r < T; ++r) m0 = rowf[r] < m0 ? rowf[r] : m0;
+    typename D::Acc acc, zc;
+    for (int m = m0; m <= L - 2; ++m) {
+      const int jn = units[m + 1];
+      t.fields(net.Z[m], Ns, zc);
+      if (m > m0) {
+        t.product(net, m, ta, acc);
+      } else {
 #pragma unroll
-    for (int sb = 0; sb < SB; ++sb)
+        for (int h = 0; h < H; ++h)
 #pragma unroll
-      for (int cb = 0; cb < CB; ++cb) acc[sb][cb] = floatx4{0.f, 0.f, 0.f, 0.f};
-    // k in blocks of 16: lane group q holds k = 16 kb + 4 q + t, t = 0..3,
-    // for the four MFMAs of the block in turn
-    floatx4 bcur[CB], bnext[CB];
+          for (int sb = 0; sb < SB; ++sb)
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb)
-      bcur[cb] = gload(reinterpret_cast<const floatx4*>(&Wm[(int64_t)(UW * wave + 16 * cb + li) * W + 4 * q]));
-    for (int kb = 0; kb < W / 16; ++kb) {
-      if (kb + 1 < W / 16) {
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb)
-          bnext[cb] = gload(reinterpret_cast<const floatx4*>(
-              &Wm[(int64_t)(UW * wave + 16 * cb + li) * W + 16 * (kb + 1) + 4 * q]));
+            for (int cb = 0; cb < 4; ++cb) acc[h][sb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
-      floatx4 a4[SB];
+      // the rank-1 term of the rows whose changed unit enters here, and the path
+      // weight's own change
 #pragma unroll
-      for (int sb = 0; sb < SB; ++sb)
-        a4[sb] = *reinterpret_cast<const floatx4*>(&ta[(16 * sb + li) * RS + 16 * kb + 4 * q]);
+      for (int h = 0; h < H; ++h)
 #pragma unroll
-      for (int t = 0; t < 4; ++t)
+        for (int cb = 0; cb < 4; ++cb) {
+          const int u = t.unit(h, cb);
+          if (m == m0 || !front) {
+            const float wm = gload(&net.W[m][(int64_t)u * W + units[m]]);
+#pragma unroll
+            for (int sb = 0; sb < SB; ++sb)
+#pragma unroll
+              for (int v = 0; v < 4; ++v) {
+                const int r = 16 * sb + 4 * t.q + v;
+                if (rowf[r] == m) acc[h][sb][cb][v] = rowd[r] * wm;
+              }
+          }
+          if (u == jn) {
+#pragma unroll
+            for (int sb = 0; sb < SB; ++sb)
+#pragma unroll
+              for (int v = 0; v < 4; ++v) {
+                const int r = 16 * sb + 4 * t.q + v;
+                if (rowf[r] <= m) {
+                  const float dz = fmaf(de[m], rowa[r], acc[h][sb][cb][v]);
+                  acc[h][sb][cb][v] = dz;
+                  rowa[r] = act_fn(zc[h][sb][cb][v] + dz, ACT, gamma);
+                }
+              }
+          }
+        }
+      if (commit) t.store_fields(net.Z[m], Ns, zc, acc);
+#pragma unroll
+      for (int h = 0; h < H; ++h)
 #pragma unroll
         for (int sb = 0; sb < SB; ++sb)
 #pragma unroll
-          for (int cb = 0; cb < CB; ++cb)
-            acc[sb][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[sb][t], bcur[cb][t], acc[sb][cb], 0, 0, 0);
+          for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
-      for (int cb = 0; cb < CB; ++cb) bcur[cb] = bnext[cb];
+            for (int v = 0; v < 4; ++v) acc[h][sb][cb][v] = dphi(zc[h][sb][cb][v], acc[h][sb][cb][v], ACT, gamma);
+      __syncthreads();  // every wave has read the tile
+      t.write_tile(ta, acc);
+      __syncthreads();
     }
-    // D layout: lane (q, li), element v -> row 16 sb + 4 q + v, unit
-    // UW w + 16 cb + li.  A lane's four rows are four consecutive samples:
-    // one 16-byte load of the cached fields each (the tile starts at a
-    // multiple of 16 samples; rows past N read the padding and are unused).
-    float* Zm = net.Z[m];
-    floatx4 zc[SB][CB];
-#pragma unroll
-    for (int sb = 0; sb < SB; ++sb)
-#pragma unroll
-      for (int cb = 0; cb < CB; ++cb)
-        zc[sb][cb] = gload(reinterpret_cast<const floatx4*>(
-            &Zm[(int64_t)(UW * wave + 16 * cb + li) * Ns + n0 + 16 * sb + 4 * q]));
-    __syncthreads();
-#pragma unroll
-    for (int sb = 0; sb < SB; ++sb)
-#pragma unroll
-      for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int r = 16 * sb + 4 * q + v, u = UW * wave + 16 * cb + li;
-          const int64_t n = n0 + r;
-          float out = 0.f;
-          if (n < N) {
-            float dz = acc[sb][cb][v];
-            if (u == jn) dz = fmaf(de[m], apath[cur][r], dz);
-            const float z = zc[sb][cb][v];
-            out = dphi(z, dz, act, gamma);
-            if (u == jn) apath[cur ^ 1][r] = act_fn(z + dz, act, gamma);
-            if (commit) gstore(&Zm[(int64_t)u * Ns + n], z + dz);
-          }
-          ta[r * RS + u] = out;
-        }
-    __syncthreads();
-    cur ^= 1;
-  }
-  // 4. logit changes: a dense product of the last hidden layer's change plus
-  // the path change at class u_L (L >= 3); the rank-1 term plus the path
-  // change (L = 2); the one moved logit (L = 1)
-  {
-    const int r = tid / TPR, cq = tid % TPR;
+    f32x4 lg[SB][1];
+    t.logit_part(net, ta, lg);
+    __syncthreads();  // every wave has read the tile: the sums take its place
     const int cls = units[L];
 #pragma unroll
-    for (int c0 = 0; c0 < CM; c0 += TPR) {
-      const int c = c0 + cq;
-      if (c < C) {
-        float a = 0.f;
-        if (L >= 3) {
-          const float* WL = net.W[L - 1];
-          for (int u = 0; u < W; ++u) a = fmaf(ta[r * RS + u], gload(&WL[(int64_t)c * W + u]), a);
-          if (c == cls) a = fmaf(de[L - 1], apath[cur][r], a);
-        } else if (L == 2) {
-          a = da0[r] * wcol[c];
-          if (c == cls) a = fmaf(de[1], apath[0][r], a);
-        } else {
-          a = (c == cls) ? da0[r] : 0.f;
-        }
-        logit[r][c] = a;
+    for (int sb = 0; sb < SB; ++sb)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int r = 16 * sb + 4 * t.q + v;
+        float s = lg[sb][0][v];
+        if (t.wave == 0 && t.li == cls) s = fmaf(de[L - 1], rowa[r], s);
+        logit[t.wave][r][t.li] = s;
       }
+    __syncthreads();
+    if (tid < T) dls[tid] = rown[tid] < 0 ? 0.f : sample_change<NW, T>(net, rown[tid], logit, tid, commit);
+    __syncthreads();
+    if (!commit && tid == 0) {
+      float v = 0.f;
+      for (int r = 0; r < T; ++r) v += dls[r];
+      // front tiles from the start of the channel's sums, back tiles after them
+      const int slot = front ? tile : (lists.cnt[k] + T - 1) / T + tile;
+      partial[(int64_t)k * nchan + slot] = v;
     }
   }
-  __syncthreads();
-  // 5. per-sample loss change from the logit change and the cached softmax;
-  // the tile's sum in row order
-  if (tid < T) {
-    const int64_t n = n0 + tid;
-    float d = 0.f;
-    if (n < N) {
-      const int y = gload(&net.y[n]);
-      float dz[CM], p[CM], dzy = 0.f;
-#pragma unroll
-      for (int c = 0; c < CM; ++c) {
-        dz[c] = (c < C) ? logit[tid][c] : 0.f;
-        p[c] = (c < C) ? gload(&net.prob[(int64_t)c * Ns + n]) : 0.f;
-        dzy = (c == y) ? dz[c] : dzy;
-      }
-      d = ce_change<CM>(p, dz, C, dzy);
-      if (commit) {
-        float* ZL = net.Z[L - 1];
-        float z[CM], pn[CM];
-#pragma unroll
-        for (int c = 0; c < CM; ++c) z[c] = (c < C) ? gload(&ZL[(int64_t)c * Ns + n]) + dz[c] : 0.f;
-        const float ln = softmax_ce<CM>(z, C, y, pn);
-#pragma unroll
-        for (int c = 0; c < CM; ++c)
-          if (c < C) {
-            gstore(&ZL[(int64_t)c * Ns + n], z[c]);
-            gstore(&net.prob[(int64_t)c * Ns + n], pn[c]);
-          }
-        gstore(&net.ell[n], ln);
-      }
-    }
-    dls[tid] = d;
-  }
-  __syncthreads();
-  if (!commit && tid == 0) {
-    float v = 0.f;
-    for (int r = 0; r < T; ++r) v += dls[r];
-    partial[(int64_t)k * ntiles + tile] = v;
-  }
+}
+
+int channel_tiles(int64_t n_samples, int w) {
+  const int T = w == 256 ? Dense<256, false>::T : (w == 512 ? Dense<512, false>::T : Dense<1024, false>::T);
+  // two lists a channel, at most one part-filled tile more, and the walked sum
+  return (int)((n_samples + T - 1) / T) + 2;
 }
 
 // After the field commit: the path's new weights (and the transposed copy of
@@ -351,7 +471,7 @@ __global__ void k_channel_weights(NetDev net, const mca_channel* chans, int k_mo
   if (m < net.L) {
     const int j = chans[k].units[m + 1], i = chans[k].units[m];
     const float w = chans[k].w_new[m];
-    net.W[m][(int64_t)j * net.widths[m] + i] = w;
+    put_weight(net, m, j, i, w);
     if (net.WT != nullptr && m == net.L - 2) net.WT[(int64_t)i * net.widths[m + 1] + j] = w;
   }
   if (m == 0) {
@@ -375,38 +495,39 @@ hipError_t launch_channel_prepare(const NetDev& net, const mca_channel* ch, int 
   return hipGetLastError();
 }
 
-namespace {
-template <int CM>
-hipError_t launch_width(const NetDev& net, dim3 grid, const mca_channel* ch, const Aux* aux,
-                        float* partial, int ntiles, int k_mode, DevState* st, hipStream_t s) {
-  switch (net.widths[1]) {
-    case 256:
-      hipLaunchKernelGGL((k_channel<CM, 256>), grid, dim3(kChThreads), 0, s, net, ch, aux,
-                         partial, ntiles, k_mode, st);
-      break;
-    case 512:
-      hipLaunchKernelGGL((k_channel<CM, 512>), grid, dim3(kChThreads), 0, s, net, ch, aux,
-                         partial, ntiles, k_mode, st);
-      break;
-    case 1024:
-      hipLaunchKernelGGL((k_channel<CM, 1024>), grid, dim3(kChThreads), 0, s, net, ch, aux,
-                         partial, ntiles, k_mode, st);
-      break;
-    default:
-      return hipErrorInvalidValue;  // the context's validation admits no other width
-  }
-  return hipGetLastError();
-}
-}  // namespace
-
 hipError_t launch_channel(const NetDev& net, const mca_channel* ch, const Aux* aux, int K,
-                          float* partial, int ntiles, int k_mode, DevState* st,
-                          const double* dL, hipStream_t s) {
+                          const ChannelLists& lists, float* partial, int nchan, int k_mode,
+                          DevState* st, const double* dL, hipStream_t s) {
   const bool commit = k_mode != -2;
-  const dim3 grid((unsigned)ntiles, commit ? 1u : (unsigned)K);
-  hipError_t e = (net.C == 10)
-                     ? launch_width<10>(net, grid, ch, aux, partial, ntiles, k_mode, st, s)
-                     : launch_width<kCMax>(net, grid, ch, aux, partial, ntiles, k_mode, st, s);
+  auto go = [&](auto w, auto act) {
+    constexpr int W = decltype(w)::value, ACT = decltype(act)::value;
+    auto run = [&](auto com) {
+      typedef Dense<W, decltype(com)::value> D;
+      hipLaunchKernelGGL(k_channel_rows, dim3(commit ? 1 : K), dim3(kListThreads), 0, s, net, ch, aux, lists,
+                         partial, nchan, D::T, K, k_mode, st);
+      // nets of two layers have no layer between the walk and the logits
+      if (net.L < 3) return;
+      const int64_t tiles = ((net.N + D::T - 1) / D::T + 1) * (commit ? 1 : K);
+      const int64_t most = kChannelBlocks * D::blocks_per_cu;
+      hipLaunchKernelGGL((k_channel<W, ACT, decltype(com)::value>), dim3((unsigned)(tiles < most ? tiles : most)),
+                         dim3(D::threads), 0, s, net, ch, lists, partial, nchan, K, k_mode, st);
+    };
+    if (commit) run(std::true_type{});
+    else run(std::false_type{});
+    return hipGetLastError();
+  };
+  auto by_act = [&](auto w) {
+    if (net.act == MCA_ACT_TANH) return go(w, std::integral_constant<int, MCA_ACT_TANH>{});
+    if (net.act == MCA_ACT_RELU) return go(w, std::integral_constant<int, MCA_ACT_RELU>{});
+    return go(w, std::integral_constant<int, MCA_ACT_GAUSS>{});
+  };
+  hipError_t e;
+  switch (net.widths[1]) {
+    case 256: e = by_act(std::integral_constant<int, 256>{}); break;
+    case 512: e = by_act(std::integral_constant<int, 512>{}); break;
+    case 1024: e = by_act(std::integral_constant<int, 1024>{}); break;
+    default: return hipErrorInvalidValue;  // the context's validation admits no other width
+  }
   if (e != hipSuccess || !commit) return e;
   hipLaunchKernelGGL(k_channel_weights, dim3(1), dim3(64), 0, s, net, ch, k_mode, st, dL);
   return hipGetLastError();

@@ -131,7 +131,7 @@ struct DevState {
   uint64_t steps, evaluated, accepted, wasted, tie;
   uint64_t trace_base;   // step index stored at trace slot 0
   uint32_t sel_done;     // blocks of the selection kernel done (zero between launches)
-  uint32_t pad32;
+  uint32_t list_done;    // blocks of the listing kernel done (zero between launches)
   uint64_t pad[5];
 };
 static_assert(sizeof(DevState) <= 256, "state block");

@@ -89,6 +89,7 @@ struct Layout {
   size_t cols = 0, nnz = 0;  // nonzero entries of layer L-3 candidates' W_{L-2} columns
   size_t rows = 0, rda = 0, rcnt = 0, pchain = 0;  // deep nets: affected samples, tile sums
   size_t wf = 0;                                    // split copy of the dense layers' weights
+  size_t cap = 0, cf = 0, cfirst = 0;               // channel mutations: the listed samples' path units
   size_t chans = 0, pchan = 0;                      // channel mutations: records, tile sums
   size_t pnorm = 0;                                 // nets with biases / normalization: tile sums
   size_t aug[MCA_MAX_LAYERS] = {};  // the augmented matrices as the host has them
@@ -404,6 +405,13 @@ Layout make_layout(const mca_net_desc* net, int64_t N, int32_t k_max) {
     lo.nchan = mca::channel_tiles(N, net->widths[1]);
     lo.chans = take((size_t)k_max * sizeof(mca_channel));
     lo.pchan = take((size_t)k_max * lo.nchan * sizeof(float));
+    lo.rows = take((size_t)k_max * N * sizeof(int32_t));
+    lo.rda = take((size_t)k_max * N * sizeof(float));
+    lo.cap = take((size_t)k_max * N * sizeof(float));
+    lo.cf = take((size_t)k_max * N * sizeof(int32_t));
+    lo.rcnt = take((size_t)2 * k_max * sizeof(int32_t));
+    lo.cfirst = take((size_t)(2 * k_max + 1) * sizeof(int32_t));
+    lo.wf = take((size_t)mca::split_size(net->widths[1], L) * sizeof(uint16_t));
   }
   // persistent loop: tiles of T samples (16..64), one workgroup each; the
   // partial sums are sized for the smallest tile
@@ -449,6 +457,7 @@ struct mca_ctx {
   bool chan = false;             // candidates are channel mutations (Sec. 2.3)
   mca_channel* chans = nullptr;  // their records
   float* pchan = nullptr;        // their tile sums
+  mca::ChannelLists chan_lists{};  // the samples their changes reach past the path
   bool norm = false;             // biases and / or normalized hidden fields (Sec. 2.1)
   mca::NormDev nd{};             // normalization statistics
   float* pnorm = nullptr;        // tile sums of the dense evaluation
@@ -753,7 +762,7 @@ hipError_t eval_into(mca_ctx* ctx, const NetDev& net, const Bufs& b, int K, bool
                             ctx->lo.nnorm, -2,
                             ctx->st, b.dl, ctx->stream);
   if (ctx->chan)
-    return mca::launch_channel(net, ctx->chans, b.aux, K, ctx->pchan, ctx->lo.nchan, -2,
+    return mca::launch_channel(net, ctx->chans, b.aux, K, ctx->chan_lists, ctx->pchan, ctx->lo.nchan, -2,
                                ctx->st, b.dl, ctx->stream);
   if (ctx->tf)
     return mca::tf_launch_eval(ctx->tfd, ctx->tfh, b.cands, b.aux, K, false, b.partial,
@@ -824,7 +833,7 @@ hipError_t commit_all(mca_ctx* ctx, const NetDev& net, int k, int K) {
                             ctx->pnorm, ctx->lo.nnorm, k,
                             ctx->st, ctx->dl, ctx->stream);
   if (ctx->chan)
-    return mca::launch_channel(net, ctx->chans, ctx->aux, 0, ctx->pchan, ctx->lo.nchan, k,
+    return mca::launch_channel(net, ctx->chans, ctx->aux, 0, ctx->chan_lists, ctx->pchan, ctx->lo.nchan, k,
                                ctx->st, ctx->dl, ctx->stream);
   if (ctx->tf)
     return mca::tf_launch_commit(ctx->tfd, ctx->tfh, ctx->cands, ctx->aux, ctx->dl, ctx->st, k,
@@ -1110,13 +1119,16 @@ int mca_init(mca_ctx** out, const mca_net_desc* net, const float* const* params,
   }
   ctx->chan = net->mutation != MCA_MUTATE_SINGLE;
   const bool deep = L >= 4 && !ctx->chan && !ctx->norm;
-  const bool listed = deep || ctx->norm;  // kernels that list the samples a candidate moves
+  const bool listed = deep || ctx->norm || ctx->chan;  // kernels that list the samples a candidate moves
   nd.WF = listed ? (uint16_t*)(ws + lo.wf) : nullptr;
   ctx->rows = listed ? (int*)(ws + lo.rows) : nullptr;
   ctx->rda = listed ? (float*)(ws + lo.rda) : nullptr;
   ctx->rcnt = listed ? (int*)(ws + lo.rcnt) : nullptr;
   ctx->pchain = deep ? (float*)(ws + lo.pchain) : nullptr;
   ctx->chans = ctx->chan ? (mca_channel*)(ws + lo.chans) : nullptr;
+  if (ctx->chan)
+    ctx->chan_lists = mca::ChannelLists{ctx->rows, ctx->rda, (float*)(ws + lo.cap), (int*)(ws + lo.cf),
+                                        ctx->rcnt, (int*)(ws + lo.cfirst)};
   ctx->pchan = ctx->chan ? (float*)(ws + lo.pchan) : nullptr;
   if (ctx->chan) ctx->use_loop = false;
   ctx->cands = (mca_cand*)(ws + lo.cands);
