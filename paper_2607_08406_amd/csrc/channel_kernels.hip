@@ -21,7 +21,7 @@
 // the others are listed, those of f = 1 first, and blocks of k_channel take tiles
 // of T of them (dense_tile.hpp).  On 784-1024x3-10 with ReLU a tenth of the
 // samples need the dense layer, a fifth a rank-1 second layer: 16 channels on 8192
-// samples, with the products on bf16 parts, 5.4 -> 0.61 ms.
+// samples, with the products on bf16 parts, 5.4 -> 0.41 ms.
 // The commit runs the same arithmetic for the chosen channel and moves every
 // cached field by its change; a last kernel writes the path's weights.
 #include <type_traits>
@@ -36,6 +36,11 @@ namespace {
 // Blocks of k_channel per unit of residency: one a CU, and a second round's worth
 // so that a slow one is not waited for.
 constexpr int kChannelBlocks = 512;
+
+// Samples of a listing block, and its tile sums: the tiles of its two lists, at
+// most one part-filled tile more, and the walked samples.
+constexpr int kSegU = 2, kSegment = kSegU * kListThreads;
+__host__ __device__ constexpr int segment_slots(int T) { return (kSegment + T - 1) / T + 2; }
 
 // The channel of draw (t, k): 2L + 1 words of the Philox blocks at counters
 // (t, k, 2 + b, 0), four words per block, in order.
@@ -125,13 +130,17 @@ __device__ __forceinline__ void load_path(const NetDev& net, const mca_channel& 
   __syncthreads();
 }
 
-// Block k (eval) or the committed channel: every sample's walk along the path.
-// Samples that break off at layer f <= L-2 are listed in sample order, f = 1 from
-// the front of the channel's part of the lists, later ones from its back: the
-// sample, the changed activation entering layer f, the path unit's new one, f.
-// The others' loss changes are summed here: partial[k * nchan + nchan - 1].
-// An evaluation's last block then adds up the tiles of all lists (those of f = 1
-// first): lists.first[e], e <= 2 K.  A commit stores the walked fields.
+// Block (s, k) (eval) or (s, 0) for the committed channel: the walk of the samples
+// of segment s along the path.  Samples that break off at layer f <= L-2 are
+// listed in sample order, f = 1 from the front of the segment's part of the
+// channel's lists, later ones from its back: the sample, the changed activation
+// entering layer f, the path unit's new one, f.  The others' loss changes are
+// summed here, the segment's last tile sum.  The grid's last block then adds up
+// the tiles of all lists (those of f = 1 first): lists.first[e], e = (list K + k)
+// S + s.  A commit stores the walked fields.  Segments of 2048 samples: the walk
+// is a chain of dependent loads, so its time is one block's; more samples a block
+// take longer, fewer leave more part-filled tiles (8192 samples, 16 channels: 76
+// us with one block a channel, 24 with these).
 __global__ __launch_bounds__(kListThreads) void k_channel_rows(NetDev net_arg, const mca_channel* chans,
                                                                const Aux* aux, ChannelLists lists, float* partial,
                                                                int nchan, int T, int K, int k_mode, DevState* st) {
@@ -139,42 +148,45 @@ __global__ __launch_bounds__(kListThreads) void k_channel_rows(NetDev net_arg, c
   stage_net(net, net_arg);
   __shared__ int units[MCA_MAX_LAYERS + 1];
   __shared__ float de[MCA_MAX_LAYERS];
-  __shared__ int counts[2][64];  // [list][u][wave]
+  __shared__ int counts[2][32];  // [list][u][wave]
   __shared__ double sums[kListThreads / 64];
   __shared__ int last;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const bool commit = k_mode != -2;
-  const int k = commit ? ((k_mode >= 0) ? k_mode : st->chosen) : (int)blockIdx.x;
+  const int k = commit ? ((k_mode >= 0) ? k_mode : st->chosen) : (int)blockIdx.y;
+  const int S = (int)gridDim.x, seg = (int)blockIdx.x, nl = commit ? 1 : K;
   if (k < 0) {
-    if (tid == 0) lists.first[0] = lists.first[1] = lists.first[2] = 0;
+    if (tid == 0) lists.first[2 * S] = 0;
     return;
   }
   const int L = net.L, C = net.C, act = net.act;
   const float gamma = net.gamma;
   const int64_t N = net.N, Ns = net.Ns;
   const bool scored = commit || aux[k].valid;  // rejected unevaluated: selection gives +inf
-  int base[2] = {0, 0};
+  int count[2] = {0, 0};
   double sum = 0.0;
-  if (!commit)
-    for (int t = tid; t < nchan; t += kListThreads) partial[(int64_t)k * nchan + t] = 0.f;
+  float* const sums_out = partial + (int64_t)k * nchan + seg * segment_slots(T);
+  if (!commit && tid < segment_slots(T)) sums_out[tid] = 0.f;
   if (scored) {
     load_path(net, chans[k], units, de);
-    for (int64_t n0 = 0; n0 < N; n0 += kListU * kListThreads) {
-      int64_t ns[kListU];
-      float d[kListU], ap[kListU];  // the last walked unit's change and new activation
-      int f[kListU];                // the layer they enter
+    const int64_t n0 = (int64_t)seg * kSegment;
+    const int64_t part = (int64_t)k * N + n0, part_n = N - n0 < kSegment ? N - n0 : kSegment;
+    {
+      int64_t ns[kSegU];
+      float d[kSegU], ap[kSegU];  // the last walked unit's change and new activation
+      int f[kSegU];                // the layer they enter
       {
         float* z0 = net.Z[0] + (int64_t)units[1] * Ns;
-        float x[kListU], z[kListU];
+        float x[kSegU], z[kSegU];
 #pragma unroll
-        for (int u = 0; u < kListU; ++u) {
+        for (int u = 0; u < kSegU; ++u) {
           const int64_t n = n0 + u * kListThreads + tid;
           ns[u] = n < N ? n : N - 1;
           x[u] = gload(&net.XT[(int64_t)units[0] * Ns + ns[u]]);
           z[u] = gload(&z0[ns[u]]);
         }
 #pragma unroll
-        for (int u = 0; u < kListU; ++u) {
+        for (int u = 0; u < kSegU; ++u) {
           const float dz = de[0] * x[u];
           d[u] = dphi(z[u], dz, act, gamma);
           ap[u] = act_fn(z[u] + dz, act, gamma);
@@ -184,11 +196,11 @@ __global__ __launch_bounds__(kListThreads) void k_channel_rows(NetDev net_arg, c
       }
       for (int m = 1; m <= L - 2; ++m) {
         float* zm = net.Z[m] + (int64_t)units[m + 1] * Ns;
-        float z[kListU];
+        float z[kSegU];
 #pragma unroll
-        for (int u = 0; u < kListU; ++u) z[u] = gload(&zm[ns[u]]);
+        for (int u = 0; u < kSegU; ++u) z[u] = gload(&zm[ns[u]]);
 #pragma unroll
-        for (int u = 0; u < kListU; ++u) {
+        for (int u = 0; u < kSegU; ++u) {
           if (f[u] == m && d[u] == 0.f) {
             const float dz = de[m] * ap[u];
             d[u] = dphi(z[u], dz, act, gamma);
@@ -198,9 +210,9 @@ __global__ __launch_bounds__(kListThreads) void k_channel_rows(NetDev net_arg, c
           }
         }
       }
-      uint64_t b[2][kListU];
+      uint64_t b[2][kSegU];
 #pragma unroll
-      for (int u = 0; u < kListU; ++u) {
+      for (int u = 0; u < kSegU; ++u) {
         const bool in = n0 + u * kListThreads + tid < N;
         b[0][u] = __ballot(in && f[u] <= L - 2 && f[u] == 1);
         b[1][u] = __ballot(in && f[u] <= L - 2 && f[u] > 1);
@@ -244,7 +256,7 @@ __global__ __launch_bounds__(kListThreads) void k_channel_rows(NetDev net_arg, c
       __syncthreads();
 #pragma unroll
       for (int g = 0; g < 2; ++g) {
-        const int mine = counts[g][lane];
+        const int mine = lane < 32 ? counts[g][lane] : 0;
         int incl = mine;
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
@@ -252,20 +264,19 @@ __global__ __launch_bounds__(kListThreads) void k_channel_rows(NetDev net_arg, c
           if (lane >= o) incl += w;
         }
 #pragma unroll
-        for (int u = 0; u < kListU; ++u) {
-          const int off = base[g] + __shfl(incl - mine, u * (kListThreads / 64) + wave, 64);
+        for (int u = 0; u < kSegU; ++u) {
+          const int off = __shfl(incl - mine, u * (kListThreads / 64) + wave, 64);
           if ((b[g][u] >> lane) & 1ull) {
             const int64_t e = off + (int)__popcll(b[g][u] & ((1ull << lane) - 1ull));
-            const int64_t at = (int64_t)k * N + (g == 0 ? e : N - 1 - e);
+            const int64_t at = part + (g == 0 ? e : part_n - 1 - e);
             gstore(&lists.rows[at], (int)ns[u]);
             gstore(&lists.d[at], d[u]);
             gstore(&lists.ap[at], ap[u]);
             gstore(&lists.f[at], f[u]);
           }
         }
-        base[g] += __shfl(incl, 63, 64);
+        count[g] = __shfl(incl, 63, 64);
       }
-      __syncthreads();
     }
   }
   if (!commit && scored) {
@@ -277,24 +288,24 @@ __global__ __launch_bounds__(kListThreads) void k_channel_rows(NetDev net_arg, c
     if (tid == 0) {
       double s = 0.0;
       for (int w = 0; w < kListThreads / 64; ++w) s += sums[w];
-      partial[(int64_t)k * nchan + nchan - 1] = (float)s;
+      sums_out[segment_slots(T) - 1] = (float)s;
     }
   }
-  // the tiles of every list, in order (a commit: of its channel's two)
-  const int nl = commit ? 1 : K;
+  // the tiles of every list, in order (a commit: of its channel's)
+  const int ne = 2 * nl * S, e_k = (commit ? 0 : k) * S + seg;
   if (tid == 0) {
-    __hip_atomic_store(&lists.cnt[commit ? 0 : k], base[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&lists.cnt[commit ? 1 : K + k], base[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&lists.cnt[e_k], count[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&lists.cnt[nl * S + e_k], count[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __threadfence();
-    last = commit || atomicAdd(&st->list_done, 1u) == gridDim.x - 1;
+    last = atomicAdd(&st->list_done, 1u) == gridDim.x * gridDim.y - 1;
   }
   __syncthreads();
   if (!last || wave != 0) return;
   __threadfence();
   int total = 0;
-  for (int e0 = 0; e0 < 2 * nl; e0 += 64) {
+  for (int e0 = 0; e0 < ne; e0 += 64) {
     const int e = e0 + lane;
-    const int c = e < 2 * nl ? __hip_atomic_load(&lists.cnt[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+    const int c = e < ne ? __hip_atomic_load(&lists.cnt[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
     const int tiles = (c + T - 1) / T;
     int incl = tiles;
 #pragma unroll
@@ -302,7 +313,7 @@ __global__ __launch_bounds__(kListThreads) void k_channel_rows(NetDev net_arg, c
       const int w = __shfl_up(incl, o, 64);
       if (lane >= o) incl += w;
     }
-    if (e < 2 * nl) lists.first[e + 1] = total + incl;
+    if (e < ne) lists.first[e + 1] = total + incl;
     total += __shfl(incl, 63, 64);
   }
   if (lane == 0) {
@@ -315,14 +326,14 @@ __global__ __launch_bounds__(kListThreads) void k_channel_rows(NetDev net_arg, c
 template <int W, int ACT, bool commit>
 __global__ __launch_bounds__((Dense<W, commit>::threads), (Dense<W, commit>::blocks_per_cu)) void k_channel(
     NetDev net_arg, const mca_channel* chans, ChannelLists lists, float* partial, int nchan, int K,
-    int k_mode, const DevState* st) {
+    int S, int k_mode, const DevState* st) {
   typedef Dense<W, commit> D;
-  constexpr int T = D::T, SB = D::SB, H = D::H, NW = D::NW, RS = D::RS;
-  const int nl = commit ? 1 : K;
-  if ((int)blockIdx.x >= lists.first[2 * nl]) return;
+  constexpr int T = D::T, SB = D::SB, H = D::H, NW = D::NW;
+  const int nl = commit ? 1 : K, ne = 2 * nl * S;
+  if ((int)blockIdx.x >= lists.first[ne]) return;
   __shared__ NetDev net;
   stage_net(net, net_arg);
-  __shared__ __attribute__((aligned(16))) uint16_t ta[3 * T * RS];
+  __shared__ __attribute__((aligned(16))) typename D::Tile ta;
   __shared__ int rown[T], rowf[T];
   __shared__ float rowd[T], rowa[T], dls[T];
   __shared__ int units[MCA_MAX_LAYERS + 1];
@@ -333,13 +344,13 @@ __global__ __launch_bounds__((Dense<W, commit>::threads), (Dense<W, commit>::blo
   const int tid = threadIdx.x, L = net.L;
   const float gamma = net.gamma;
   const int64_t N = net.N, Ns = net.Ns;
-  const int total = lists.first[2 * nl];
+  const int total = lists.first[ne];
   for (int w = blockIdx.x; w < total; w += gridDim.x) {
     __syncthreads();  // the last item's rows and sums are read
     if (tid < 64) {   // the list of item w: the first whose end lies past it
-      for (int e0 = 0; e0 < 2 * nl; e0 += 64) {
+      for (int e0 = 0; e0 < ne; e0 += 64) {
         const int e = e0 + tid;
-        const uint64_t past = __ballot(e < 2 * nl && lists.first[e + 1] > w);
+        const uint64_t past = __ballot(e < ne && lists.first[e + 1] > w);
         if (past != 0ull) {
           if (tid == 0) {
             const int e1 = e0 + (int)__ffsll((unsigned long long)past) - 1;
@@ -352,14 +363,16 @@ __global__ __launch_bounds__((Dense<W, commit>::threads), (Dense<W, commit>::blo
     }
     __syncthreads();
     const int e1 = item[0], tile = item[1];
-    const bool front = e1 < nl;
-    const int k = commit ? ((k_mode >= 0) ? k_mode : st->chosen) : (front ? e1 : e1 - nl);
+    const bool front = e1 < nl * S;
+    const int ks = front ? e1 : e1 - nl * S, seg = ks % S;
+    const int k = commit ? ((k_mode >= 0) ? k_mode : st->chosen) : ks / S;
     const int n_rows = lists.cnt[e1];
     load_path(net, chans[k], units, de);
     if (tid < T) {
       const int e = tile * T + tid;
       const bool in = e < n_rows;
-      const int64_t at = (int64_t)k * N + (front ? (in ? e : 0) : N - 1 - (in ? e : 0));
+      const int64_t n0 = (int64_t)seg * kSegment, n1 = N - n0 < kSegment ? N : n0 + kSegment;
+      const int64_t at = (int64_t)k * N + (front ? n0 + (in ? e : 0) : n1 - 1 - (in ? e : 0));
       rown[tid] = in ? gload(&lists.rows[at]) : -1;
       rowd[tid] = in ? gload(&lists.d[at]) : 0.f;
       rowa[tid] = in ? gload(&lists.ap[at]) : 0.f;
@@ -374,7 +387,8 @@ __global__ __launch_bounds__((Dense<W, commit>::threads), (Dense<W, commit>::blo
     typename D::Acc acc, zc;
     for (int m = m0; m <= L - 2; ++m) {
       const int jn = units[m + 1];
-      t.fields(net.Z[m], Ns, zc);
+      // (a 1024-unit product has no registers for the fields beside it)
+      if constexpr (!D::kF32) t.fields(net.Z[m], Ns, zc);
       if (m > m0) {
         t.product(net, m, ta, acc);
       } else {
@@ -385,6 +399,7 @@ __global__ __launch_bounds__((Dense<W, commit>::threads), (Dense<W, commit>::blo
 #pragma unroll
             for (int cb = 0; cb < 4; ++cb) acc[h][sb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
+      if constexpr (D::kF32) t.fields(net.Z[m], Ns, zc);
       // the rank-1 term of the rows whose changed unit enters here, and the path
       // weight's own change
 #pragma unroll
@@ -448,17 +463,18 @@ __global__ __launch_bounds__((Dense<W, commit>::threads), (Dense<W, commit>::blo
     if (!commit && tid == 0) {
       float v = 0.f;
       for (int r = 0; r < T; ++r) v += dls[r];
-      // front tiles from the start of the channel's sums, back tiles after them
-      const int slot = front ? tile : (lists.cnt[k] + T - 1) / T + tile;
-      partial[(int64_t)k * nchan + slot] = v;
+      // front tiles from the start of the segment's sums, back tiles after them
+      const int slot = front ? tile : (lists.cnt[ks] + T - 1) / T + tile;
+      partial[(int64_t)k * nchan + seg * segment_slots(T) + slot] = v;
     }
   }
 }
 
+int channel_segments(int64_t n_samples) { return (int)((n_samples + kSegment - 1) / kSegment); }
+
 int channel_tiles(int64_t n_samples, int w) {
   const int T = w == 256 ? Dense<256, false>::T : (w == 512 ? Dense<512, false>::T : Dense<1024, false>::T);
-  // two lists a channel, at most one part-filled tile more, and the walked sum
-  return (int)((n_samples + T - 1) / T) + 2;
+  return channel_segments(n_samples) * segment_slots(T);
 }
 
 // After the field commit: the path's new weights (and the transposed copy of
@@ -503,14 +519,15 @@ hipError_t launch_channel(const NetDev& net, const mca_channel* ch, const Aux* a
     constexpr int W = decltype(w)::value, ACT = decltype(act)::value;
     auto run = [&](auto com) {
       typedef Dense<W, decltype(com)::value> D;
-      hipLaunchKernelGGL(k_channel_rows, dim3(commit ? 1 : K), dim3(kListThreads), 0, s, net, ch, aux, lists,
+      const int S = channel_segments(net.N);
+      hipLaunchKernelGGL(k_channel_rows, dim3(S, commit ? 1 : K), dim3(kListThreads), 0, s, net, ch, aux, lists,
                          partial, nchan, D::T, K, k_mode, st);
       // nets of two layers have no layer between the walk and the logits
       if (net.L < 3) return;
-      const int64_t tiles = ((net.N + D::T - 1) / D::T + 1) * (commit ? 1 : K);
+      const int64_t tiles = (int64_t)S * segment_slots(D::T) * (commit ? 1 : K);
       const int64_t most = kChannelBlocks * D::blocks_per_cu;
       hipLaunchKernelGGL((k_channel<W, ACT, decltype(com)::value>), dim3((unsigned)(tiles < most ? tiles : most)),
-                         dim3(D::threads), 0, s, net, ch, lists, partial, nchan, K, k_mode, st);
+                         dim3(D::threads), 0, s, net, ch, lists, partial, nchan, K, S, k_mode, st);
     };
     if (commit) run(std::true_type{});
     else run(std::false_type{});

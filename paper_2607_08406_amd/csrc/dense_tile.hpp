@@ -5,10 +5,13 @@
 // registers, in the layout the matrix cores leave: lane (q, li) of wave w holds,
 // for rows 16 sb + 4 q + v, units 64 (H w + h) + 16 cb + li.
 //
-// T by width: as many rows as leave the parts room in LDS.  256 units: 48 rows,
-// two blocks a CU (one's products beside the other's transfer functions); 512:
-// 32 rows; 1024: 16 rows, each wave two blocks of 64 units in turn.  Every
-// block reads a layer's 6 W^2 bytes of weights, so fewer rows cost L2 reads.
+// T by width.  Every block reads a layer's 6 W^2 bytes of weights, so fewer rows
+// cost reads, of L2 and, where a layer's weights pass its 4 MiB, of the cache
+// behind it.  256 units: 48 rows, two blocks a CU (one's products beside the
+// other's transfer functions); 512: 32 rows; 1024: 32 rows whose changes stay
+// fp32 in LDS (their parts would leave room for 16) and are split by each wave as
+// it reads them, 88 instructions beside 96 matrix instructions (784-1024x3-10
+// channels, 16 of them on 8192 samples: 537 -> 381 us).
 #pragma once
 
 #include "split_mma.hpp"
@@ -21,10 +24,13 @@ namespace mca {
 template <int W, bool COMMIT>
 struct Dense {
   static_assert(W == 256 || W == 512 || W == 1024, "hidden widths of the dense kernels");
-  static constexpr int T = W == 1024 || COMMIT ? 16 : (W == 512 ? 32 : 48);
+  static constexpr int T = COMMIT ? 16 : (W == 256 ? 48 : 32);
+  static constexpr bool kF32 = W == 1024;      // the tile holds fp32 changes, not their parts
   static constexpr int NW = W == 256 ? 4 : 8;  // waves
   static constexpr int H = W / 64 / NW;        // blocks of 64 units per wave
-  static constexpr int SB = T / 16, RS = W + 8, threads = 64 * NW;
+  static constexpr int SB = T / 16, RS = kF32 ? W + 4 : W + 8, threads = 64 * NW;
+  static constexpr int tile_bytes = kF32 ? T * RS * 4 : 3 * T * RS * 2;
+  typedef unsigned char Tile[tile_bytes];
   static constexpr int blocks_per_cu = W == 256 && !COMMIT ? 2 : 1;
   typedef f32x4 Acc[H][SB][4];
 
@@ -75,43 +81,73 @@ struct Dense {
           for (int v = 0; v < 4; ++v)
             if (nrow[sb][v] >= 0) gstore(&Z[(int64_t)unit(h, cb) * Ns + nrow[sb][v]], z[h][sb][cb][v] + dz[h][sb][cb][v]);
   }
-  // The changes d into the tile's parts.
-  __device__ __forceinline__ void write_tile(uint16_t* ta, const Acc& d) const {
+  // The changes d into the tile.
+  __device__ __forceinline__ void write_tile(Tile& tile, const Acc& d) const {
 #pragma unroll
     for (int h = 0; h < H; ++h)
 #pragma unroll
       for (int sb = 0; sb < SB; ++sb)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          const Split2 s0 = split2(d[h][sb][0][v], d[h][sb][1][v]), s1 = split2(d[h][sb][2][v], d[h][sb][3][v]);
-          uint16_t* at = ta + (16 * sb + 4 * q + v) * RS + 64 * (H * wave + h) + 4 * li;
+          const int at = (16 * sb + 4 * q + v) * RS + 64 * (H * wave + h) + 4 * li;
+          if constexpr (kF32) {
+            *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(tile) + at) =
+                f32x4{d[h][sb][0][v], d[h][sb][1][v], d[h][sb][2][v], d[h][sb][3][v]};
+          } else {
+            const Split2 s0 = split2(d[h][sb][0][v], d[h][sb][1][v]), s1 = split2(d[h][sb][2][v], d[h][sb][3][v]);
 #pragma unroll
-          for (int p = 0; p < 3; ++p) *reinterpret_cast<uint2*>(at + p * T * RS) = make_uint2(s0.p[p], s1.p[p]);
+            for (int p = 0; p < 3; ++p)
+              *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(tile) + at + p * T * RS) = make_uint2(s0.p[p], s1.p[p]);
+          }
         }
   }
   // acc = tile x the split weights of dense layer m.
-  __device__ __forceinline__ void product(const NetDev& net, int m, const uint16_t* ta, Acc& acc) const {
+  __device__ __forceinline__ void product(const NetDev& net, int m, const Tile& tile, Acc& acc) const {
 #pragma unroll
-    for (int h = 0; h < H; ++h) {
+    for (int h = 0; h < H; ++h)
 #pragma unroll
       for (int sb = 0; sb < SB; ++sb)
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb) acc[h][sb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-      const uint16_t* wf = net.WF + split_layer(W, m) + (int64_t)4 * (H * wave + h) * (W / 32) * 3 * 512;
-      split_product<W, T, RS>(ta, wf, lane, acc[h]);
+    const uint16_t* wf = net.WF + split_layer(W, m) + (int64_t)4 * H * wave * (W / 32) * 3 * 512;
+    if constexpr (kF32) {
+      static_assert(H == 2, "the two blocks of units alternate, each in its own registers");
+      constexpr int64_t kH = (int64_t)4 * (W / 32) * 3 * 512;
+      constexpr int KS = W / 32;
+      bf16x8 b0[4][3], b1[4][3];
+      fetch_weights<W>(wf, lane, 0, b0);
+#pragma unroll 1
+      for (int ks = 0; ks < KS; ++ks) {
+        bf16x8 a[SB][3];
+        fetch_weights<W>(wf + kH, lane, ks, b1);
+        split_rows<RS>(reinterpret_cast<const float*>(tile), lane, ks, a);
+        multiply_parts(a, b0, acc[0]);
+        fetch_weights<W>(wf, lane, ks + 1 < KS ? ks + 1 : 0, b0);
+        multiply_parts(a, b1, acc[1]);
+      }
+    } else {
+      static_assert(kF32 || H == 1, "one block of units a wave");
+      split_product<W, T, RS>(reinterpret_cast<const uint16_t*>(tile), wf, lane, acc[0]);
     }
   }
   // The wave's share of the logits' change (64 H of the k): partial sums of
   // rows x 16 padded classes.
-  __device__ __forceinline__ void logit_part(const NetDev& net, const uint16_t* ta, f32x4 (&lg)[SB][1]) const {
+  __device__ __forceinline__ void logit_part(const NetDev& net, const Tile& tile, f32x4 (&lg)[SB][1]) const {
     const uint16_t* wf = net.WF + split_layer(W, net.L - 1);
 #pragma unroll
     for (int sb = 0; sb < SB; ++sb) lg[sb][0] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int u = 0; u < 2 * H; ++u) {
+      const int ks = 2 * H * wave + u;
       bf16x8 b[1][3];
-      fetch_weights<W>(wf, lane, 2 * H * wave + u, b);
-      multiply_step<T, RS>(ta, lane, 2 * H * wave + u, b, lg);
+      fetch_weights<W>(wf, lane, ks, b);
+      if constexpr (kF32) {
+        bf16x8 a[SB][3];
+        split_rows<RS>(reinterpret_cast<const float*>(tile), lane, ks, a);
+        multiply_parts(a, b, lg);
+      } else {
+        multiply_step<T, RS>(reinterpret_cast<const uint16_t*>(tile), lane, ks, b, lg);
+      }
     }
   }
 };

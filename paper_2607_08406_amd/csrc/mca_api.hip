@@ -409,8 +409,9 @@ Layout make_layout(const mca_net_desc* net, int64_t N, int32_t k_max) {
     lo.rda = take((size_t)k_max * N * sizeof(float));
     lo.cap = take((size_t)k_max * N * sizeof(float));
     lo.cf = take((size_t)k_max * N * sizeof(int32_t));
-    lo.rcnt = take((size_t)2 * k_max * sizeof(int32_t));
-    lo.cfirst = take((size_t)(2 * k_max + 1) * sizeof(int32_t));
+    const size_t lists = (size_t)2 * k_max * mca::channel_segments(N);
+    lo.rcnt = take(lists * sizeof(int32_t));
+    lo.cfirst = take((lists + 1) * sizeof(int32_t));
     lo.wf = take((size_t)mca::split_size(net->widths[1], L) * sizeof(uint16_t));
   }
   // persistent loop: tiles of T samples (16..64), one workgroup each; the

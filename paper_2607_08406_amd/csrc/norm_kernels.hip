@@ -103,10 +103,10 @@ __global__ __launch_bounds__((Dense<W, commit>::threads), (Dense<W, commit>::blo
     NetDev net_arg, NormDev nd, const mca_cand* cands, const int* rows, const float* vals,
     const int* cnt, float* partial, int ntiles, int K, int k_mode, const DevState* st) {
   typedef Dense<W, commit> D;
-  constexpr int T = D::T, SB = D::SB, H = D::H, NW = D::NW, RS = D::RS;
+  constexpr int T = D::T, SB = D::SB, H = D::H, NW = D::NW;
   __shared__ NetDev net;
   stage_net(net, net_arg);
-  __shared__ __attribute__((aligned(16))) uint16_t ta[3 * T * RS];
+  __shared__ __attribute__((aligned(16))) typename D::Tile ta;
   __shared__ int rown[T];
   __shared__ float rowv[T];
   __shared__ __attribute__((aligned(16))) float red[2][NW][T];  // row sums by wave
@@ -288,8 +288,10 @@ __global__ __launch_bounds__((Dense<W, commit>::threads), (Dense<W, commit>::blo
       finish(s, false);
       // 2. dense layers
       for (int m = s + 1; m <= L - 2; ++m) {
-        t.fields(net.Z[m], Ns, zc);
+        // (a 1024-unit product has no registers for the fields beside it)
+        if constexpr (!D::kF32) t.fields(net.Z[m], Ns, zc);
         t.product(net, m, ta, acc);
+        if constexpr (D::kF32) t.fields(net.Z[m], Ns, zc);
         finish(m, true);
       }
       // 3. the logits: the last hidden layer's change through W_{L-1}

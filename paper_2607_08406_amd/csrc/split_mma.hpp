@@ -85,8 +85,22 @@ __device__ __forceinline__ void fetch_weights(const uint16_t* wf, int lane, int 
     for (int p = 0; p < 3; ++p) d[cb][p] = gload(wl + ((cb * (W / 32) + ks) * 3 + p) * 64);
 }
 
+// acc += a b over one step, from the parts of both; small terms first.
+template <int SB, int CB>
+__device__ __forceinline__ void multiply_parts(const bf16x8 (&a)[SB][3], const bf16x8 (&b)[CB][3],
+                                               f32x4 (&acc)[SB][CB]) {
+  constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+  for (int t = 0; t < 6; ++t)
+#pragma unroll
+    for (int sb = 0; sb < SB; ++sb)
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb)
+        acc[sb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[sb][pa[t]], b[cb][pb[t]], acc[sb][cb], 0, 0, 0);
+}
+
 // acc += rows 16 sb + li of the tile (part p of row r at tile + (p * T + r) *
-// RS, in bf16 values) times the weights b, over step ks; small terms first.
+// RS, in bf16 values) times the weights b, over step ks.
 template <int T, int RS, int SB, int CB>
 __device__ __forceinline__ void multiply_step(const uint16_t* tile, int lane, int ks, const bf16x8 (&b)[CB][3],
                                               f32x4 (&acc)[SB][CB]) {
@@ -96,14 +110,23 @@ __device__ __forceinline__ void multiply_step(const uint16_t* tile, int lane, in
   for (int sb = 0; sb < SB; ++sb)
 #pragma unroll
     for (int p = 0; p < 3; ++p) a[sb][p] = *reinterpret_cast<const bf16x8*>(al + (p * T + 16 * sb) * RS);
-  constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
+  multiply_parts(a, b, acc);
+}
+
+// The same from a tile of fp32 values (row r at tile + r * RS floats), split as
+// they are read.
+template <int RS, int SB>
+__device__ __forceinline__ void split_rows(const float* tile, int lane, int ks, bf16x8 (&a)[SB][3]) {
+  const float* al = tile + (lane & 15) * RS + 8 * (lane >> 4) + 32 * ks;
 #pragma unroll
-  for (int t = 0; t < 6; ++t)
+  for (int sb = 0; sb < SB; ++sb) {
+    const f32x4 x = *reinterpret_cast<const f32x4*>(al + 16 * sb * RS);
+    const f32x4 y = *reinterpret_cast<const f32x4*>(al + 16 * sb * RS + 4);
+    const Split2 s[4] = {split2(x[0], x[1]), split2(x[2], x[3]), split2(y[0], y[1]), split2(y[2], y[3])};
 #pragma unroll
-    for (int sb = 0; sb < SB; ++sb)
-#pragma unroll
-      for (int cb = 0; cb < CB; ++cb)
-        acc[sb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[sb][pa[t]], b[cb][pb[t]], acc[sb][cb], 0, 0, 0);
+    for (int p = 0; p < 3; ++p)
+      a[sb][p] = __builtin_bit_cast(bf16x8, make_uint4(s[0].p[p], s[1].p[p], s[2].p[p], s[3].p[p]));
+  }
 }
 
 // acc += (T x W tile) x (weights wf of the wave's 16 CB output units), the
