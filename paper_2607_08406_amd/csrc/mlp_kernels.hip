@@ -16,6 +16,7 @@
 #include "device_common.hpp"
 #include "mlp_kernels.hpp"
 #include "norm_kernels.hpp"
+#include "split_mma.hpp"
 
 namespace mca {
 
@@ -481,215 +482,173 @@ __global__ __launch_bounds__(kTile) void k_commit_column(NetDev net_arg, const m
 // the B tile is staged in LDS, then the per-sample losses and their mean
 // ---------------------------------------------------------------------------
 
-// C[M][ldc] = A[M][Kd] * f(B[Kd][ldb]), 64x64 tile per block, 4x4 per thread.
-// C = A op(B) (+ bias): op applies the transfer function to each input, after
-// normalizing it with its column's statistics when bmu is given
-// ((b - mu) / sqrt(S)); bias (may be null) adds one value per output row.
-template <int ACT>  // -1: identity, else MCA_ACT_*
-__global__ __launch_bounds__(256) void k_gemm_fwd(const float* __restrict__ A, int M, int Kd,
-                                                  const float* __restrict__ B, int64_t ldb,
-                                                  int64_t ncols, float* __restrict__ Cm,
-                                                  int64_t ldc, float gamma,
-                                                  const float* __restrict__ bmu,
-                                                  const float* __restrict__ bS,
-                                                  const float* __restrict__ bias) {
-  __shared__ float As[16][64 + 4];
-  __shared__ float Bs[16][64 + 4];
-  const int64_t m0 = (int64_t)blockIdx.y * 64, n0 = (int64_t)blockIdx.x * 64;
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  float acc[4][4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) acc[r][c] = 0.f;
-  for (int k0 = 0; k0 < Kd; k0 += 16) {
-    for (int e = threadIdx.x; e < 1024; e += 256) {
-      const int r = e >> 4, kk = e & 15;
-      const int64_t gm = m0 + r;
-      const int gk = k0 + kk;
-      As[kk][r] = (gm < M && gk < Kd) ? A[gm * Kd + gk] : 0.f;
-    }
-    for (int e = threadIdx.x; e < 1024; e += 256) {
-      const int kk = e >> 6, cc = e & 63;
-      const int gk = k0 + kk;
-      const int64_t gn = n0 + cc;
-      float v = 0.f;
-      if (gk < Kd && gn < ncols) {
-        v = B[(int64_t)gk * ldb + gn];
-        if (bmu != nullptr) v = (v - bmu[gn]) * (1.0f / sqrtf(bS[gn]));
-        if (ACT >= 0) v = act_fn(v, ACT, gamma);
-      }
-      Bs[kk][cc] = v;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float av[4], bv[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) av[r] = As[kk][ty * 4 + r];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) bv[c] = Bs[kk][tx * 4 + c];
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[r][c] = fmaf(av[r], bv[c], acc[r][c]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int64_t gm = m0 + ty * 4 + r;
-    if (gm >= M) continue;
-    const float b = (bias != nullptr) ? bias[gm] : 0.f;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int64_t gn = n0 + tx * 4 + c;
-      if (gn < ncols) Cm[gm * ldc + gn] = (bias != nullptr) ? acc[r][c] + b : acc[r][c];
-    }
-  }
-}
-
-// The same product on the matrix cores (v_mfma_f32_16x16x4f32), for Kd a
-// multiple of 16: a 128 x 128 tile of C per block, wave (wr, wc) its 64 x 64
-// quarter as four by four 16 x 16 MFMA tiles.  The reduction runs in chunks
-// of 16: A's rows (row-major, 16 k) staged as float4 and read back as float4
-// (lane group q holds k = 4 q + t of the chunk, t = 0..3, one per MFMA); B's
-// chunk ([16 k][128 columns], columns contiguous) transformed by op on its
-// way into LDS and read one value per MFMA (conflict-free: the 16 lanes of a
-// group read consecutive columns, the four groups rows 4 apart on a padded
-// row).  The next chunk's loads are in flight while the current one is
-// multiplied (double-buffered LDS).  Rows and columns beyond the matrix are
-// clamped on load and dropped on store.
-constexpr int kFwdT = 128;       // rows and columns of the block's tile
-constexpr int kFwdK = 16;        // reduction chunk
+// C[M][ldc] = A[M][Kd] op(B[Kd][ldb]) (+ bias): op applies the transfer
+// function to each input, after normalizing it with its column's statistics
+// when bmu is given ((b - mu) / sqrt(S)); bias (may be null) adds one value per
+// output row.
+//
+// fp32 operands as three bf16 parts each and six matrix products per 32 k
+// (split_mma.hpp).  A block takes 32 SB rows x 128 columns, wave (wr, wc) its
+// 16 SB x 64 part.  Chunks of 32 k: A's rows are read as float4 (single values
+// when Kd is not a multiple of four, ROW4 = false), B's as pairs of columns of
+// eight k rows, so that a thread holds the eight k that one LDS row's 16 bytes
+// take; both are split on their way into LDS ([part][row][32 k], part_at).  Column 2 p + b of
+// the tile sits in LDS row p + 64 b, so neighbouring columns end in one lane and
+// are stored together.  The next chunk's values are requested before the
+// products; the other block of the CU multiplies while this one splits.
+// 784 x 16384 weights on 10000 columns (257 GFLOP): 2.15 ms on fp32 matrix
+// instructions, 1.57 here, of which the six products are 0.62 at the matrix
+// cores' peak; splitting (700 vector cycles a chunk beside 1536) and LDS
+// traffic (1150) overlap them in part.  (Three blocks a CU fit only without
+// add_product's sums: 1.42 ms, at 1.6 times the fp32 error.)  1024 x 1024 on
+// 8192 columns: 153 -> 110 us.  What
+// lies beyond M and the columns is clamped on load and dropped on store, what
+// lies beyond Kd is zero in both operands.
+constexpr int kFwdT = 128;       // columns of the block's tile
+constexpr int kFwdK = 32;        // reduction chunk
 constexpr int kFwdThreads = 256;
 typedef float fwdx4 __attribute__((ext_vector_type(4)));
 
-template <int ACT>  // -1: identity, else MCA_ACT_*
-__global__ __launch_bounds__(kFwdThreads, 3) void k_gemm_fwd_mfma(
+template <int ACT, int SB, bool ROW4>  // ACT -1: identity, else MCA_ACT_*
+__global__ __launch_bounds__(kFwdThreads, SB == 4 ? 2 : 3) void k_gemm_fwd_split(
     const float* __restrict__ A, int M, int Kd, const float* __restrict__ B, int64_t ldb,
     int64_t ncols, float* __restrict__ Cm, int64_t ldc, float gamma,
     const float* __restrict__ bmu, const float* __restrict__ bS,
     const float* __restrict__ bias) {
-  __shared__ __attribute__((aligned(16))) float As[2][kFwdT][kFwdK + 4];
-  __shared__ __attribute__((aligned(16))) float Bs[2][kFwdK][kFwdT + 4];
-  const int64_t m0 = (int64_t)blockIdx.y * kFwdT, n0 = (int64_t)blockIdx.x * kFwdT;
+  constexpr int TM = 32 * SB;
+  __shared__ __attribute__((aligned(16))) uint16_t As[3][TM][kFwdK];
+  __shared__ __attribute__((aligned(16))) uint16_t Bs[3][kFwdT][kFwdK];
+  const int64_t m0 = (int64_t)blockIdx.y * TM, n0 = (int64_t)blockIdx.x * kFwdT;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, q = lane >> 4, li = lane & 15;
   const int wr = wave >> 1, wc = wave & 1;
-  // staging: thread tid loads float4 number tid + 256 u of A's chunk
-  // (128 rows x 4 float4) and of B's chunk (16 rows x 32 float4)
-  constexpr int kA4 = kFwdT * kFwdK / 4 / kFwdThreads;  // 2
-  constexpr int kB4 = kFwdK * kFwdT / 4 / kFwdThreads;  // 2
-  const float* ga[kA4];
-  const float* gb[kB4];
-  float nmu[kB4][4], nrs[kB4][4];  // B's column statistics (normalized inputs)
+  const int acol = 4 * (tid & 7);  // this thread's four k of A's chunk (its rows: tid / 8 + 32 u)
+  const int bk = 8 * wave;         // its eight k of B's chunk
+  const int64_t nb = n0 + 2 * lane < ncols ? n0 + 2 * lane : 0;  // its two columns (ldb is even)
+  const float* ga[SB];
 #pragma unroll
-  for (int u = 0; u < kA4; ++u) {
-    const int e = tid + kFwdThreads * u;
-    const int64_t m = m0 + e / (kFwdK / 4);
-    ga[u] = A + (m < M ? m : M - 1) * (int64_t)Kd + 4 * (e % (kFwdK / 4));
+  for (int u = 0; u < SB; ++u) {
+    const int64_t m = m0 + (tid >> 3) + 32 * u;
+    ga[u] = A + (m < M ? m : M - 1) * (int64_t)Kd;
   }
+  const float* gb = B + nb;
+  float nmu[2] = {0.f, 0.f}, nrs[2] = {1.f, 1.f};
+  if (bmu != nullptr) {
 #pragma unroll
-  for (int u = 0; u < kB4; ++u) {
-    const int e = tid + kFwdThreads * u;
-    const int kk = e / (kFwdT / 4);
-    const int64_t nb = n0 + 4 * (e % (kFwdT / 4));
-    gb[u] = B + (int64_t)kk * ldb + (nb < ncols ? nb : 0);
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int64_t nn = nb + t < ncols ? nb + t : 0;
-      nmu[u][t] = bmu != nullptr ? bmu[nn] : 0.f;
-      nrs[u][t] = bmu != nullptr ? 1.0f / sqrtf(bS[nn]) : 1.f;
+    for (int t = 0; t < 2; ++t) {
+      const int64_t n = nb + t < ncols ? nb + t : nb;
+      nmu[t] = bmu[n];
+      nrs[t] = 1.0f / sqrtf(bS[n]);
     }
   }
-  fwdx4 ra[kA4], rb[kB4];
-  auto fetch = [&](int c) {
+  fwdx4 ra[SB];
+  f32x2 rb[8];
+  auto fetch = [&](int k0) {
 #pragma unroll
-    for (int u = 0; u < kA4; ++u) ra[u] = *reinterpret_cast<const fwdx4*>(ga[u] + kFwdK * c);
+    for (int u = 0; u < SB; ++u) {
+      const int k = k0 + acol;
+      if constexpr (ROW4) {
+        ra[u] = gload(reinterpret_cast<const fwdx4*>(ga[u] + (k < Kd ? k : 0)));
+      } else {
 #pragma unroll
-    for (int u = 0; u < kB4; ++u) rb[u] = *reinterpret_cast<const fwdx4*>(gb[u] + (int64_t)kFwdK * c * ldb);
-  };
-  auto store = [&](int buf) {
-#pragma unroll
-    for (int u = 0; u < kA4; ++u) {
-      const int e = tid + kFwdThreads * u;
-      *reinterpret_cast<fwdx4*>(&As[buf][e / (kFwdK / 4)][4 * (e % (kFwdK / 4))]) = ra[u];
-    }
-#pragma unroll
-    for (int u = 0; u < kB4; ++u) {
-      const int e = tid + kFwdThreads * u;
-      const int kk = e / (kFwdT / 4), c4 = e % (kFwdT / 4);
-      const int64_t nb = n0 + 4 * c4;
-      fwdx4 v = rb[u];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        float x = v[t];
-        if (bmu != nullptr) x = (x - nmu[u][t]) * nrs[u][t];
-        if (ACT >= 0) x = act_fn(x, ACT, gamma);
-        v[t] = (nb + t < ncols) ? x : 0.f;
+        for (int t = 0; t < 4; ++t) ra[u][t] = gload(ga[u] + (k + t < Kd ? k + t : 0));
       }
-      *reinterpret_cast<fwdx4*>(&Bs[buf][kk][4 * c4]) = v;
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int k = k0 + bk + e;
+      rb[e] = gload(reinterpret_cast<const f32x2*>(gb + (int64_t)(k < Kd ? k : 0) * ldb));
     }
   };
-  const fwdx4 zero = {0.f, 0.f, 0.f, 0.f};
-  fwdx4 acc[4][4];
+  auto store = [&](int k0) {
+    const bool tail = k0 + kFwdK > Kd;
 #pragma unroll
-  for (int sb = 0; sb < 4; ++sb)
+    for (int u = 0; u < SB; ++u) {
+      if (tail) {
 #pragma unroll
-    for (int cb = 0; cb < 4; ++cb) acc[sb][cb] = zero;
-  auto compute = [&](int buf) {
-    fwdx4 a[4];
+        for (int t = 0; t < 4; ++t) ra[u][t] = k0 + acol + t < Kd ? ra[u][t] : 0.f;
+      }
+      const Split2 s0 = split2(ra[u][0], ra[u][1]), s1 = split2(ra[u][2], ra[u][3]);
 #pragma unroll
-    for (int sb = 0; sb < 4; ++sb)
-      a[sb] = *reinterpret_cast<const fwdx4*>(&As[buf][64 * wr + 16 * sb + li][4 * q]);
+      for (int p = 0; p < 3; ++p)
+        *reinterpret_cast<uint2*>(&As[p][(tid >> 3) + 32 * u][part_at((tid >> 3) + 32 * u, acol)]) = make_uint2(s0.p[p], s1.p[p]);
+    }
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      float bv[4];
+    for (int t = 0; t < 2; ++t) {
+      float x[8];
 #pragma unroll
-      for (int cb = 0; cb < 4; ++cb) bv[cb] = Bs[buf][4 * q + t][64 * wc + 16 * cb + li];
+      for (int e = 0; e < 8; ++e) {
+        x[e] = rb[e][t];
+        if (bmu != nullptr) x[e] = (x[e] - nmu[t]) * nrs[t];
+        if (ACT >= 0) x[e] = act_fn(x[e], ACT, gamma);
+        if (tail) x[e] = k0 + bk + e < Kd ? x[e] : 0.f;
+      }
+      const Split2 s[4] = {split2(x[0], x[1]), split2(x[2], x[3]), split2(x[4], x[5]), split2(x[6], x[7])};
 #pragma unroll
-      for (int sb = 0; sb < 4; ++sb)
-#pragma unroll
-        for (int cb = 0; cb < 4; ++cb)
-          acc[sb][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[sb][t], bv[cb], acc[sb][cb], 0, 0, 0);
+      for (int p = 0; p < 3; ++p)
+        *reinterpret_cast<uint4*>(&Bs[p][lane + 64 * t][part_at(lane, bk)]) = make_uint4(s[0].p[p], s[1].p[p], s[2].p[p], s[3].p[p]);
     }
   };
-  const int nc = Kd / kFwdK;
+  f32x4 acc[SB][4];
+#pragma unroll
+  for (int sb = 0; sb < SB; ++sb)
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb) acc[sb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // block cb of the wave's columns: LDS rows 64 (cb & 1) + 32 wc + 16 (cb / 2) + li
+  auto compute = [&]() {
+    bf16x8 b[4][3];
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+      for (int p = 0; p < 3; ++p)
+        b[cb][p] = *reinterpret_cast<const bf16x8*>(&Bs[p][64 * (cb & 1) + 32 * wc + 16 * (cb >> 1) + li][part_at(li, 8 * q)]);
+#pragma unroll
+    for (int sb = 0; sb < SB; ++sb) {
+      bf16x8 a[3];
+#pragma unroll
+      for (int p = 0; p < 3; ++p)
+        a[p] = *reinterpret_cast<const bf16x8*>(&As[p][16 * (SB * wr + sb) + li][part_at(li, 8 * q)]);
+      add_product<4>(a, b, acc[sb]);
+    }
+  };
   fetch(0);
-  store(0);
-  __syncthreads();
-  for (int c = 0; c < nc; ++c) {
-    if (c + 1 < nc) fetch(c + 1);
-    compute(c & 1);
-    if (c + 1 < nc) store((c + 1) & 1);
+  for (int k0 = 0; k0 < Kd; k0 += kFwdK) {
+    store(k0);
+    __syncthreads();
+    fetch(k0 + kFwdK < Kd ? k0 + kFwdK : 0);
+    compute();
     __syncthreads();
   }
-  // D layout: lane (q, li), element v -> row 16 sb + 4 q + v, column 16 cb + li
+  // D layout: lane (q, li), element v -> row 16 sb + 4 q + v, LDS row .. + li
 #pragma unroll
-  for (int sb = 0; sb < 4; ++sb)
+  for (int sb = 0; sb < SB; ++sb)
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const int64_t m = m0 + 64 * wr + 16 * sb + 4 * q + v;
+      const int64_t m = m0 + 16 * (SB * wr + sb) + 4 * q + v;
       if (m >= M) continue;
       const float b = (bias != nullptr) ? bias[m] : 0.f;
 #pragma unroll
-      for (int cb = 0; cb < 4; ++cb) {
-        const int64_t n = n0 + 64 * wc + 16 * cb + li;
-        if (n < ncols) Cm[m * ldc + n] = (bias != nullptr) ? acc[sb][cb][v] + b : acc[sb][cb][v];
+      for (int c = 0; c < 2; ++c) {
+        const int64_t n = n0 + 64 * wc + 32 * c + 2 * li;
+        f32x2 z = {acc[sb][2 * c][v], acc[sb][2 * c + 1][v]};
+        if (bias != nullptr) z = f32x2{z[0] + b, z[1] + b};
+        float* at = Cm + m * ldc + n;
+        if (n + 1 < ncols) gstore(reinterpret_cast<f32x2*>(at), z);
+        else if (n < ncols) gstore(at, z[0]);
       }
     }
 }
 
 // The product for at most 16 output rows (a logit layer): a block takes 64
-// columns and eight waves, each wave an eighth of the reduction (Kd a
-// multiple of 128) as four 16 x 16 MFMA tiles.  Lane (q, li) holds columns
+// columns and eight waves, each wave an eighth of the reduction (rounded up to
+// blocks of 16; RAGGED: Kd is not a multiple of 128, and what lies beyond it is
+// zero in both operands) as four 16 x 16 MFMA tiles.  Lane (q, li) holds columns
 // n0 + 4 li + j of tile j, so that op(B) arrives as one float4 per row, and
 // k = 4 q + t of each block of 16 (A's row li as one float4); the next
 // block's values are requested before the current one's products.  The
 // eight partial tiles meet in LDS and are added in wave order.
 constexpr int kSkinnyCols = 64;
 constexpr int kSkinnyWaves = 8;
-template <int ACT>
+template <int ACT, bool RAGGED>
 __global__ __launch_bounds__(64 * kSkinnyWaves) void k_gemm_fwd_skinny(
     const float* __restrict__ A, int M, int Kd, const float* __restrict__ B, int64_t ldb,
     int64_t ncols, float* __restrict__ Cm, int64_t ldc, float gamma,
@@ -705,18 +664,23 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void k_gemm_fwd_skinny(
     nmu[j] = bmu != nullptr ? bmu[nn] : 0.f;
     nrs[j] = bmu != nullptr ? 1.0f / sqrtf(bS[nn]) : 1.f;
   }
-  const int kq = Kd / kSkinnyWaves, nkb = kq / 16;
-  const int64_t k0 = (int64_t)wave * kq + 4 * q;
+  const int nkb = (Kd + 16 * kSkinnyWaves - 1) / (16 * kSkinnyWaves);
+  const int k0 = 16 * wave * nkb + 4 * q;
   const bool mrow = li < M;
-  const float* arow = A + (int64_t)(mrow ? li : 0) * Kd + k0;
-  const float* bp = B + k0 * ldb + (nb < ncols ? nb : 0);
+  const float* arow = A + (int64_t)(mrow ? li : 0) * Kd;
+  const float* bp = B + (nb < ncols ? nb : 0);
   const fwdx4 zero = {0.f, 0.f, 0.f, 0.f};
   fwdx4 acc[4] = {zero, zero, zero, zero};
   fwdx4 a_nx, b_nx[4];
   auto fetch = [&](int kb) {
-    a_nx = *reinterpret_cast<const fwdx4*>(arow + 16 * kb);
+    const int k = k0 + 16 * kb;
+    if constexpr (!RAGGED) a_nx = gload(reinterpret_cast<const fwdx4*>(arow + k));
 #pragma unroll
-    for (int t = 0; t < 4; ++t) b_nx[t] = *reinterpret_cast<const fwdx4*>(bp + (int64_t)(16 * kb + t) * ldb);
+    for (int t = 0; t < 4; ++t) {
+      const int kt = !RAGGED || k + t < Kd ? k + t : 0;
+      if constexpr (RAGGED) a_nx[t] = gload(arow + kt);
+      b_nx[t] = gload(reinterpret_cast<const fwdx4*>(bp + (int64_t)kt * ldb));
+    }
   };
   fetch(0);
   for (int kb = 0; kb < nkb; ++kb) {
@@ -726,15 +690,18 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void k_gemm_fwd_skinny(
     for (int t = 0; t < 4; ++t) bv[t] = b_nx[t];
     if (kb + 1 < nkb) fetch(kb + 1);
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+    for (int t = 0; t < 4; ++t) {
+      const bool in = !RAGGED || k0 + 16 * kb + t < Kd;
+      const float at = in ? a4[t] : 0.f;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         float x = bv[t][j];
         if (bmu != nullptr) x = (x - nmu[j]) * nrs[j];
         if (ACT >= 0) x = act_fn(x, ACT, gamma);
-        x = (nb + j < ncols) ? x : 0.f;
-        acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[t], x, acc[j], 0, 0, 0);
+        x = (in && nb + j < ncols) ? x : 0.f;
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(at, x, acc[j], 0, 0, 0);
       }
+    }
   }
   // D layout: lane (q, li), element v of tile j -> row 4 q + v, column 4 li + j
 #pragma unroll
@@ -754,24 +721,29 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void k_gemm_fwd_skinny(
   }
 }
 
-// One layer of the forward pass: the skinny matrix-core product for a logit
-// layer (at most 16 rows, reduction a multiple of 128), the tiled one when the
-// reduction width is a multiple of 16, the vector one otherwise.
+// One layer of the forward pass: the skinny product for at most 16 rows, the
+// tiled one otherwise, with 64-row tiles while 128-row ones would not give
+// every CU its two blocks.
 template <int ACT>
 hipError_t forward_layer(const float* A, int M, int Kd, const float* B, int64_t ldb, int64_t N,
                          float* Cm, int64_t ldc, float gamma, const float* mu, const float* S,
                          const float* bias, hipStream_t s) {
-  if (M <= 16 && Kd % (16 * kSkinnyWaves) == 0 && ldb % 4 == 0) {
-    hipLaunchKernelGGL(k_gemm_fwd_skinny<ACT>, dim3((unsigned)((N + kSkinnyCols - 1) / kSkinnyCols)),
-                       dim3(64 * kSkinnyWaves), 0, s, A, M, Kd, B, ldb, N, Cm, ldc, gamma, mu, S, bias);
-  } else if (Kd % kFwdK == 0) {
-    dim3 grid((unsigned)((N + kFwdT - 1) / kFwdT), (unsigned)((M + kFwdT - 1) / kFwdT));
-    hipLaunchKernelGGL(k_gemm_fwd_mfma<ACT>, grid, dim3(kFwdThreads), 0, s, A, M, Kd, B, ldb, N,
-                       Cm, ldc, gamma, mu, S, bias);
+  const int64_t nx = (N + kFwdT - 1) / kFwdT;
+  auto go = [&](auto kernel, dim3 grid, int threads) {
+    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, A, M, Kd, B, ldb, N, Cm, ldc, gamma, mu, S, bias);
+  };
+  if (M <= 16) {
+    const dim3 grid((unsigned)((N + kSkinnyCols - 1) / kSkinnyCols));
+    if (Kd % (16 * kSkinnyWaves) == 0) go(k_gemm_fwd_skinny<ACT, false>, grid, 64 * kSkinnyWaves);
+    else go(k_gemm_fwd_skinny<ACT, true>, grid, 64 * kSkinnyWaves);
+  } else if (nx * ((M + 127) / 128) >= 512) {
+    const dim3 grid((unsigned)nx, (unsigned)((M + 127) / 128));
+    if (Kd % 4 == 0) go(k_gemm_fwd_split<ACT, 4, true>, grid, kFwdThreads);
+    else go(k_gemm_fwd_split<ACT, 4, false>, grid, kFwdThreads);
   } else {
-    dim3 grid((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64));
-    hipLaunchKernelGGL(k_gemm_fwd<ACT>, grid, dim3(256), 0, s, A, M, Kd, B, ldb, N, Cm, ldc,
-                       gamma, mu, S, bias);
+    const dim3 grid((unsigned)nx, (unsigned)((M + 63) / 64));
+    if (Kd % 4 == 0) go(k_gemm_fwd_split<ACT, 2, true>, grid, kFwdThreads);
+    else go(k_gemm_fwd_split<ACT, 2, false>, grid, kFwdThreads);
   }
   return hipGetLastError();
 }

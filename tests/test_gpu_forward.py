@@ -1,0 +1,50 @@
+"""The full forward pass at the edges of its kernels' tiles (rows of 64 and
+128, 128 columns, chunks of 32 k, logit layers in blocks of 128 k, reduction
+widths that are no multiple of four), against 64-bit numpy.
+
+Tolerance: the first-order bound of fp32 sums.  With u = 2^-24, a layer's field
+is off by at most (n + 16) u sum |w| |a| for its n terms and the operands'
+rounding, plus the error of its inputs through |w|; tanh and relu do not
+enlarge an error and add 8 u.  A sample's loss moves by at most twice the
+largest logit error, plus 32 u of its own size.
+"""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [((17, 17, 2), 1), ((33, 129, 10), 129), ((100, 64, 16), 63), ((31, 65, 130, 3), 200),
+          ((16, 100, 10), 127), ((257, 300, 33, 7), 1001), ((784, 512, 10), 2050), ((32, 8, 9), 128),
+          ((21, 4100, 11), 2051), ((64, 4096, 10), 2048)]
+
+
+@pytest.mark.parametrize("act", ["tanh", "relu"])
+@pytest.mark.parametrize("widths,N", SHAPES, ids=["-".join(map(str, w)) + f"x{n}" for w, n in SHAPES])
+def test_forward_edges(widths, N, act):
+    from paper_2607_08406_amd import mca
+
+    rng = np.random.default_rng(sum(widths) + N)
+    X = (rng.random((N, widths[0])) * (rng.random((N, widths[0])) < 0.5)).astype(np.float32)
+    y = rng.integers(0, widths[-1], N).astype(np.int32)
+    W = [((rng.random((m, n)) * 2 - 1) * np.sqrt(3.0 / n)).astype(np.float32)
+         for n, m in zip(widths[:-1], widths[1:])]
+    ctx = mca.Context(mca.mlp_desc(list(widths), act, delta=0.1, seed=1, stream_tag=1), W, X, y, k_max=1)
+    u = 2.0 ** -24
+    a, err = X.astype(np.float64), 0.0
+    for l, w in enumerate(W):
+        w = w.astype(np.float64)
+        z = a @ w.T
+        size = np.abs(a) @ np.abs(w).T
+        err = (w.shape[1] + 16) * u * size + (0.0 if l == 0 else err @ np.abs(w).T)
+        a = np.tanh(z) if act == "tanh" else np.maximum(z, 0.0)
+        if l < len(W) - 1:
+            err = err + 8 * u
+    top = z.max(1)
+    loss = np.log(np.exp(z - top[:, None]).sum(1)) + top - z[np.arange(N), y]
+    tol = 2 * err.max(1) + 32 * u * (1 + np.abs(loss) + np.abs(z).max(1))
+    for again in range(2):
+        got = ctx.sample_losses()
+        ratio = np.abs(got - loss) / tol
+        assert got.shape == (N,) and ratio.max() <= 1, (again, ratio.max(), int(ratio.argmax()))
+        ctx.refresh()
+    ctx.close()
