@@ -332,23 +332,47 @@ int norm_tiles(int64_t n_samples, int w) {
   return (int)((n_samples + T - 1) / T);
 }
 
-// Statistics of hidden layer l, one thread per sample, units in order.
-__global__ void k_norm_stats(NetDev net, NormDev nd, int l) {
-  const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= net.N) return;
-  const int W = net.widths[l + 1];
+// Statistics of hidden layer l.  A block takes 16 samples (64 bytes of each
+// unit's row) and shares their W units among 64 groups of lanes: a thread reads
+// its W / 64 values once, and both sums meet in LDS in group order, by each
+// sample's first thread.  A thread a sample ran 2 W dependent loads on N / 64
+// waves (1024 units, 3000 samples: 339 us).
+constexpr int kStatSamples = 16, kStatGroups = 64;
+template <int PER>
+__global__ __launch_bounds__(kStatSamples * kStatGroups) void k_norm_stats(NetDev net, NormDev nd, int l) {
+  __shared__ float part[kStatGroups][kStatSamples];
+  __shared__ float mean[kStatSamples];
+  const int t = threadIdx.x % kStatSamples, g = threadIdx.x / kStatSamples;
+  const int64_t n = (int64_t)blockIdx.x * kStatSamples + t;
+  const int64_t nc = n < net.N ? n : net.N - 1;
   const float* Z = net.Z[l];
-  const float inv = 1.0f / (float)W;  // W is a power of two
-  float s = 0.f;
-  for (int u = 0; u < W; ++u) s += gload(&Z[(int64_t)u * net.Ns + n]);
-  const float mu = s * inv;
+  const float inv = 1.0f / (float)(PER * kStatGroups);  // a power of two
+  float z[PER], s = 0.f;
+#pragma unroll
+  for (int u = 0; u < PER; ++u) z[u] = gload(&Z[(int64_t)(g * PER + u) * net.Ns + nc]);
+#pragma unroll
+  for (int u = 0; u < PER; ++u) s += z[u];
+  auto total = [&](float v) {  // in the first 16 threads, thread t sample t
+    part[g][t] = v;
+    __syncthreads();
+    float a = 0.f;
+    if (g == 0)
+      for (int i = 0; i < kStatGroups; ++i) a += part[i][t];
+    __syncthreads();
+    return a;
+  };
+  const float a = total(s) * inv;
+  if (g == 0) mean[t] = a;
+  __syncthreads();
+  const float mu = mean[t];
   float v = 0.f;
-  for (int u = 0; u < W; ++u) {
-    const float c = gload(&Z[(int64_t)u * net.Ns + n]) - mu;
-    v += c * c;
+#pragma unroll
+  for (int u = 0; u < PER; ++u) v += (z[u] - mu) * (z[u] - mu);
+  const float q = total(v);
+  if (g == 0 && n < net.N) {
+    gstore(&nd.MU[l][n], mu);
+    gstore(&nd.S[l][n], q * inv + net.ln_eps);
   }
-  gstore(&nd.MU[l][n], mu);
-  gstore(&nd.S[l][n], v * inv + net.ln_eps);
 }
 
 // One layer's augmented matrix [rows][n + 1] (each row's weights, then its
@@ -373,7 +397,13 @@ hipError_t launch_augment(float* aug, float* W, float* B, int rows, int n, bool 
 }
 
 hipError_t launch_norm_stats(const NetDev& net, const NormDev& nd, int l, hipStream_t s) {
-  hipLaunchKernelGGL(k_norm_stats, dim3((unsigned)((net.N + 255) / 256)), dim3(256), 0, s, net, nd, l);
+  const dim3 grid((unsigned)((net.N + kStatSamples - 1) / kStatSamples)), block(kStatSamples * kStatGroups);
+  switch (net.widths[l + 1]) {
+    case 256: hipLaunchKernelGGL(k_norm_stats<4>, grid, block, 0, s, net, nd, l); break;
+    case 512: hipLaunchKernelGGL(k_norm_stats<8>, grid, block, 0, s, net, nd, l); break;
+    case 1024: hipLaunchKernelGGL(k_norm_stats<16>, grid, block, 0, s, net, nd, l); break;
+    default: return hipErrorInvalidValue;  // the context's validation admits no other width
+  }
   return hipGetLastError();
 }
 
