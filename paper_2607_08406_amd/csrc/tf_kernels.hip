@@ -28,6 +28,7 @@
 // that reads it; attention, GELU and the loss run in fp32 on the vector units.
 #include <algorithm>
 
+#include "split_mma.hpp"
 #include "tf_kernels.hpp"
 
 namespace mca {
@@ -39,7 +40,7 @@ typedef float floatx2 __attribute__((ext_vector_type(2)));
 
 constexpr int kGemmThreads = 256;  // 4 waves per output tile of 128 rows x 16 CB WC columns
 constexpr int kGemmRows = 128;     // rows (positions) per block
-constexpr int kChunkK = 16;        // reduction chunk staged in LDS
+constexpr int kChunkK = 32;        // reduction chunk staged in LDS
 constexpr int kStatSteps = 4;      // groups of four rows whose LayerNorm statistics a wave takes at once
 constexpr int kRowThreads = 256;   // row kernels: a wave per row
 constexpr int kDlSteps = 4;        // groups of four rows a wave of the loss-change kernel loads at once
@@ -463,12 +464,13 @@ __global__ __launch_bounds__(kRowThreads) void k_tf_stats(const TfDev* tf, const
 // that read one) with an epilogue, for the slots active in `stage`.
 // A 128 x 16 CB WC output tile per block: the 4 waves form a (4 / WC) x WC
 // grid and wave (wr, wc) takes its 16 SB x 16 CB part (SB = 2 WC) as SB by
-// CB 16 x 16 MFMA tiles, so each operand fragment read from LDS feeds
-// several MFMAs.  The reduction dimension runs in
-// chunks of 16 staged in LDS (two buffers; the loads run two chunks ahead of
-// the products).  Inside a chunk, k
-// runs in blocks of 16; lane group q holds k = 16 kb + 4 q + t (t = 0..3),
-// used by four MFMAs in turn, so each lane reads its operands as float4.
+// CB 16 x 16 tiles, each product of fp32 values as six of their bf16 parts
+// (split_mma.hpp).  The reduction runs in chunks of 32 k, split on their way
+// into LDS; the next chunk's loads are in flight during the products, and the
+// CU's other block multiplies while this one splits.  A wider tile splits its
+// rows for more columns: 128 x 128 spends 830 vector cycles a chunk beside
+// 1536 of the matrix cores, 128 x 64 660 beside 768.  Output columns 2 p and
+// 2 p + 1 are in one lane (EPI != 3), which stores them together.
 // Rows and columns beyond the matrix are clamped on load and dropped on
 // store.  Requires Kd % 32 == 0.  The Q, K and V projections are one
 // product with 3 D output columns: column n takes its weight row and bias
@@ -482,7 +484,7 @@ __global__ __launch_bounds__(kRowThreads) void k_tf_stats(const TfDev* tf, const
 // output, MLP down), 3 logits and each position's cross-entropy (output layer; one column
 // tile, with the logit tile in LDS).
 template <int EPI, int CB, int WC>
-__global__ __launch_bounds__(kGemmThreads, (EPI == 2 && CB == 4) || (EPI == 3 && CB == 8) ? 2 : 3) void k_tf_gemm(
+__global__ __launch_bounds__(kGemmThreads, EPI == 3 ? 2 : 3) void k_tf_gemm(
     const TfDev* tf, int stage, int role, int ncand) {
   const int k = slot_of(tf, blockIdx.z, ncand);
   const bool attn_half = role == kGemmQKV || role == kGemmO;
@@ -536,13 +538,13 @@ __global__ __launch_bounds__(kGemmThreads, (EPI == 2 && CB == 4) || (EPI == 3 &&
     const int w = n / D;
     return tab[tb + kBq + 2 * w][n - w * D];
   };
-  constexpr int kStage = 2 * kGemmRows * (kChunkK + 4);  // floats of the A operand's double buffer
-  constexpr int kStageB = 2 * kTileN * (kChunkK + 4);
-  constexpr int kZ = kGemmRows * (kTileN + 1);           // the output layer's logit tile
+  constexpr int kStage = 3 * kGemmRows * kChunkK * 2;  // bytes of the A operand's parts
+  constexpr int kStageB = 3 * kTileN * kChunkK * 2;
+  constexpr int kZ = kGemmRows * (kTileN + 1) * 4;      // the output layer's logit tile
   constexpr int kSmem = (EPI == 3 && kZ > kStage + kStageB) ? kZ : kStage + kStageB;
-  __shared__ __attribute__((aligned(16))) float smem[kSmem];
-  auto As = reinterpret_cast<float (*)[kGemmRows][kChunkK + 4]>(smem);
-  auto Bs = reinterpret_cast<float (*)[kTileN][kChunkK + 4]>(smem + kStage);
+  __shared__ __attribute__((aligned(16))) unsigned char smem[kSmem];
+  auto As = reinterpret_cast<uint16_t (*)[kGemmRows][kChunkK]>(smem);
+  auto Bs = reinterpret_cast<uint16_t (*)[kTileN][kChunkK]>(smem + kStage);
   const int tid = threadIdx.x;
   const int wave = tid >> 6, lane = tid & 63, q = lane >> 4, li = lane & 15;
   const int wr = wave / WC, wc = wave % WC;
@@ -557,21 +559,18 @@ __global__ __launch_bounds__(kGemmThreads, (EPI == 2 && CB == 4) || (EPI == 3 &&
     }
   }
   // staging: thread tid loads float4 number tid + 256 u of the A chunk
-  // (128 rows x 4 float4) and of the B chunk (128 rows x 4 float4); its A
-  // elements sit in one float4 column group of every chunk
-  constexpr int kA4 = kGemmRows * kChunkK / 4 / kGemmThreads;  // 2
-  // (the B chunk has kTileN x 4 float4: threads beyond it load a clamped row
-  // and store nothing)
-  constexpr int kB4 = (kTileN * kChunkK / 4 + kGemmThreads - 1) / kGemmThreads;
-  const int acol = 4 * (tid % (kChunkK / 4));
+  // (128 rows x 8 float4) and of the B chunk (kTileN rows x 8 float4: threads
+  // beyond it load a clamped row and store nothing); its elements sit in one
+  // float4 column group of every chunk
+  constexpr int kA4 = kGemmRows / 32;
+  constexpr int kB4 = (kTileN + 31) / 32;
+  const int acol = 4 * (tid & 7), arow = tid >> 3;
   const float* ga[kA4];
   const float* gb[kB4];
   float amu[kA4], ars[kA4];
 #pragma unroll
   for (int u = 0; u < kA4; ++u) {
-    const int e = tid + kGemmThreads * u;
-    const int r = e / (kChunkK / 4);
-    const int64_t m = m0 + r;
+    const int64_t m = m0 + arow + 32 * u;
     ga[u] = X + (m < N ? m : N - 1) * ldX + acol;
     const float2 st2 = ln ? stats[m < N ? m : N - 1] : make_float2(0.f, 1.f);
     amu[u] = st2.x;
@@ -579,123 +578,107 @@ __global__ __launch_bounds__(kGemmThreads, (EPI == 2 && CB == 4) || (EPI == 3 &&
   }
 #pragma unroll
   for (int u = 0; u < kB4; ++u) {
-    const int e = tid + kGemmThreads * u;
-    const int n = n0 + e / (kChunkK / 4);
-    gb[u] = wrow(n < Nout ? n : Nout - 1) + 4 * (e % (kChunkK / 4));
+    const int n = n0 + arow + 32 * u;
+    gb[u] = wrow(n < Nout ? n : Nout - 1) + acol;
   }
-  const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
   // a chunk's operands on their way from memory into LDS
-  struct Staged {
-    floatx4 a[kA4];
-    floatx4 b[kB4];
-  };
-  auto fetch = [&](int c, Staged& S) {
+  floatx4 ra[kA4], rb[kB4];
+  auto fetch = [&](int k0) {
 #pragma unroll
-    for (int u = 0; u < kA4; ++u) S.a[u] = gload(reinterpret_cast<const floatx4*>(ga[u] + kChunkK * c));
+    for (int u = 0; u < kA4; ++u) ra[u] = gload(reinterpret_cast<const floatx4*>(ga[u] + k0));
 #pragma unroll
-    for (int u = 0; u < kB4; ++u) S.b[u] = gload(reinterpret_cast<const floatx4*>(gb[u] + kChunkK * c));
+    for (int u = 0; u < kB4; ++u) rb[u] = gload(reinterpret_cast<const floatx4*>(gb[u] + k0));
   };
-  auto store = [&](int c, const Staged& S) {
-    const int buf = c & 1;
+  auto put = [&](uint16_t* tile, int r, int part_stride, const floatx4& x) {
+    uint16_t* row = tile + r * kChunkK + part_at(r, acol);
+    const Split2 s0 = split2(x[0], x[1]), s1 = split2(x[2], x[3]);
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+      *reinterpret_cast<uint2*>(row + p * part_stride) = make_uint2(s0.p[p], s1.p[p]);
+  };
+  auto store = [&](int k0) {
+    floatx4 g4 = {1.f, 1.f, 1.f, 1.f}, b4 = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (ln) {
+      g4 = *reinterpret_cast<const floatx4*>(&s_g[k0 + acol]);
+      b4 = *reinterpret_cast<const floatx4*>(&s_b[k0 + acol]);
+    }
 #pragma unroll
     for (int u = 0; u < kA4; ++u) {
-      const int e = tid + kGemmThreads * u;
-      floatx4 a = S.a[u];
+      floatx4 a = ra[u];
       if constexpr (ln) {
-        const floatx4 g4 = *reinterpret_cast<const floatx4*>(&s_g[kChunkK * c + acol]);
-        const floatx4 b4 = *reinterpret_cast<const floatx4*>(&s_b[kChunkK * c + acol]);
 #pragma unroll
         for (int t = 0; t < 4; ++t) a[t] = fmaf((a[t] - amu[u]) * ars[u], g4[t], b4[t]);
       }
-      *reinterpret_cast<floatx4*>(&As[buf][e / (kChunkK / 4)][acol]) = a;
+      put(As[0][0], arow + 32 * u, kGemmRows * kChunkK, a);
     }
+    // column 2 p + b of each 32 goes to LDS row p + 16 b (in order for EPI 3)
+    const int brow = EPI == 3 ? arow : ((arow & 1) << 4) | (arow >> 1);
 #pragma unroll
-    for (int u = 0; u < kB4; ++u) {
-      const int e = tid + kGemmThreads * u;
-      if ((kTileN * kChunkK / 4) % kGemmThreads == 0 || e < kTileN * kChunkK / 4)
-        *reinterpret_cast<floatx4*>(&Bs[buf][e / (kChunkK / 4)][4 * (e % (kChunkK / 4))]) = S.b[u];
-    }
+    for (int u = 0; u < kB4; ++u)
+      if (kTileN % 32 == 0 || arow + 32 * u < kTileN) put(Bs[0][0], brow + 32 * u, kTileN * kChunkK, rb[u]);
   };
-  floatx4 acc[SB][CB];
+  f32x4 acc[SB][CB];
 #pragma unroll
   for (int sb = 0; sb < SB; ++sb)
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb) acc[sb][cb] = zero;
-  auto compute = [&](int buf) {
+    for (int cb = 0; cb < CB; ++cb) acc[sb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto compute = [&]() {
+    bf16x8 bv[CB][3];
 #pragma unroll
-    for (int kb = 0; kb < kChunkK / 16; ++kb) {
-      floatx4 a[SB], bv[CB];
+    for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-      for (int sb = 0; sb < SB; ++sb)
-        a[sb] = *reinterpret_cast<const floatx4*>(&As[buf][16 * SB * wr + 16 * sb + li][16 * kb + 4 * q]);
+      for (int p = 0; p < 3; ++p)
+        bv[cb][p] = *reinterpret_cast<const bf16x8*>(&Bs[p][16 * (CB * wc + cb) + li][part_at(li, 8 * q)]);
 #pragma unroll
-      for (int cb = 0; cb < CB; ++cb)
-        bv[cb] = *reinterpret_cast<const floatx4*>(&Bs[buf][16 * CB * wc + 16 * cb + li][16 * kb + 4 * q]);
+    for (int sb = 0; sb < SB; ++sb) {
+      bf16x8 a[1][3];
 #pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int sb = 0; sb < SB; ++sb)
-#pragma unroll
-          for (int cb = 0; cb < CB; ++cb)
-            acc[sb][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[sb][t], bv[cb][t], acc[sb][cb], 0, 0, 0);
+      for (int p = 0; p < 3; ++p)
+        a[0][p] = *reinterpret_cast<const bf16x8*>(&As[p][16 * (SB * wr + sb) + li][part_at(li, 8 * q)]);
+      multiply_parts<1, CB>(a, bv, reinterpret_cast<f32x4(&)[1][CB]>(acc[sb]));
     }
   };
-  // D layout: lane (q, li), element v -> row 16 sb + 4 q + v, column 16 cb + li.
-  // The residual a lane adds is loaded before the last chunk's products, so
-  // its latency hides behind them.
-  float res[SB][CB][4];
+  if constexpr (EPI != 3) static_assert(CB % 2 == 0 && kTileN % 32 == 0, "columns in pairs");
+  // D layout: lane (q, li), element v -> row 16 sb + 4 q + v, LDS row 16 cb + li
+  // of the wave's part: columns 32 c + 2 li + b for cb = 2 c + b (EPI 3: 16 cb
+  // + li).  The residual a lane adds is requested whole once the products'
+  // operands have left their registers.
+  constexpr int kC2 = EPI == 2 ? CB / 2 : 1;
+  f32x2 res[EPI == 2 ? SB : 1][kC2][4];
   (void)res;
   auto load_residual = [&]() {
 #pragma unroll
     for (int sb = 0; sb < SB; ++sb)
 #pragma unroll
-      for (int cb = 0; cb < CB; ++cb)
+      for (int c = 0; c < CB / 2; ++c)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          const int64_t m = m0 + 16 * SB * wr + 16 * sb + 4 * q + v;
-          const int n = n0 + 16 * CB * wc + 16 * cb + li;
-          res[sb][cb][v] = (m < N && n < Nout) ? R[m * D + n] : 0.f;
+          const int64_t m = m0 + 16 * (SB * wr + sb) + 4 * q + v;
+          const int n = n0 + 16 * CB * wc + 32 * c + 2 * li;  // D is even: n < Nout takes both
+          res[sb][c][v] = gload(reinterpret_cast<const f32x2*>(R + (m < N ? m : N - 1) * D + (n < Nout ? n : 0)));
         }
   };
-  // Chunk c + 2's loads are issued while chunk c is multiplied and chunk
-  // c + 1 (loaded one chunk earlier) goes into the other LDS buffer: two
-  // register sets, the loop unrolled by two so that each is fixed.  The
-  // number of chunks is even (Kd % 32 == 0), so every load in the loop is
-  // unconditional and each store waits only for its own chunk's loads.
-  const int nc = Kd / kChunkK;
-  Staged S0, S1;
-  fetch(0, S0);
-  fetch(1, S1);
+  fetch(0);
   if constexpr (ln) __syncthreads();  // the LayerNorm gain and bias are in LDS
-  store(0, S0);
-  __syncthreads();
-  for (int c = 0; c + 2 < nc; c += 2) {
-    fetch(c + 2, S0);
-    compute(0);
-    store(c + 1, S1);
+  for (int k0 = 0; k0 < Kd; k0 += kChunkK) {
+    store(k0);
     __syncthreads();
-    fetch(c + 3, S1);
-    compute(1);
-    store(c + 2, S0);
+    fetch(k0 + kChunkK < Kd ? k0 + kChunkK : 0);
+    compute();
     __syncthreads();
   }
-  compute(0);
-  store(nc - 1, S1);
-  __syncthreads();
   if constexpr (EPI == 2) load_residual();
-  compute(1);
-  __syncthreads();
   float bvv[CB];
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb) {
-    const int n = n0 + 16 * CB * wc + 16 * cb + li;
+    const int n = n0 + 16 * CB * wc + (EPI == 3 ? 16 * cb + li : 32 * (cb / 2) + 2 * li + (cb & 1));
     bvv[cb] = (n < Nout) ? bias_of(n) : 0.f;
   }
   if constexpr (EPI == 3) {
     // the logits into LDS (the operand buffers are free) and to the slot,
     // then a thread per position
     const int ldz = V + 1;
-    float* Z = smem;
+    float* Z = reinterpret_cast<float*>(smem);
 #pragma unroll
     for (int sb = 0; sb < SB; ++sb)
 #pragma unroll
@@ -715,21 +698,21 @@ __global__ __launch_bounds__(kGemmThreads, (EPI == 2 && CB == 4) || (EPI == 3 &&
       slot_ell(tf, k)[m0 + tid] = cross_entropy(Z + tid * ldz, V, tf->tgt[m0 + tid]);
     return;
   }
+  if constexpr (EPI != 3) {
 #pragma unroll
-  for (int sb = 0; sb < SB; ++sb)
+    for (int sb = 0; sb < SB; ++sb)
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb)
+      for (int c = 0; c < CB / 2; ++c)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int64_t m = m0 + 16 * SB * wr + 16 * sb + 4 * q + v;
-        const int n = n0 + 16 * CB * wc + 16 * cb + li;
-        if (m < N && n < Nout) {
-          float y = acc[sb][cb][v] + bvv[cb];
-          if constexpr (EPI == 1) y = gelu(y);
-          if constexpr (EPI == 2) y = res[sb][cb][v] + y;
-          Y[m * ldY + n] = y;
+        for (int v = 0; v < 4; ++v) {
+          const int64_t m = m0 + 16 * (SB * wr + sb) + 4 * q + v;
+          const int n = n0 + 16 * CB * wc + 32 * c + 2 * li;
+          f32x2 y = {acc[sb][2 * c][v] + bvv[2 * c], acc[sb][2 * c + 1][v] + bvv[2 * c + 1]};
+          if constexpr (EPI == 1) y = f32x2{gelu(y[0]), gelu(y[1])};
+          if constexpr (EPI == 2) y = f32x2{res[sb][c][v][0] + y[0], res[sb][c][v][1] + y[1]};
+          if (m < N && n < Nout) gstore(reinterpret_cast<f32x2*>(Y + m * ldY + n), y);
         }
-      }
+  }
 }
 
 // Causal softmax attention, scale 1/sqrt(32), on the matrix cores: a block
@@ -1082,19 +1065,22 @@ hipError_t tf_launch_eval(const TfDev* tf, const TfDev& h, const mca_cand* cands
     else
       hipLaunchKernelGGL(k_tf_stats<4>, srow, dim3(kRowThreads), 0, s, tf, cands, aux, stage, which, ncand);
   };
+  // 128-column tiles, or 64-column ones where those leave fewer columns unused
+  auto gemm = [&](auto wide_tile, auto narrow_tile, int stage, int nout, int role) {
+    if (tiles(nout, 128) * 2 == tiles(nout, 64))
+      hipLaunchKernelGGL(wide_tile, dim3(mt, tiles(nout, 128), rows), dim3(kGemmThreads), 0, s, tf, stage, role, ncand);
+    else
+      hipLaunchKernelGGL(narrow_tile, dim3(mt, tiles(nout, 64), rows), dim3(kGemmThreads), 0, s, tf, stage, role, ncand);
+  };
   for (int b = 0; b < h.NB; ++b) {
     const int stage = b + 1;
     stats(stage, 0);
-    hipLaunchKernelGGL((k_tf_gemm<0, 2, 2>), dim3(mt, tiles(3 * h.D, 64), rows), dim3(kGemmThreads), 0, s, tf,
-                       stage, (int)kGemmQKV, ncand);
+    gemm(k_tf_gemm<0, 4, 2>, k_tf_gemm<0, 2, 2>, stage, 3 * h.D, kGemmQKV);
     hipLaunchKernelGGL(k_tf_attn, dim3((unsigned)(h.S * h.H), rows), dim3(256), 0, s, tf, stage, ncand);
-    hipLaunchKernelGGL((k_tf_gemm<2, 2, 2>), dim3(mt, tiles(h.D, 64), rows), dim3(kGemmThreads), 0, s, tf, stage,
-                       (int)kGemmO, ncand);
+    gemm(k_tf_gemm<2, 4, 2>, k_tf_gemm<2, 2, 2>, stage, h.D, kGemmO);
     stats(stage, 1);
-    hipLaunchKernelGGL((k_tf_gemm<1, 2, 2>), dim3(mt, tiles(h.M, 64), rows), dim3(kGemmThreads), 0, s, tf, stage,
-                       (int)kGemmFc, ncand);
-    hipLaunchKernelGGL((k_tf_gemm<2, 2, 2>), dim3(mt, tiles(h.D, 64), rows), dim3(kGemmThreads), 0, s, tf, stage,
-                       (int)kGemmProj, ncand);
+    gemm(k_tf_gemm<1, 4, 2>, k_tf_gemm<1, 2, 2>, stage, h.M, kGemmFc);
+    gemm(k_tf_gemm<2, 4, 2>, k_tf_gemm<2, 2, 2>, stage, h.D, kGemmProj);
   }
   stats(h.NB + 1, 2);
   // the output layer: one column tile over the vocabulary (80 or 128 wide)
