@@ -13,10 +13,10 @@
 // samples.  It stages their second-hidden-layer local fields ([n_2][T],
 // unit-major as in HBM, rows padded to T+1 floats), the logit-layer weights
 // transposed ([n_2][C]) and the tile's logits, softmax and labels in LDS, lists
-// every affected (candidate, sample) pair, and scores each pair with 32 lanes:
-// lane g adds the list entries g, g+32, ... in order (the next entries are
-// requested while the current ones are used), then the 32 lane sums meet in a
-// fixed butterfly.  The commit runs the same expressions in the same order for
+// every affected (candidate, sample) pair, and scores them with a wave for each
+// two of a candidate: lane g adds the list entries g, g+64, ... in order (the
+// next entries are requested while the current ones are used), then the lane
+// sums meet in a fixed butterfly.  The commit runs the same expressions in the same order for
 // the chosen candidate, so the caches hold exactly the values that were
 // scored.
 #include "device_common.hpp"
@@ -29,11 +29,11 @@ namespace {
 
 constexpr int kSlabThreads = 1024;
 constexpr int kGroupK = 64;  // candidate slots listed at a time
-constexpr int kLanesPerPair = 32;    // a half-wave scores one candidate's pairs
-constexpr int kHalves = kSlabThreads / kLanesPerPair;
-constexpr int kPairChunk = 2;        // pairs of one candidate scored together
+constexpr int kWaves = kSlabThreads / 64;
+constexpr int kPairChunk = 2;        // pairs of one candidate that a wave scores together
 constexpr int kChunk = 2;    // list entries a lane loads at once (two batches in flight)
 constexpr int kStageU = 8;   // tile elements a thread loads at once
+constexpr int kStage4 = 4;   // the same in four samples each
 
 template <int CM>
 struct SlabTile;
@@ -47,33 +47,33 @@ template <int kCtrl>
 __device__ __forceinline__ float dpp_mov(float x) {
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), kCtrl, 0xF, 0xF, true));
 }
-// Sum over the 32 lanes of a half-wave in one fixed order, valid in its lane
-// 0: DPP within rows of 16 (lane ^ 1, ^ 2, then the mirrored partners), then
-// the other row.
-__device__ __forceinline__ float half_sum(float v) {
+// Sum over the wave in one fixed order, the same bits in every lane: DPP
+// within rows of 16 (lane ^ 1, ^ 2, then the mirrored partners), then the
+// other rows.
+__device__ __forceinline__ float wave_sum(float v) {
   v += dpp_mov<0xB1>(v);   // quad_perm [1,0,3,2]
   v += dpp_mov<0x4E>(v);   // quad_perm [2,3,0,1]
   v += dpp_mov<0x141>(v);  // row_half_mirror
   v += dpp_mov<0x140>(v);  // row_mirror
-  return v + __shfl_xor(v, 16, 64);
+  v += __shfl_xor(v, 16, 64);
+  return v + __shfl_xor(v, 32, 64);
 }
 
 // Logit changes of up to kPairChunk pairs of one candidate (samples tp[p],
-// activation changes dp[p] of its first-hidden-layer unit, p < np); the 32
-// lanes of a half-wave share them: lane g takes the list entries g, g+32, ...
-// in order, reads each entry's logit-layer weights once for all the pairs,
-// and the lane sums meet in half_sum().  zt: the block's tile (row stride
-// TS); w2: [n2][CM]; col: the candidate's nnz column entries (m in the low
-// word, the bits of W_1[m, j] in the high word).  With STORE each lane writes
-// its units' new local fields into the tile.  All 64 lanes of the wave must
-// call this.
+// activation changes dp[p] of its first-hidden-layer unit, p < np, all uniform
+// over the wave): lane g takes the list entries g, g+64, ... in order, reads
+// each entry's logit-layer weights once for all the pairs, and the lane sums
+// meet in wave_sum().  zt: the block's tile (row stride TS); w2: [n2][CM]; col:
+// the candidate's nnz column entries (m in the low word, the bits of W_1[m, j]
+// in the high word).  With STORE each lane writes its units' new local fields
+// into the tile.
 template <int CM, int ACT, int TS, bool STORE>
 __device__ __forceinline__ void chunk_logit_delta(float* zt, const float* w2, const uint64_t* col,
                                                   int nnz, const int (&tp)[kPairChunk],
                                                   const float (&dp)[kPairChunk], int np,
-                                                  float gamma, bool active,
+                                                  float gamma,
                                                   float (&acc)[kPairChunk][CM]) {
-  const int g = threadIdx.x & (kLanesPerPair - 1);
+  const int g = threadIdx.x & 63;
 #pragma unroll
   for (int p = 0; p < kPairChunk; ++p)
 #pragma unroll
@@ -85,14 +85,14 @@ __device__ __forceinline__ void chunk_logit_delta(float* zt, const float* w2, co
   auto fetch = [&](int e0, uint64_t (&ent)[kChunk]) {
 #pragma unroll
     for (int u = 0; u < kChunk; ++u) {
-      const int e = e0 + kLanesPerPair * u;
+      const int e = e0 + 64 * u;
       ent[u] = gload(&col[e < nnz ? e : 0]);
     }
   };
   auto use = [&](int e0, const uint64_t (&ent)[kChunk]) {
 #pragma unroll
     for (int u = 0; u < kChunk; ++u) {
-      const int e = e0 + kLanesPerPair * u;
+      const int e = e0 + 64 * u;
       if (e < nnz) {
         const int m = (int)(uint32_t)ent[u];
         const float w = __uint_as_float((uint32_t)(ent[u] >> 32));
@@ -113,8 +113,8 @@ __device__ __forceinline__ void chunk_logit_delta(float* zt, const float* w2, co
       }
     }
   };
-  if (active && nnz > 0) {
-    constexpr int kStride = kLanesPerPair * kChunk;
+  if (nnz > 0) {
+    constexpr int kStride = 64 * kChunk;
     uint64_t ea[kChunk], eb[kChunk];
     fetch(g, ea);
 #pragma unroll 1
@@ -128,7 +128,8 @@ __device__ __forceinline__ void chunk_logit_delta(float* zt, const float* w2, co
 #pragma unroll
   for (int p = 0; p < kPairChunk; ++p)
 #pragma unroll
-    for (int c = 0; c < CM; ++c) acc[p][c] = half_sum(acc[p][c]);
+    for (int c = 0; c < CM; ++c)
+      if (p < np) acc[p][c] = wave_sum(acc[p][c]);
 }
 
 }  // namespace
@@ -279,39 +280,37 @@ __global__ __launch_bounds__(kSlabThreads) void k_slab(NetDev net_arg, const mca
   // Every load is issued from an index clamped into its array and its value
   // selected when it is stored (a load under a branch would make the merge
   // wait for every load in flight).
+  // Four samples of a unit a load (n0 is a multiple of four; a quad past the
+  // padded row is read from the row's start and belongs to no sample), a unit's
+  // weights by one thread: the divisions by n_2 of one value a load cost as much
+  // as a fifth of the scoring.
   auto stage = [&]() {
-    for (int e0 = tid; e0 < n2 * T; e0 += kStageU * kSlabThreads) {
-      float v[kStageU];
+    constexpr int TQ = T / 4;
+    for (int e0 = tid; e0 < n2 * TQ; e0 += kStage4 * kSlabThreads) {
+      f32x4 v[kStage4];
 #pragma unroll
-      for (int u = 0; u < kStageU; ++u) {
+      for (int u = 0; u < kStage4; ++u) {
         const int e = e0 + u * kSlabThreads;
-        const int m = e / T, t = e - m * T;
-        const bool ok = e < n2 * T && n0 + t < N;
-        v[u] = gload(&Z2[ok ? (int64_t)m * Ns + n0 + t : 0]);
+        const int m = e / TQ, t = 4 * (e - m * TQ);
+        v[u] = gload(reinterpret_cast<const f32x4*>(
+            &Z2[(int64_t)(e < n2 * TQ ? m : 0) * Ns + (n0 + t < Ns ? n0 + t : 0)]));
       }
 #pragma unroll
-      for (int u = 0; u < kStageU; ++u) {
+      for (int u = 0; u < kStage4; ++u) {
         const int e = e0 + u * kSlabThreads;
-        const int m = e / T, t = e - m * T;
-        if (e < n2 * T) zt[m * TS + t] = (n0 + t < N) ? v[u] : 0.f;
+        const int m = e / TQ, t = 4 * (e - m * TQ);
+        if (e < n2 * TQ)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) zt[m * TS + t + i] = v[u][i];
       }
     }
     const float* WL = net.W[L - 1];
-    for (int e0 = tid; e0 < CM * n2; e0 += kStageU * kSlabThreads) {
-      float v[kStageU];
+    for (int m = tid; m < n2; m += kSlabThreads) {
+      float v[CM];
 #pragma unroll
-      for (int u = 0; u < kStageU; ++u) {
-        const int e = e0 + u * kSlabThreads;
-        const int c = e / n2, m = e - c * n2;
-        const bool ok = e < CM * n2 && c < C;
-        v[u] = gload(&WL[ok ? (int64_t)c * n2 + m : 0]);
-      }
+      for (int c = 0; c < CM; ++c) v[c] = gload(&WL[(int64_t)(c < C ? c : 0) * n2 + m]);
 #pragma unroll
-      for (int u = 0; u < kStageU; ++u) {
-        const int e = e0 + u * kSlabThreads;
-        const int c = e / n2, m = e - c * n2;
-        if (e < CM * n2) w2[m * CM + c] = (c < C) ? v[u] : 0.f;
-      }
+      for (int c = 0; c < CM; ++c) w2[m * CM + c] = (c < C) ? v[c] : 0.f;
     }
   };
   // The commit reads and writes only the units of the winner's column list:
@@ -448,14 +447,13 @@ __global__ __launch_bounds__(kSlabThreads) void k_slab(NetDev net_arg, const mca
       stage_listed(cols + (int64_t)kc * n2, nnz[kc]);
       __syncthreads();
     }
-    // 4. score: half-wave h takes items h, h + kHalves, ...; every half-wave
-    // runs the same rounds (the wave shares its shuffles)
-    for (int i0 = 0; i0 < ni; i0 += kHalves) {
-      const int it = i0 + (tid >> 5);
-      const bool active = it < ni;
-      const int code = active ? items[it] : 0;
+    // 4. score: wave w takes items w, w + kWaves, ... (a whole wave an item: at
+    // 47 items a block, the ternary net's, 32 half-waves would take two rounds
+    // at three quarters of their lanes)
+    for (int it = wave; it < ni; it += kWaves) {
+      const int code = __builtin_amdgcn_readfirstlane(items[it]);
       const int s = code >> 4, ch = code & 15;
-      uint32_t pm = active ? pmask[s] : 0u;
+      uint32_t pm = __builtin_amdgcn_readfirstlane(pmask[s]);
       for (int r = 0; r < kPairChunk * ch; ++r) pm &= pm - 1u;  // the earlier chunks' samples
       int tp[kPairChunk];
       float dp[kPairChunk];
@@ -472,46 +470,47 @@ __global__ __launch_bounds__(kSlabThreads) void k_slab(NetDev net_arg, const mca
           np = p + 1;
         }
       }
-      const int k = gk[s];
-      const uint64_t* col = cols + (int64_t)k * n2;
-      const int cnt = active ? gnnz[s] : 0;
+      const uint64_t* col = cols + (int64_t)__builtin_amdgcn_readfirstlane(gk[s]) * n2;
+      const int cnt = __builtin_amdgcn_readfirstlane(gnnz[s]);
       float acc[kPairChunk][CM];
       if (commit)  // the commit also writes the new fields into the tile
-        chunk_logit_delta<CM, ACT, TS, true>(zt, w2, col, cnt, tp, dp, np, gamma, active, acc);
+        chunk_logit_delta<CM, ACT, TS, true>(zt, w2, col, cnt, tp, dp, np, gamma, acc);
       else
-        chunk_logit_delta<CM, ACT, TS, false>(zt, w2, col, cnt, tp, dp, np, gamma, active, acc);
-      if (active && (tid & (kLanesPerPair - 1)) == 0) {
+        chunk_logit_delta<CM, ACT, TS, false>(zt, w2, col, cnt, tp, dp, np, gamma, acc);
+      if (lane < np) {  // lane p finishes pair p
+        int t = tp[0];
+        float pr[CM], dz[CM];
 #pragma unroll
-        for (int p = 0; p < kPairChunk; ++p) {
-          if (p < np) {
-            const int t = tp[p];
-            const int64_t n = n0 + t;
-            float pr[CM], dz[CM];
+        for (int c = 0; c < CM; ++c) dz[c] = acc[0][c];
 #pragma unroll
-            for (int c = 0; c < CM; ++c) {
-              pr[c] = plt[c * T + t];
-              dz[c] = (c < C) ? acc[p][c] : 0.f;
+        for (int p = 1; p < kPairChunk; ++p) {
+          t = lane == p ? tp[p] : t;
+#pragma unroll
+          for (int c = 0; c < CM; ++c) dz[c] = lane == p ? acc[p][c] : dz[c];
+        }
+        const int64_t n = n0 + t;
+        const int y = yt[t];
+        float dzy = 0.f;
+#pragma unroll
+        for (int c = 0; c < CM; ++c) {
+          pr[c] = plt[c * T + t];
+          dz[c] = (c < C) ? dz[c] : 0.f;
+          dzy = (c == y) ? dz[c] : dzy;
+        }
+        dlp[s * T + t] = ce_change<CM>(pr, dz, C, dzy);
+        if (commit) {
+          float z[CM], pn[CM];
+#pragma unroll
+          for (int c = 0; c < CM; ++c) z[c] = (c < C) ? zlt[c * T + t] + dz[c] : 0.f;
+          const float ln = softmax_ce<CM>(z, C, y, pn);
+#pragma unroll
+          for (int c = 0; c < CM; ++c)
+            if (c < C) {
+              gstore(&ZL[(int64_t)c * Ns + n], z[c]);
+              gstore(&net.prob[(int64_t)c * Ns + n], pn[c]);
             }
-            const int y = yt[t];
-            float dzy = 0.f;
-#pragma unroll
-            for (int c = 0; c < CM; ++c) dzy = (c == y) ? dz[c] : dzy;
-            dlp[s * T + t] = ce_change<CM>(pr, dz, C, dzy);
-            if (commit) {
-              float z[CM], pn[CM];
-#pragma unroll
-              for (int c = 0; c < CM; ++c) z[c] = (c < C) ? zlt[c * T + t] + dz[c] : 0.f;
-              const float ln = softmax_ce<CM>(z, C, y, pn);
-#pragma unroll
-              for (int c = 0; c < CM; ++c)
-                if (c < C) {
-                  gstore(&ZL[(int64_t)c * Ns + n], z[c]);
-                  gstore(&net.prob[(int64_t)c * Ns + n], pn[c]);
-                }
-              gstore(&net.ell[n], ln);
-              atomicOr(&touched, 1u << t);
-            }
-          }
+          gstore(&net.ell[n], ln);
+          atomicOr(&touched, 1u << t);
         }
       }
     }
