@@ -93,7 +93,7 @@ __device__ __forceinline__ mca_cand placeholder() {
 
 __global__ void k_channel_propose(NetDev net_arg, uint64_t t_host, int use_dev_t,
                                   const DevState* st, int K, mca_channel* chans, mca_cand* cands,
-                                  Aux* aux) {
+                                  Aux* aux, mca_channel* host) {
   __shared__ NetDev net;
   stage_net(net, net_arg);
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
@@ -101,19 +101,22 @@ __global__ void k_channel_propose(NetDev net_arg, uint64_t t_host, int use_dev_t
   const uint64_t t = use_dev_t ? st->t : t_host;
   const mca_channel ch = draw_channel(net, t, (uint64_t)k);
   chans[k] = ch;
+  if (host != nullptr) host[k] = ch;
   Aux a = channel_aux(net, ch);
   a.theta = accept_theta(net.rule, net.beta, net.seed, net.tag, t, (uint64_t)k);
   aux[k] = a;
   cands[k] = placeholder();
 }
 
-__global__ void k_channel_prepare(NetDev net_arg, const mca_channel* chans, int K,
-                                  mca_cand* cands, Aux* aux) {
+__global__ void k_channel_prepare(NetDev net_arg, mca_channel* chans, int K,
+                                  mca_cand* cands, Aux* aux, const mca_channel* host) {
   __shared__ NetDev net;
   stage_net(net, net_arg);
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= K) return;
-  aux[k] = channel_aux(net, chans[k]);
+  const mca_channel ch = host != nullptr ? host[k] : chans[k];
+  if (host != nullptr) chans[k] = ch;
+  aux[k] = channel_aux(net, ch);
   cands[k] = placeholder();
 }
 
@@ -498,16 +501,16 @@ __global__ void k_channel_weights(NetDev net, const mca_channel* chans, int k_mo
 
 hipError_t launch_channel_propose(const NetDev& net, uint64_t t, bool use_dev_t,
                                   const DevState* st, int K, mca_channel* ch, mca_cand* cands,
-                                  Aux* aux, hipStream_t s) {
+                                  Aux* aux, hipStream_t s, mca_channel* host) {
   hipLaunchKernelGGL(k_channel_propose, dim3((K + 63) / 64), dim3(64), 0, s, net, t,
-                     use_dev_t ? 1 : 0, st, K, ch, cands, aux);
+                     use_dev_t ? 1 : 0, st, K, ch, cands, aux, host);
   return hipGetLastError();
 }
 
-hipError_t launch_channel_prepare(const NetDev& net, const mca_channel* ch, int K,
-                                  mca_cand* cands, Aux* aux, hipStream_t s) {
+hipError_t launch_channel_prepare(const NetDev& net, mca_channel* ch, int K,
+                                  mca_cand* cands, Aux* aux, hipStream_t s, const mca_channel* host) {
   hipLaunchKernelGGL(k_channel_prepare, dim3((K + 63) / 64), dim3(64), 0, s, net, ch, K, cands,
-                     aux);
+                     aux, host);
   return hipGetLastError();
 }
 

@@ -31,10 +31,11 @@ struct ChannelLists {
 // cands (the shared selection reads one).
 hipError_t launch_channel_propose(const NetDev& net, uint64_t t, bool use_dev_t,
                                   const DevState* st, int K, mca_channel* ch, mca_cand* cands,
-                                  Aux* aux, hipStream_t s);
+                                  Aux* aux, hipStream_t s, mca_channel* host = nullptr);
 // The same acceptance data for K channels given by the caller (threshold 0).
-hipError_t launch_channel_prepare(const NetDev& net, const mca_channel* ch, int K,
-                                  mca_cand* cands, Aux* aux, hipStream_t s);
+hipError_t launch_channel_prepare(const NetDev& net, mca_channel* ch, int K,
+                                  mca_cand* cands, Aux* aux, hipStream_t s,
+                                  const mca_channel* host = nullptr);
 // k_mode -2: partial[k * nchan + tile] for every channel k < K; -1: commit
 // st->chosen (nothing when -1); >= 0: commit that channel.  A commit moves
 // every cached field and writes the path's weights, the loss and the count.

@@ -473,6 +473,11 @@ struct mca_ctx {
   mca::LoopSync* loop_sync = nullptr;
   DevState* snap = nullptr;  // counters at the start of the current run_steps call
   unsigned char* host_blk = nullptr;  // pinned host copy of the state block (null: none)
+  // Pinned host memory that the kernels of the explicit calls read and write in
+  // place of copies (null: none, copies are made): k_max candidate or channel
+  // records, and k_max loss changes with the committed loss behind them.
+  void* io_recs = nullptr;
+  double* io_dl = nullptr;
   bool use_loop = true;
   bool loop_coop = false;    // cooperative launch of the step loop (default: ordinary)
   void* scratch_dev = nullptr;  // this device's static scratch array (no-allocation entry point)
@@ -711,6 +716,24 @@ int check_cands(mca_ctx* ctx, const mca_cand* c, int K) {
   return MCA_OK;
 }
 
+// Pinned host memory for the state read-back of every run_steps call and for
+// the explicit calls' records and loss changes (where it cannot be had, plain
+// host buffers and copies take its place).
+void pin_host(mca_ctx* ctx) {
+  if (hipHostMalloc((void**)&ctx->host_blk, kStateBlock, hipHostMallocDefault) != hipSuccess) {
+    ctx->host_blk = nullptr;
+    (void)hipGetLastError();
+  }
+  const size_t K = (size_t)std::max<int64_t>(ctx->k_max, mca::kMaxK);  // (the no-allocation call takes any K up to kMaxK)
+  const size_t recs = align_up(K * (ctx->chan ? sizeof(mca_channel) : sizeof(mca_cand)));
+  if (hipHostMalloc(&ctx->io_recs, recs + (K + 1) * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+    ctx->io_recs = nullptr;
+    (void)hipGetLastError();
+  } else {
+    ctx->io_dl = (double*)((char*)ctx->io_recs + recs);
+  }
+}
+
 // Where one evaluation's per-call buffers live: the context's workspace, or
 // the static scratch array of the no-allocation entry point.
 struct Bufs {
@@ -733,26 +756,48 @@ Bufs ctx_bufs(const mca_ctx* ctx) {
               ctx->cols, ctx->nnz, ctx->rows, ctx->rda, ctx->rcnt, ctx->pchain};
 }
 
-hipError_t propose_dev(mca_ctx* ctx, uint64_t step, bool use_dev_t, int K) {
+// host (may be null): pinned memory that also receives the records.
+hipError_t propose_dev(mca_ctx* ctx, uint64_t step, bool use_dev_t, int K, void* host = nullptr) {
   if (ctx->chan)
     return mca::launch_channel_propose(ctx->net, step, use_dev_t, ctx->st, K, ctx->chans,
-                                       ctx->cands, ctx->aux, ctx->stream);
+                                       ctx->cands, ctx->aux, ctx->stream, (mca_channel*)host);
   if (ctx->tf)
     return mca::tf_launch_propose(ctx->tfd, ctx->tfh, step, use_dev_t, ctx->st, K, ctx->cands,
-                                  ctx->aux, ctx->stream);
+                                  ctx->aux, ctx->stream, (mca_cand*)host);
   // (a bias of a first-layer unit has no input feature: no tile list for it)
   return mca::launch_propose(ctx->net, step, use_dev_t, ctx->st, K, ctx->cands, ctx->aux,
-                             ctx->norm ? nullptr : ctx->fmask, ctx->cmask, ctx->stream);
+                             ctx->norm ? nullptr : ctx->fmask, ctx->cmask, ctx->stream, (mca_cand*)host);
 }
 
-hipError_t prepare_into(mca_ctx* ctx, const Bufs& b, int K) {
-  if (ctx->chan)
-    return mca::launch_channel_prepare(ctx->net, ctx->chans, K, b.cands, b.aux, ctx->stream);
-  if (ctx->tf) return mca::tf_launch_prepare(ctx->tfd, b.cands, K, b.aux, ctx->stream);
-  return mca::launch_prepare(ctx->net, b.cands, K, b.aux, ctx->norm ? nullptr : ctx->fmask,
-                             b.cmask, ctx->stream);
+// Proposes K records of `step` and hands them to the caller.  A copy into
+// pageable memory is a launch and a staged transfer of its own; the kernel
+// writes the few bytes through the bus itself.
+template <class Rec>
+int propose_out(mca_ctx* ctx, uint64_t step, int K, const Rec* dev, Rec* out) {
+  MCA_HIP(ctx, timed(ctx, 0, [&] { return propose_dev(ctx, step, false, K, ctx->io_recs); }));
+  if (ctx->io_recs == nullptr)
+    MCA_HIP(ctx, hipMemcpyAsync(out, dev, (size_t)K * sizeof(Rec), hipMemcpyDeviceToHost, ctx->stream));
+  MCA_HIP(ctx, wait_stream(ctx->stream));
+  if (ctx->io_recs != nullptr) std::memcpy(out, ctx->io_recs, (size_t)K * sizeof(Rec));
+  return MCA_OK;
 }
-hipError_t prepare_dev(mca_ctx* ctx, int K) { return prepare_into(ctx, ctx_bufs(ctx), K); }
+
+// Puts the caller's K records and their prepared values into the buffers.
+template <class Rec>
+hipError_t prepare_in(mca_ctx* ctx, const Bufs& b, int K, Rec* dev, const Rec* in) {
+  const void* host = ctx->io_recs;
+  if (host != nullptr) {
+    std::memcpy(ctx->io_recs, in, (size_t)K * sizeof(Rec));
+  } else {
+    const hipError_t e = hipMemcpyAsync(dev, in, (size_t)K * sizeof(Rec), hipMemcpyHostToDevice, ctx->stream);
+    if (e != hipSuccess) return e;
+  }
+  if (ctx->chan)
+    return mca::launch_channel_prepare(ctx->net, ctx->chans, K, b.cands, b.aux, ctx->stream, (const mca_channel*)host);
+  if (ctx->tf) return mca::tf_launch_prepare(ctx->tfd, b.cands, K, b.aux, ctx->stream, (const mca_cand*)host);
+  return mca::launch_prepare(ctx->net, b.cands, K, b.aux, ctx->norm ? nullptr : ctx->fmask,
+                             b.cmask, ctx->stream, (const mca_cand*)host);
+}
 
 // Scores the K staged candidates: the column kernel for the last two layers,
 // the tile kernel for layer L-3, the dense chain for layers 0..L-4.
@@ -796,13 +841,13 @@ hipError_t propose_step(mca_ctx* ctx, const NetDev& net, int K) {
 }
 
 hipError_t select_into(mca_ctx* ctx, const NetDev& net, const Bufs& b, int K, bool do_select,
-                       int32_t* trc, double* trd) {
+                       int32_t* trc, double* trd, double* host = nullptr) {
   if (ctx->norm) {
     NetDev one = net;  // one source of tile sums for every candidate
     one.L = 0;
     return mca::launch_select(one, ctx->pnorm, ctx->lo.nnorm, b.cands, nullptr, 0, nullptr, 0,
                               b.aux, K, b.dl, ctx->st, do_select, trc, trd, kTraceCap,
-                              ctx->stream);
+                              ctx->stream, host);
   }
   if (ctx->chan) {
     // every channel has one source of tile sums (an L = 0 view of the net
@@ -811,19 +856,42 @@ hipError_t select_into(mca_ctx* ctx, const NetDev& net, const Bufs& b, int K, bo
     one.L = 0;
     return mca::launch_select(one, ctx->pchan, ctx->lo.nchan, b.cands, nullptr, 0, nullptr, 0,
                               b.aux, K, b.dl, ctx->st, do_select, trc, trd, kTraceCap,
-                              ctx->stream);
+                              ctx->stream, host);
   }
   if (ctx->tf)
     return mca::launch_select(net, b.partial, ctx->tf_nblk, b.cands, nullptr, 0, nullptr, 0,
                               b.aux, K, b.dl, ctx->st, do_select, trc, trd, kTraceCap,
-                              ctx->stream);
+                              ctx->stream, host);
   return mca::launch_select(net, b.partial, ctx->lo.ntiles_ev, b.cands, b.pslab,
                             ctx->lo.nslab, b.pchain, ctx->lo.nchain, b.aux, K, b.dl,
-                            ctx->st, do_select, trc, trd, kTraceCap, ctx->stream);
+                            ctx->st, do_select, trc, trd, kTraceCap, ctx->stream, host);
 }
 hipError_t select_all(mca_ctx* ctx, const NetDev& net, int K, bool do_select, int32_t* trc,
                       double* trd) {
   return select_into(ctx, net, ctx_bufs(ctx), K, do_select, trc, trd);
+}
+
+// Reduces an explicit batch (no selection), and hands its loss changes and the
+// losses they lead to to the caller; dl gets the changes.
+int losses_out(mca_ctx* ctx, const NetDev& net, const Bufs& b, int K, double* loss_out, double* dloss_out,
+               std::vector<double>& dl) {
+  MCA_HIP(ctx, timed(ctx, 2, [&] { return select_into(ctx, net, b, K, false, nullptr, nullptr, ctx->io_dl); }));
+  dl.resize(K);
+  double L_c = 0.0;
+  if (ctx->io_dl == nullptr) {
+    MCA_HIP(ctx, hipMemcpyAsync(dl.data(), b.dl, (size_t)K * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
+    MCA_HIP(ctx, hipMemcpyAsync(&L_c, &ctx->st->L, sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
+  }
+  MCA_HIP(ctx, wait_stream(ctx->stream));
+  if (ctx->io_dl != nullptr) {
+    std::memcpy(dl.data(), ctx->io_dl, (size_t)K * sizeof(double));
+    L_c = ctx->io_dl[K];
+  }
+  for (int k = 0; k < K; ++k) {
+    if (loss_out) loss_out[k] = L_c + dl[k];
+    if (dloss_out) dloss_out[k] = dl[k];
+  }
+  return MCA_OK;
 }
 
 // Commits candidate k (k < 0: the device decision) of a batch of K; each
@@ -984,12 +1052,7 @@ int tf_init(mca_ctx** out, const mca_net_desc* net, const float* const* params, 
     delete ctx;
     return rc;
   }
-  // pinned host memory for the state read-back of every run_steps call (a
-  // plain host buffer is used if it cannot be had)
-  if (hipHostMalloc((void**)&ctx->host_blk, kStateBlock, hipHostMallocDefault) != hipSuccess) {
-    ctx->host_blk = nullptr;
-    (void)hipGetLastError();
-  }
+  pin_host(ctx);
   *out = ctx;
   return MCA_OK;
 }
@@ -1187,12 +1250,7 @@ int mca_init(mca_ctx** out, const mca_net_desc* net, const float* const* params,
     delete ctx;
     return rc;
   }
-  // pinned host memory for the state read-back of every run_steps call (a
-  // plain host buffer is used if it cannot be had)
-  if (hipHostMalloc((void**)&ctx->host_blk, kStateBlock, hipHostMallocDefault) != hipSuccess) {
-    ctx->host_blk = nullptr;
-    (void)hipGetLastError();
-  }
+  pin_host(ctx);
   *out = ctx;
   return MCA_OK;
 }
@@ -1204,10 +1262,7 @@ int mca_propose(mca_ctx* ctx, uint64_t step, int32_t K, mca_cand* out_host) {
   if (out_host == nullptr) return fail(ctx, MCA_EINVAL, "out_host is NULL");
   // the proposal reuses the candidate buffers of a pending batch
   if (ctx->pending) return fail(ctx, MCA_ESTATE, "a batch is pending: commit or roll back first");
-  MCA_HIP(ctx, timed(ctx, 0, [&] { return propose_dev(ctx, step, false, K); }));
-  MCA_HIP(ctx, hipMemcpyAsync(out_host, ctx->cands, (size_t)K * sizeof(mca_cand), hipMemcpyDeviceToHost, ctx->stream));
-  MCA_HIP(ctx, hipStreamSynchronize(ctx->stream));
-  return MCA_OK;
+  return propose_out(ctx, step, K, ctx->cands, out_host);
 }
 
 int mca_eval_losses(mca_ctx* ctx, const mca_cand* cands_host, int32_t K, double* loss_out,
@@ -1219,22 +1274,13 @@ int mca_eval_losses(mca_ctx* ctx, const mca_cand* cands_host, int32_t K, double*
   if (cands_host == nullptr) return fail(ctx, MCA_EINVAL, "cands_host is NULL");
   int rc = check_cands(ctx, cands_host, K);
   if (rc != MCA_OK) return rc;
-  MCA_HIP(ctx, hipMemcpyAsync(ctx->cands, cands_host, (size_t)K * sizeof(mca_cand), hipMemcpyHostToDevice, ctx->stream));
-  MCA_HIP(ctx, timed(ctx, 0, [&] { return prepare_dev(ctx, K); }));
+  const Bufs b = ctx_bufs(ctx);
+  MCA_HIP(ctx, timed(ctx, 0, [&] { return prepare_in(ctx, b, K, ctx->cands, cands_host); }));
   MCA_HIP(ctx, timed(ctx, 1, [&] { return eval_all(ctx, ctx->net, K); }));
-  MCA_HIP(ctx, timed(ctx, 2, [&] { return select_all(ctx, ctx->net, K, false, nullptr, nullptr); }));
-  std::vector<double> dl(K);
-  DevState s{};
-  MCA_HIP(ctx, hipMemcpyAsync(dl.data(), ctx->dl, (size_t)K * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
-  MCA_HIP(ctx, hipMemcpyAsync(&s, ctx->st, sizeof s, hipMemcpyDeviceToHost, ctx->stream));
-  MCA_HIP(ctx, hipStreamSynchronize(ctx->stream));
-  for (int k = 0; k < K; ++k) {
-    if (loss_out) loss_out[k] = s.L + dl[k];
-    if (dloss_out) dloss_out[k] = dl[k];
-  }
+  rc = losses_out(ctx, ctx->net, b, K, loss_out, dloss_out, ctx->pending_dl);
+  if (rc != MCA_OK) return rc;
   ctx->pending = true;
   ctx->pending_K = K;
-  ctx->pending_dl = dl;
   return MCA_OK;
 }
 
@@ -1266,10 +1312,7 @@ int mca_propose_channels(mca_ctx* ctx, uint64_t step, int32_t K, mca_channel* ou
   if (K < 1 || K > ctx->k_max) return fail(ctx, MCA_EINVAL, "K out of range [1, k_max]");
   if (out_host == nullptr) return fail(ctx, MCA_EINVAL, "out_host is NULL");
   if (ctx->pending) return fail(ctx, MCA_ESTATE, "a batch is pending: commit or roll back first");
-  MCA_HIP(ctx, timed(ctx, 0, [&] { return propose_dev(ctx, step, false, K); }));
-  MCA_HIP(ctx, hipMemcpyAsync(out_host, ctx->chans, (size_t)K * sizeof(mca_channel), hipMemcpyDeviceToHost, ctx->stream));
-  MCA_HIP(ctx, hipStreamSynchronize(ctx->stream));
-  return MCA_OK;
+  return propose_out(ctx, step, K, ctx->chans, out_host);
 }
 
 int mca_eval_channels(mca_ctx* ctx, const mca_channel* chans_host, int32_t K, double* loss_out,
@@ -1287,22 +1330,13 @@ int mca_eval_channels(mca_ctx* ctx, const mca_channel* chans_host, int32_t K, do
     for (int m = 0; m < d.n_layers; ++m)
       if (!std::isfinite(chans_host[k].w_new[m])) return fail(ctx, MCA_EINVAL, "channel weight is not finite");
   }
-  MCA_HIP(ctx, hipMemcpyAsync(ctx->chans, chans_host, (size_t)K * sizeof(mca_channel), hipMemcpyHostToDevice, ctx->stream));
-  MCA_HIP(ctx, timed(ctx, 0, [&] { return prepare_dev(ctx, K); }));
+  const Bufs b = ctx_bufs(ctx);
+  MCA_HIP(ctx, timed(ctx, 0, [&] { return prepare_in(ctx, b, K, ctx->chans, chans_host); }));
   MCA_HIP(ctx, timed(ctx, 1, [&] { return eval_all(ctx, ctx->net, K); }));
-  MCA_HIP(ctx, timed(ctx, 2, [&] { return select_all(ctx, ctx->net, K, false, nullptr, nullptr); }));
-  std::vector<double> dl(K);
-  DevState s{};
-  MCA_HIP(ctx, hipMemcpyAsync(dl.data(), ctx->dl, (size_t)K * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
-  MCA_HIP(ctx, hipMemcpyAsync(&s, ctx->st, sizeof s, hipMemcpyDeviceToHost, ctx->stream));
-  MCA_HIP(ctx, hipStreamSynchronize(ctx->stream));
-  for (int k = 0; k < K; ++k) {
-    if (loss_out) loss_out[k] = s.L + dl[k];
-    if (dloss_out) dloss_out[k] = dl[k];
-  }
+  const int rc = losses_out(ctx, ctx->net, b, K, loss_out, dloss_out, ctx->pending_dl);
+  if (rc != MCA_OK) return rc;
   ctx->pending = true;
   ctx->pending_K = K;
-  ctx->pending_dl = dl;
   return MCA_OK;
 }
 
@@ -1364,20 +1398,10 @@ int mca_eval_losses_noalloc(mca_ctx* ctx, const mca_cand* cands_host, int32_t K,
   // every scratch word a kernel reads is written earlier in this call (the
   // prepared values, masks, lists, counts, tile sums and loss changes), so
   // nothing is cleared; overlapping calls on one GPU would race on them
-  MCA_HIP(ctx, hipMemcpyAsync(b.cands, cands_host, kk * sizeof(mca_cand), hipMemcpyHostToDevice, ctx->stream));
-  MCA_HIP(ctx, prepare_into(ctx, b, K));
+  MCA_HIP(ctx, prepare_in(ctx, b, K, b.cands, cands_host));
   MCA_HIP(ctx, eval_into(ctx, net, b, K));
-  MCA_HIP(ctx, select_into(ctx, net, b, K, false, nullptr, nullptr));
-  std::vector<double> dl(K);
-  double L_c = 0.0;
-  MCA_HIP(ctx, hipMemcpyAsync(dl.data(), b.dl, kk * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
-  MCA_HIP(ctx, hipMemcpyAsync(&L_c, &ctx->st->L, sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
-  MCA_HIP(ctx, hipStreamSynchronize(ctx->stream));
-  for (int k = 0; k < K; ++k) {
-    if (loss_out) loss_out[k] = L_c + dl[k];
-    if (dloss_out) dloss_out[k] = dl[k];
-  }
-  return MCA_OK;
+  std::vector<double> dl;
+  return losses_out(ctx, net, b, K, loss_out, dloss_out, dl);
 }
 
 int mca_set_option(mca_ctx* ctx, int32_t option, int64_t value) {
@@ -1660,6 +1684,7 @@ void mca_destroy(mca_ctx* ctx) {
   }
   for (auto e : ctx->pool) (void)hipEventDestroy(e);
   if (ctx->host_blk) (void)hipHostFree(ctx->host_blk);
+  if (ctx->io_recs) (void)hipHostFree(ctx->io_recs);
   delete ctx;
 }
 

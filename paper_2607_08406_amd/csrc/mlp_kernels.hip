@@ -26,7 +26,7 @@ namespace mca {
 
 __global__ void k_propose(NetDev net_arg, uint64_t t_host, int use_dev_t, const DevState* st,
                           int K, mca_cand* cands, Aux* aux, const uint64_t* fmask,
-                          uint64_t* cmask) {
+                          uint64_t* cmask, mca_cand* host) {
   __shared__ NetDev net;
   stage_net(net, net_arg);
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
@@ -34,19 +34,21 @@ __global__ void k_propose(NetDev net_arg, uint64_t t_host, int use_dev_t, const 
   const uint64_t t = use_dev_t ? st->t : t_host;
   const mca_cand c = decode_candidate(net, t, (uint64_t)k);
   cands[k] = c;
+  if (host != nullptr) host[k] = c;
   Aux a = prepare_candidate(net, c);
   a.theta = accept_theta(net.rule, net.beta, net.seed, net.tag, t, (uint64_t)k);
   aux[k] = a;
   cmask[k] = candidate_tiles(c, fmask);
 }
 
-__global__ void k_prepare(NetDev net_arg, const mca_cand* cands, int K, Aux* aux,
-                          const uint64_t* fmask, uint64_t* cmask) {
+__global__ void k_prepare(NetDev net_arg, mca_cand* cands, int K, Aux* aux,
+                          const uint64_t* fmask, uint64_t* cmask, const mca_cand* host) {
   __shared__ NetDev net;
   stage_net(net, net_arg);
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= K) return;
-  const mca_cand c = cands[k];
+  const mca_cand c = host != nullptr ? host[k] : cands[k];
+  if (host != nullptr) cands[k] = c;
   aux[k] = prepare_candidate(net, c);
   cmask[k] = candidate_tiles(c, fmask);
 }
@@ -397,12 +399,16 @@ constexpr int kSelThreads = 64;
 constexpr int kSelPerBlock = kSelThreads / 16;
 __global__ __launch_bounds__(kSelThreads) void k_reduce_select(
     const NetDev net, PartialSrc src, const mca_cand* cands, const Aux* aux, int K, double* dL,
-    DevState* st, int do_select, int32_t* tr_chosen, double* tr_dl, int64_t tr_cap) {
+    DevState* st, int do_select, int32_t* tr_chosen, double* tr_dl, int64_t tr_cap, double* host) {
   const int tid = threadIdx.x;
   {
     const int k = blockIdx.x * kSelPerBlock + (tid >> 4), r = tid & 15;
     const double v = candidate_dl(net, src, cands, aux, K, k, r);
     if (k < K && r == 0) dL[k] = v;
+    if (host != nullptr) {  // and the committed loss behind the changes
+      if (k < K && r == 0) host[k] = v;
+      if (blockIdx.x == 0 && tid == 0) host[K] = st->L;
+    }
   }
   if (!do_select) return;
   __shared__ int last;
@@ -800,16 +806,16 @@ __global__ void k_loss_total(NetDev net, const double* bsum, int nb, DevState* s
 
 hipError_t launch_propose(const NetDev& net, uint64_t t, bool use_dev_t, const DevState* st,
                           int K, mca_cand* cands, Aux* aux, const uint64_t* fmask,
-                          uint64_t* cmask, hipStream_t s) {
+                          uint64_t* cmask, hipStream_t s, mca_cand* host) {
   hipLaunchKernelGGL(k_propose, dim3((K + 63) / 64), dim3(64), 0, s, net, t, use_dev_t ? 1 : 0,
-                     st, K, cands, aux, fmask, cmask);
+                     st, K, cands, aux, fmask, cmask, host);
   return hipGetLastError();
 }
 
-hipError_t launch_prepare(const NetDev& net, const mca_cand* cands, int K, Aux* aux,
-                          const uint64_t* fmask, uint64_t* cmask, hipStream_t s) {
+hipError_t launch_prepare(const NetDev& net, mca_cand* cands, int K, Aux* aux,
+                          const uint64_t* fmask, uint64_t* cmask, hipStream_t s, const mca_cand* host) {
   hipLaunchKernelGGL(k_prepare, dim3((K + 63) / 64), dim3(64), 0, s, net, cands, K, aux, fmask,
-                     cmask);
+                     cmask, host);
   return hipGetLastError();
 }
 
@@ -885,7 +891,7 @@ hipError_t launch_select(const NetDev& net, const float* partial, int ntiles,
                          const mca_cand* cands, const float* pslab, int nslab,
                          const float* pchain, int nchain, const Aux* aux, int K, double* dL,
                          DevState* st, bool do_select, int32_t* tr_chosen, double* tr_dl,
-                         int64_t tr_cap, hipStream_t s) {
+                         int64_t tr_cap, hipStream_t s, double* host) {
   PartialSrc src;
   src.partial = partial;
   src.ntiles = ntiles;
@@ -897,7 +903,7 @@ hipError_t launch_select(const NetDev& net, const float* partial, int ntiles,
   src.chain_top = (net.L >= 4) ? net.L - 4 : -1;
   const int nblk = K > 0 ? (K + kSelPerBlock - 1) / kSelPerBlock : 1;
   hipLaunchKernelGGL(k_reduce_select, dim3(nblk), dim3(kSelThreads), 0, s, net, src, cands, aux,
-                     K, dL, st, do_select ? 1 : 0, tr_chosen, tr_dl, tr_cap);
+                     K, dL, st, do_select ? 1 : 0, tr_chosen, tr_dl, tr_cap, host);
   return hipGetLastError();
 }
 

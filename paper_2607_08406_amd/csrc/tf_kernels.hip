@@ -184,7 +184,7 @@ __device__ __forceinline__ float cross_entropy(const float* z, int V, int y) {
 // ---------------------------------------------------------------------------
 
 __global__ void k_tf_propose(const TfDev* tf, uint64_t t_host, int use_dev_t,
-                             const DevState* st, int K, mca_cand* cands, Aux* aux) {
+                             const DevState* st, int K, mca_cand* cands, Aux* aux, mca_cand* host) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= K) return;
   const uint64_t t = use_dev_t ? st->t : t_host;
@@ -206,6 +206,7 @@ __global__ void k_tf_propose(const TfDev* tf, uint64_t t_host, int use_dev_t,
   c.code = 0;
   c.flags = 0;
   cands[k] = c;
+  if (host != nullptr) host[k] = c;
   Aux a;
   a.w_old = tf->param[layer][off];
   a.w_new = a.w_old + c.d;
@@ -215,10 +216,11 @@ __global__ void k_tf_propose(const TfDev* tf, uint64_t t_host, int use_dev_t,
   aux[k] = a;
 }
 
-__global__ void k_tf_prepare(const TfDev* tf, const mca_cand* cands, int K, Aux* aux) {
+__global__ void k_tf_prepare(const TfDev* tf, mca_cand* cands, int K, Aux* aux, const mca_cand* host) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= K) return;
-  const mca_cand c = cands[k];
+  const mca_cand c = host != nullptr ? host[k] : cands[k];
+  if (host != nullptr) cands[k] = c;
   Aux a;
   a.w_old = tf->param[c.layer][(int64_t)c.j * tf->cols[c.layer] + c.i];
   a.w_new = a.w_old + c.d;
@@ -1028,16 +1030,16 @@ int tf_loss_blocks(int64_t N) { return (int)((N + kLossThreads - 1) / kLossThrea
 
 hipError_t tf_launch_propose(const TfDev* tf, const TfDev& h, uint64_t t, bool use_dev_t,
                              const DevState* st, int K, mca_cand* cands, Aux* aux,
-                             hipStream_t s) {
+                             hipStream_t s, mca_cand* host) {
   (void)h;
   hipLaunchKernelGGL(k_tf_propose, dim3((K + 63) / 64), dim3(64), 0, s, tf, t, use_dev_t ? 1 : 0,
-                     st, K, cands, aux);
+                     st, K, cands, aux, host);
   return hipGetLastError();
 }
 
-hipError_t tf_launch_prepare(const TfDev* tf, const mca_cand* cands, int K, Aux* aux,
-                             hipStream_t s) {
-  hipLaunchKernelGGL(k_tf_prepare, dim3((K + 63) / 64), dim3(64), 0, s, tf, cands, K, aux);
+hipError_t tf_launch_prepare(const TfDev* tf, mca_cand* cands, int K, Aux* aux,
+                             hipStream_t s, const mca_cand* host) {
+  hipLaunchKernelGGL(k_tf_prepare, dim3((K + 63) / 64), dim3(64), 0, s, tf, cands, K, aux, host);
   return hipGetLastError();
 }
 

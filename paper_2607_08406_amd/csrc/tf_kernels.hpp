@@ -113,10 +113,10 @@ enum TfGemmRole { kGemmQKV, kGemmO, kGemmFc, kGemmProj, kGemmOut };
 // Candidates k < K of step t (t from st->t when use_dev_t): records and new values.
 hipError_t tf_launch_propose(const TfDev* tf, const TfDev& h, uint64_t t, bool use_dev_t,
                              const DevState* st, int K, mca_cand* cands, Aux* aux,
-                             hipStream_t s);
+                             hipStream_t s, mca_cand* host = nullptr);
 // New values of given candidate records (explicit evaluation).
-hipError_t tf_launch_prepare(const TfDev* tf, const mca_cand* cands, int K, Aux* aux,
-                             hipStream_t s);
+hipError_t tf_launch_prepare(const TfDev* tf, mca_cand* cands, int K, Aux* aux,
+                             hipStream_t s, const mca_cand* host = nullptr);
 // Every stage of every candidate's forward pass from its first changed stage
 // (and the pending dense recomputation in slot kr), and the tile sums of
 // each candidate's per-position loss changes: partial[k * nblk + b].
