@@ -4,7 +4,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -525,19 +524,6 @@ int device_fail(mca_ctx* ctx, hipError_t e, const char* what) {
     if ((ctx)->poisoned) return fail(ctx, MCA_EPOISONED, "context poisoned by an earlier device error: " + (ctx)->err); \
   } while (0)
 
-// Waits for the stream by polling it for up to a millisecond, then blocks: a
-// blocking wait may put the thread to sleep, and waking it costs tens of
-// microseconds, a large share of a call of a few dozen steps.
-hipError_t wait_stream(hipStream_t s) {
-  const auto t0 = std::chrono::steady_clock::now();
-  while (true) {
-    const hipError_t e = hipStreamQuery(s);
-    if (e != hipErrorNotReady) return e;
-    if (std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(1000)) break;
-  }
-  return hipStreamSynchronize(s);
-}
-
 // Events made ahead when timing is switched on (a step-loop call records one
 // pair per launch; the per-phase loop four pairs per step).
 constexpr size_t kEventsAhead = 32;
@@ -777,7 +763,7 @@ int propose_out(mca_ctx* ctx, uint64_t step, int K, const Rec* dev, Rec* out) {
   MCA_HIP(ctx, timed(ctx, 0, [&] { return propose_dev(ctx, step, false, K, ctx->io_recs); }));
   if (ctx->io_recs == nullptr)
     MCA_HIP(ctx, hipMemcpyAsync(out, dev, (size_t)K * sizeof(Rec), hipMemcpyDeviceToHost, ctx->stream));
-  MCA_HIP(ctx, wait_stream(ctx->stream));
+  MCA_HIP(ctx, hipStreamSynchronize(ctx->stream));
   if (ctx->io_recs != nullptr) std::memcpy(out, ctx->io_recs, (size_t)K * sizeof(Rec));
   return MCA_OK;
 }
@@ -871,18 +857,17 @@ hipError_t select_all(mca_ctx* ctx, const NetDev& net, int K, bool do_select, in
   return select_into(ctx, net, ctx_bufs(ctx), K, do_select, trc, trd);
 }
 
-// Reduces an explicit batch (no selection), and hands its loss changes and the
-// losses they lead to to the caller; dl gets the changes.
-int losses_out(mca_ctx* ctx, const NetDev& net, const Bufs& b, int K, double* loss_out, double* dloss_out,
+// Waits for an explicit batch reduced into io_dl, and hands its loss changes and
+// the losses they lead to to the caller; dl gets the changes.
+int losses_out(mca_ctx* ctx, const Bufs& b, int K, double* loss_out, double* dloss_out,
                std::vector<double>& dl) {
-  MCA_HIP(ctx, timed(ctx, 2, [&] { return select_into(ctx, net, b, K, false, nullptr, nullptr, ctx->io_dl); }));
   dl.resize(K);
   double L_c = 0.0;
   if (ctx->io_dl == nullptr) {
     MCA_HIP(ctx, hipMemcpyAsync(dl.data(), b.dl, (size_t)K * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
     MCA_HIP(ctx, hipMemcpyAsync(&L_c, &ctx->st->L, sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
   }
-  MCA_HIP(ctx, wait_stream(ctx->stream));
+  MCA_HIP(ctx, hipStreamSynchronize(ctx->stream));
   if (ctx->io_dl != nullptr) {
     std::memcpy(dl.data(), ctx->io_dl, (size_t)K * sizeof(double));
     L_c = ctx->io_dl[K];
@@ -1277,7 +1262,8 @@ int mca_eval_losses(mca_ctx* ctx, const mca_cand* cands_host, int32_t K, double*
   const Bufs b = ctx_bufs(ctx);
   MCA_HIP(ctx, timed(ctx, 0, [&] { return prepare_in(ctx, b, K, ctx->cands, cands_host); }));
   MCA_HIP(ctx, timed(ctx, 1, [&] { return eval_all(ctx, ctx->net, K); }));
-  rc = losses_out(ctx, ctx->net, b, K, loss_out, dloss_out, ctx->pending_dl);
+  MCA_HIP(ctx, timed(ctx, 2, [&] { return select_into(ctx, ctx->net, b, K, false, nullptr, nullptr, ctx->io_dl); }));
+  rc = losses_out(ctx, b, K, loss_out, dloss_out, ctx->pending_dl);
   if (rc != MCA_OK) return rc;
   ctx->pending = true;
   ctx->pending_K = K;
@@ -1333,7 +1319,8 @@ int mca_eval_channels(mca_ctx* ctx, const mca_channel* chans_host, int32_t K, do
   const Bufs b = ctx_bufs(ctx);
   MCA_HIP(ctx, timed(ctx, 0, [&] { return prepare_in(ctx, b, K, ctx->chans, chans_host); }));
   MCA_HIP(ctx, timed(ctx, 1, [&] { return eval_all(ctx, ctx->net, K); }));
-  const int rc = losses_out(ctx, ctx->net, b, K, loss_out, dloss_out, ctx->pending_dl);
+  MCA_HIP(ctx, timed(ctx, 2, [&] { return select_into(ctx, ctx->net, b, K, false, nullptr, nullptr, ctx->io_dl); }));
+  const int rc = losses_out(ctx, b, K, loss_out, dloss_out, ctx->pending_dl);
   if (rc != MCA_OK) return rc;
   ctx->pending = true;
   ctx->pending_K = K;
@@ -1400,8 +1387,9 @@ int mca_eval_losses_noalloc(mca_ctx* ctx, const mca_cand* cands_host, int32_t K,
   // nothing is cleared; overlapping calls on one GPU would race on them
   MCA_HIP(ctx, prepare_in(ctx, b, K, b.cands, cands_host));
   MCA_HIP(ctx, eval_into(ctx, net, b, K));
+  MCA_HIP(ctx, select_into(ctx, net, b, K, false, nullptr, nullptr, ctx->io_dl));
   std::vector<double> dl;
-  return losses_out(ctx, net, b, K, loss_out, dloss_out, dl);
+  return losses_out(ctx, b, K, loss_out, dloss_out, dl);
 }
 
 int mca_set_option(mca_ctx* ctx, int32_t option, int64_t value) {
@@ -1554,7 +1542,7 @@ int mca_run_steps(mca_ctx* ctx, uint64_t n_steps, int32_t K, mca_trace* trace, m
   alignas(8) unsigned char local[kStateBlock];
   unsigned char* blk = ctx->host_blk ? ctx->host_blk : local;
   MCA_HIP(ctx, hipMemcpyAsync(blk, ctx->st, kStateBlock, hipMemcpyDeviceToHost, ctx->stream));
-  MCA_HIP(ctx, wait_stream(ctx->stream));
+  MCA_HIP(ctx, hipStreamSynchronize(ctx->stream));
   DevState after, before;
   mca::LoopSync sync;
   std::memcpy(&after, blk, sizeof after);
