@@ -107,14 +107,17 @@ __device__ __forceinline__ void load_pairs(const float* row, int np, int l, floa
     v[i] = (i < np) ? gload(reinterpret_cast<const floatx2*>(row + 32 * i + 2 * l)) : z2;
 }
 __device__ __forceinline__ float sum16(float s) {
-#pragma unroll
-  for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, 16);
+  s += dpp_f32<0xB1>(s);   // lane ^ 1
+  s += dpp_f32<0x4E>(s);   // lane ^ 2
+  s += dpp_f32<0x141>(s);  // mirror within eight
+  s += dpp_f32<0x140>(s);  // mirror within sixteen
   return s;
 }
 __device__ __forceinline__ float max16(float s) {
-#pragma unroll
-  for (int o = 8; o > 0; o >>= 1) s = fmaxf(s, __shfl_xor(s, o, 16));
-  return s;
+  s = fmaxf(s, dpp_f32<0xB1>(s));
+  s = fmaxf(s, dpp_f32<0x4E>(s));
+  s = fmaxf(s, dpp_f32<0x141>(s));
+  return fmaxf(s, dpp_f32<0x140>(s));
 }
 // mean and 1/sqrt(biased variance + eps) of a row (zeros beyond np pairs)
 template <int P>
