@@ -399,7 +399,10 @@ __global__ __launch_bounds__(kSlabThreads) void k_slab(NetDev net_arg, const mca
     }
     __syncthreads();
     const int ng = ngroup;
-    if (ng == 0) continue;
+    if (ng == 0) {
+      __syncthreads();  // every wave has read ngroup before wave 0 lists the next group
+      continue;
+    }
     // 2. the affected pairs: a nonzero input and a changed activation (an
     // evaluation scores the step's minibatch only; a commit moves every sample)
     const int64_t sub0 = subset_start(net, commit ? 0 : st->t);

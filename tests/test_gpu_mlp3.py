@@ -14,7 +14,8 @@ import torch
 from oracle import mca as omca
 from oracle.mlp import FullMLP, MLPState, per_sample_ce
 from parity_util import (REL_TOL, ParityStats, assert_cands_equal, assert_state_equal,
-                         check_batch, explicit_steps, make_pair, replay_trace)
+                         check_batch, check_step, explicit_steps, kappa_of, make_pair,
+                         replay_trace)
 from workloads import CONFIGS, mlp_workload
 
 pytestmark = pytest.mark.gpu
@@ -180,4 +181,36 @@ def test_full_ternary_workload(mca):
     replay_trace(ref, cfg, 0, ch, dl, 64, ps)
     assert_state_equal(ctx, ref)
     assert_caches_match(ctx, ref)
+    ctx.close()
+
+
+@pytest.mark.parametrize("kind", ["ternary", "deep"])
+@pytest.mark.parametrize("empty", [1, 2])
+def test_batch_with_empty_groups(mca, kind, empty):
+    """A batch of 150 candidates whose first `empty` groups of 64 hold none of
+    layer L-3: the tile kernel lists its candidates group by group and goes past
+    a group that has none."""
+    K = 150
+    if kind == "ternary":
+        cfg = CONFIGS["ternary"].scaled(name="t3_groups", widths=(784, 96, 80, 10), n_samples=333, K=K)
+    else:
+        cfg = CONFIGS["deep"].scaled(name="deep_groups", widths=(64, 256, 256, 256, 256, 10),
+                                     data="sparse_uniform", n_samples=200, K=K, delta=0.1)
+    banner(f"{cfg.name} {cfg.widths} N={cfg.n_samples} K={K} first {empty} groups empty")
+    w = mlp_workload(cfg)
+    ctx, ref = make_pair(cfg, w, k_max=K)
+    tile_layer = cfg.n_layers - 3
+    tile, other = [], []
+    for t in range(16):
+        rc = [ref.candidate(cfg.seed_stream, cfg.stream_tag, t, k, cfg.delta, cfg.layer_pick) for k in range(K)]
+        for g, c in zip(ctx.propose(t, K), rc):
+            (tile if c.layer == tile_layer else other).append((g, c))
+    n = 64 * empty
+    batch = other[:n] + tile[:K - n - 4] + other[n:n + 4 + max(0, K - n - 4 - len(tile))]
+    assert len(batch) == K and sum(c.layer == tile_layer for _, c in batch) >= 15
+    _, dl = ctx.eval_losses(np.array([g for g, _ in batch], dtype=batch[0][0].dtype))
+    ctx.rollback()
+    ps = ParityStats(f"{kind} batch of 150, {empty} empty groups")
+    exp, mags = zip(*[omca._delta(ref, c) for _, c in batch])
+    check_step(ps, dl, exp, mags, [kappa_of(cfg, c) for _, c in batch], [0.0] * K, cfg.accept_ties, -1, -1)
     ctx.close()
