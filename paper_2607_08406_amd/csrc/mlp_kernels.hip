@@ -502,14 +502,15 @@ __global__ __launch_bounds__(kTile) void k_commit_column(NetDev net_arg, const m
 // the tile sits in LDS row p + 64 b, so neighbouring columns end in one lane and
 // are stored together.  The next chunk's values are requested before the
 // products; the other block of the CU multiplies while this one splits.
-// 784 x 16384 weights on 10000 columns (257 GFLOP): 2.15 ms on fp32 matrix
-// instructions, 1.57 here, of which the six products are 0.62 at the matrix
-// cores' peak; splitting (700 vector cycles a chunk beside 1536) and LDS
+// 784 x 16384 weights on 10000 columns (257 GFLOP): 2.11 ms on fp32 matrix
+// instructions, 1.65 here, of which the six products are 0.62 at the matrix
+// cores' peak; splitting (700 vector cycles a chunk beside 1536), add_product's
+// two additions a value (1.61 with one, and fields off to one side) and LDS
 // traffic (1150) overlap them in part.  (Three blocks a CU fit only without
-// add_product's sums: 1.42 ms, at 1.6 times the fp32 error.)  1024 x 1024 on
-// 8192 columns: 153 -> 110 us.  What
-// lies beyond M and the columns is clamped on load and dropped on store, what
-// lies beyond Kd is zero in both operands.
+// add_product's sums: 1.42 ms, at 1.6 times the fp32 error.)  1024 x 1024 with
+// tanh inputs on 8192 columns: 202 -> 170 us.  What lies beyond M and the
+// columns is clamped on load and dropped on store, what lies beyond Kd is zero
+// in both operands.
 constexpr int kFwdT = 128;       // columns of the block's tile
 constexpr int kFwdK = 32;        // reduction chunk
 constexpr int kFwdThreads = 256;

@@ -104,22 +104,35 @@ __device__ __forceinline__ void multiply_parts(const bf16x8 (&a)[SB][3], const b
         acc[sb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[sb][pa[t]], b[cb][pb[t]], acc[sb][cb], 0, 0, 0);
 }
 
-// acc[cb] += a b over one step with the six products summed from zero, so that
-// the running sum is rounded once per 32 k and not six times.  For long sums of
-// sparse inputs, where the chain on the running sum loses more than fp32
-// instructions, which skip the zeros' roundings (error over sum |w| |x|, 784
-// image inputs, 19 % of them lit: 2.4e-8 on fp32 instructions, 3.8e-8 with
-// multiply_parts, 1.2e-8 here; 1024 dense inputs: 2.4e-8, 2.0e-8, 0.5e-8).
+// acc[cb] += a b over one step, the product of the leading parts and the five
+// smaller ones summed apart, each from zero, so that the running sum is rounded
+// twice per 32 k and not six times.  For long sums of sparse inputs, where the
+// chain on the running sum loses more than fp32 instructions, which skip the
+// zeros' roundings (error over sum |w| |x|, 784 image inputs, 19 % of them lit:
+// 2.3e-8 on fp32 instructions, 3.8e-8 with multiply_parts, 0.8e-8 here; 1024
+// dense inputs: 2.6e-8, 2.0e-8, 0.7e-8).  Apart, because the instruction cuts an
+// addend far below its products off towards minus infinity: with the small sum as
+// the addend of the leading product every field came out low, by 3e-8 to 5e-8 of
+// the mean |z| (apart: below 4e-10), which no average over samples removes (loss
+// changes of 784-1024x3-10 ReLU channels: 1.5e-7 off 64 bits, 3.5e-8 apart).
 template <int CB>
 __device__ __forceinline__ void add_product(const bf16x8 (&a)[3], const bf16x8 (&b)[CB][3], f32x4 (&acc)[CB]) {
-  f32x4 t[1][CB];
+  constexpr int pa[5] = {2, 0, 1, 1, 0}, pb[5] = {0, 2, 1, 0, 1};
+  f32x4 lead[CB], rest[CB];
 #pragma unroll
-  for (int cb = 0; cb < CB; ++cb) t[0][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-  multiply_parts<1, CB>(reinterpret_cast<const bf16x8(&)[1][3]>(a), b, t);
+  for (int cb = 0; cb < CB; ++cb) {
+    rest[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    lead[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[cb][0], rest[cb], 0, 0, 0);
+  }
+#pragma unroll
+  for (int t = 0; t < 5; ++t)
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+      rest[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[pa[t]], b[cb][pb[t]], rest[cb], 0, 0, 0);
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) acc[cb][v] += t[0][cb][v];
+    for (int v = 0; v < 4; ++v) acc[cb][v] += lead[cb][v] + rest[cb][v];
 }
 
 // acc += rows 16 sb + li of the tile (part p of row r at tile + (p * T + r) *

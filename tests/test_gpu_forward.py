@@ -48,3 +48,34 @@ def test_forward_edges(widths, N, act):
         assert got.shape == (N,) and ratio.max() <= 1, (again, ratio.max(), int(ratio.argmax()))
         ctx.refresh()
     ctx.close()
+
+
+@pytest.mark.parametrize("widths,lit", [((784, 64, 2), 0.2), ((101, 257, 2), 1.0), ((64, 256, 256, 2), 0.5)])
+def test_forward_rounds_to_neither_side(widths, lit):
+    """The fields' errors have mean zero: a sample's loss is the sum of its last
+    hidden units (ReLU; near 30, where the other class's share is below an ulp),
+    so its error adds up theirs.  Over 20000 samples the mean of rounding errors
+    stays within a few of its standard errors (their deviation over
+    sqrt(20000)); 10 is allowed, and sums rounded towards one side were off by
+    60 and more."""
+    from paper_2607_08406_amd import mca
+
+    N, H = 20000, widths[-2]
+    rng = np.random.default_rng(sum(widths))
+    X = (rng.random((N, widths[0])) * (rng.random((N, widths[0])) < lit)).astype(np.float32)
+    W = [((rng.random((m, n)) * 2 - 1) * np.sqrt(3.0 / n)).astype(np.float32)
+         for n, m in zip(widths[:-2], widths[1:-1])]
+    a = X.astype(np.float64)
+    for w in W:
+        a = np.maximum(a @ w.astype(np.float64).T, 0.0)
+    top = np.zeros((2, H), np.float32)
+    top[0] = np.float32(2.0 ** np.ceil(np.log2(30.0 / a.sum(1).min())))
+    loss = a.sum(1) * float(top[0, 0])
+    assert loss.min() >= 30.0
+    ctx = mca.Context(mca.mlp_desc(list(widths), "relu", delta=0.1, seed=1, stream_tag=1), W + [top], X,
+                      np.ones(N, np.int32), k_max=1)
+    err = (ctx.sample_losses() - loss) / loss
+    off = err.mean() / (err.std() / np.sqrt(N))
+    print(f"[gpu] {widths} mean {err.mean():.2e} deviation {err.std():.2e}: {off:+.1f} standard errors", flush=True)
+    assert abs(off) <= 10
+    ctx.close()
