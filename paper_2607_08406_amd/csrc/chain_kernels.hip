@@ -213,7 +213,7 @@ __global__ __launch_bounds__(kChainThreads, T == kCommitT ? 1 : 2) void k_chain(
       }
     }
   };
-  // dA_m = phi(z_m + dz) - phi(z_m) into the tile's parts; a commit stores
+  // dA_m = phi(z_m + dz) - phi(z_m), times kPartScale, into the tile's parts; a commit stores
   // z_m + dz
   auto finish = [&](int m, const f32x4 (&dz)[SB][4], const f32x4 (&zc)[SB][4]) {
     float* Zm = net.Z[m];
@@ -228,7 +228,8 @@ __global__ __launch_bounds__(kChainThreads, T == kCommitT ? 1 : 2) void k_chain(
           if (commit && nrow[sb][v] >= 0)
             gstore(&Zm[(int64_t)(64 * wave + 16 * cb + li) * Ns + nrow[sb][v]], zc[sb][cb][v] + dz[sb][cb][v]);
         }
-        const Split2 s0 = split2(d[0], d[1]), s1 = split2(d[2], d[3]);
+        const Split2 s0 = split2(d[0] * kPartScale, d[1] * kPartScale);
+        const Split2 s1 = split2(d[2] * kPartScale, d[3] * kPartScale);
         uint16_t* at = ta + (16 * sb + 4 * q + v) * RS + 64 * wave + 4 * li;
 #pragma unroll
         for (int p = 0; p < 3; ++p)
@@ -273,6 +274,10 @@ __global__ __launch_bounds__(kChainThreads, T == kCommitT ? 1 : 2) void k_chain(
       split_product_ahead<W, T, RS>(ta, weights(m < L - 2 ? m + 1 : m), held, lane, acc);
     else
       split_product<W, T, RS>(ta, weights(m), lane, acc);
+#pragma unroll
+    for (int sb = 0; sb < SB; ++sb)
+#pragma unroll
+      for (int cb = 0; cb < 4; ++cb) acc[sb][cb] *= kPartUnscale;
     __syncthreads();
     finish(m, acc, zc);
     __syncthreads();
@@ -305,7 +310,7 @@ __global__ __launch_bounds__(kChainThreads, T == kCommitT ? 1 : 2) void k_chain(
 #pragma unroll
     for (int sb = 0; sb < SB; ++sb)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) logit[wave][16 * sb + 4 * q + v][li] = lg[sb][v];
+      for (int v = 0; v < 4; ++v) logit[wave][16 * sb + 4 * q + v][li] = lg[sb][v] * kPartUnscale;
   }
   __syncthreads();
   // 5. per-sample loss change from the logit change and the cached softmax;

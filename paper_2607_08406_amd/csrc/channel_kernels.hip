@@ -403,6 +403,7 @@ __global__ __launch_bounds__((Dense<W, commit>::threads), (Dense<W, commit>::blo
             for (int cb = 0; cb < 4; ++cb) acc[h][sb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
       if constexpr (D::kF32) t.fields(net.Z[m], Ns, zc);
+      if (m > m0) t.unscale(acc);
       // the rank-1 term of the rows whose changed unit enters here, and the path
       // weight's own change
 #pragma unroll

@@ -81,7 +81,7 @@ struct Dense {
           for (int v = 0; v < 4; ++v)
             if (nrow[sb][v] >= 0) gstore(&Z[(int64_t)unit(h, cb) * Ns + nrow[sb][v]], z[h][sb][cb][v] + dz[h][sb][cb][v]);
   }
-  // The changes d into the tile.
+  // The changes d into the tile, times kPartScale.
   __device__ __forceinline__ void write_tile(Tile& tile, const Acc& d) const {
 #pragma unroll
     for (int h = 0; h < H; ++h)
@@ -90,18 +90,30 @@ struct Dense {
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const int at = (16 * sb + 4 * q + v) * RS + 64 * (H * wave + h) + 4 * li;
+          float x[4];
+#pragma unroll
+          for (int cb = 0; cb < 4; ++cb) x[cb] = d[h][sb][cb][v] * kPartScale;
           if constexpr (kF32) {
             *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(tile) + at) =
-                f32x4{d[h][sb][0][v], d[h][sb][1][v], d[h][sb][2][v], d[h][sb][3][v]};
+                f32x4{x[0], x[1], x[2], x[3]};
           } else {
-            const Split2 s0 = split2(d[h][sb][0][v], d[h][sb][1][v]), s1 = split2(d[h][sb][2][v], d[h][sb][3][v]);
+            const Split2 s0 = split2(x[0], x[1]), s1 = split2(x[2], x[3]);
 #pragma unroll
             for (int p = 0; p < 3; ++p)
               *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(tile) + at + p * T * RS) = make_uint2(s0.p[p], s1.p[p]);
           }
         }
   }
-  // acc = tile x the split weights of dense layer m.
+  // The product's sums as they are (after the loads that follow it are on their way).
+  __device__ __forceinline__ void unscale(Acc& acc) const {
+#pragma unroll
+    for (int h = 0; h < H; ++h)
+#pragma unroll
+      for (int sb = 0; sb < SB; ++sb)
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) acc[h][sb][cb] *= kPartUnscale;
+  }
+  // acc = tile x the split weights of dense layer m, times kPartScale.
   __device__ __forceinline__ void product(const NetDev& net, int m, const Tile& tile, Acc& acc) const {
 #pragma unroll
     for (int h = 0; h < H; ++h)
@@ -149,6 +161,8 @@ struct Dense {
         multiply_step<T, RS>(reinterpret_cast<const uint16_t*>(tile), lane, ks, b, lg);
       }
     }
+#pragma unroll
+    for (int sb = 0; sb < SB; ++sb) lg[sb][0] *= kPartUnscale;
   }
 };
 

@@ -523,6 +523,7 @@ __global__ __launch_bounds__(kFwdThreads, SB == 4 ? 2 : 3) void k_gemm_fwd_split
     const float* __restrict__ bmu, const float* __restrict__ bS,
     const float* __restrict__ bias) {
   constexpr int TM = 32 * SB;
+  constexpr bool kScaled = ACT == MCA_ACT_TANH || ACT == MCA_ACT_GAUSS;  // inputs of at most 1 (kPartScale)
   __shared__ __attribute__((aligned(16))) uint16_t As[3][TM][kFwdK];
   __shared__ __attribute__((aligned(16))) uint16_t Bs[3][kFwdT][kFwdK];
   const int64_t m0 = (int64_t)blockIdx.y * TM, n0 = (int64_t)blockIdx.x * kFwdT;
@@ -587,6 +588,7 @@ __global__ __launch_bounds__(kFwdThreads, SB == 4 ? 2 : 3) void k_gemm_fwd_split
         x[e] = rb[e][t];
         if (bmu != nullptr) x[e] = (x[e] - nmu[t]) * nrs[t];
         if (ACT >= 0) x[e] = act_fn(x[e], ACT, gamma);
+        if (kScaled) x[e] *= kPartScale;
         if (tail) x[e] = k0 + bk + e < Kd ? x[e] : 0.f;
       }
       const Split2 s[4] = {split2(x[0], x[1]), split2(x[2], x[3]), split2(x[4], x[5]), split2(x[6], x[7])};
@@ -637,6 +639,7 @@ __global__ __launch_bounds__(kFwdThreads, SB == 4 ? 2 : 3) void k_gemm_fwd_split
       for (int c = 0; c < 2; ++c) {
         const int64_t n = n0 + 64 * wc + 32 * c + 2 * li;
         f32x2 z = {acc[sb][2 * c][v], acc[sb][2 * c + 1][v]};
+        if (kScaled) z *= kPartUnscale;
         if (bias != nullptr) z = f32x2{z[0] + b, z[1] + b};
         float* at = Cm + m * ldc + n;
         if (n + 1 < ncols) gstore(reinterpret_cast<f32x2*>(at), z);

@@ -292,6 +292,7 @@ __global__ __launch_bounds__((Dense<W, commit>::threads), (Dense<W, commit>::blo
         if constexpr (!D::kF32) t.fields(net.Z[m], Ns, zc);
         t.product(net, m, ta, acc);
         if constexpr (D::kF32) t.fields(net.Z[m], Ns, zc);
+        t.unscale(acc);
         finish(m, true);
       }
       // 3. the logits: the last hidden layer's change through W_{L-1}

@@ -7,7 +7,17 @@
 // below 2^-26 of a term, under the rounding of the fp32 sums, which stay in
 // fp32.  v_mfma_f32_16x16x32_bf16 takes 16 cycles for the 32 k that
 // v_mfma_f32_16x16x4f32 takes 256 for, so six of them take 96: 2.7 times the
-// fp32 rate.  Operands below 2^-110 lose their lowest part to bf16's range.
+// fp32 rate.
+//
+// The matrix cores take bf16 values below 2^-126 as zero, so a value below 2^-103
+// would lose its lowest bits.  Activation changes, which keep their relative
+// accuracy down to where fp32 ends (a change can be all there is to a loss
+// difference), and hidden activations of at most 1 (tanh, Gaussian) are therefore
+// split times 2^24, which brings the last bit of the smallest fp32 value to 2^-125,
+// and their products' sums taken times 2^-24, both exact.  Changes of 2^104 and
+// more overflow that way, far past the logit change of 88 at which a sample's loss
+// change is lost anyway.  Weights, inputs and ReLU activations are split as they
+// are.
 //
 // Hidden-layer weights are kept split beside their fp32 values (NetDev::WF), in
 // the order the kernels read them: for each block of 16 output units and each
@@ -29,6 +39,8 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr float kPartScale = 0x1p24f, kPartUnscale = 0x1p-24f;
 
 // The parts of two fp32 values, each part a packed pair (a in the low half).
 struct Split2 {

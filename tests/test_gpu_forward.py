@@ -79,3 +79,39 @@ def test_forward_rounds_to_neither_side(widths, lit):
     print(f"[gpu] {widths} mean {err.mean():.2e} deviation {err.std():.2e}: {off:+.1f} standard errors", flush=True)
     assert abs(off) <= 10
     ctx.close()
+
+
+@pytest.mark.parametrize("N,H", [(300, 64), (70, 200)])
+def test_forward_of_tiny_activations(N, H):
+    """Gaussian units far out (exp(-z^2) near 2^-123) under weights of 2^118: the
+    next layer's fields are of ordinary size.  Relative error of an activation:
+    its exponent, about 85, in fp32 (z, z^2 and its product with log2 e each
+    rounded, 4 x 2^-24 of it), 2e-5; split as they are, such values have 10 bits."""
+    from paper_2607_08406_amd import mca
+
+    rng = np.random.default_rng(N)
+    X = np.full((N, 4), 1.0, np.float32)
+    X[:, 1:] = rng.random((N, 3))
+    W0 = np.zeros((H, 4), np.float32)
+    W0[:, 0] = 9.16
+    W0[:, 1:] = rng.random((H, 3)) * 0.05
+    W1 = ((rng.random((20, H)) * 2 - 1) * 2.0 ** 118).astype(np.float32)
+    W2 = (rng.random((3, 20)) * 2 - 1).astype(np.float32)
+    y = rng.integers(0, 3, N).astype(np.int32)
+    ctx = mca.Context(mca.mlp_desc([4, H, 20, 3], "gauss", delta=0.1, seed=1, stream_tag=1), [W0, W1, W2], X, y, k_max=1)
+    a = X.astype(np.float64)
+    z0 = a @ W0.astype(np.float64).T
+    h = np.exp(-z0 * z0)
+    err = h * 4 * 2.0 ** -24 * z0 * z0 @ np.abs(W1.astype(np.float64)).T
+    z1 = h @ W1.astype(np.float64).T
+    a1 = np.exp(-z1 * z1)
+    z2 = a1 @ W2.astype(np.float64).T
+    loss = np.log(np.exp(z2).sum(1)) - z2[np.arange(N), y]
+    # |d exp(-z^2)| <= 0.86 |dz|, the logits' error through |W2|, twice it on the loss
+    tol = 2 * ((0.86 * err + 2.0 ** -20) @ np.abs(W2.astype(np.float64)).T).max(1)
+    got = ctx.sample_losses()
+    assert 0.05 < np.abs(z1).mean() < 20 and (h < 2.0 ** -121).mean() > 0.9 and h.min() > 2.0 ** -126
+    ratio = np.abs(got - loss) / tol
+    print(f"[gpu] worst error over its bound {ratio.max():.3f}", flush=True)
+    assert ratio.max() <= 1
+    ctx.close()

@@ -7,7 +7,8 @@ import numpy as np
 import pytest
 import torch
 
-from parity_util import ParityStats, assert_state_equal, make_pair, replay_trace
+from parity_util import (ParityStats, _oracle_step, assert_state_equal, make_pair,
+                         replay_trace)
 from workloads import CONFIGS, mlp_workload
 
 pytestmark = pytest.mark.gpu
@@ -37,4 +38,37 @@ def test_chain_tiles(act, N):
     ctx.rollback()
     # (the caches are recomputed: fields differ in their last bits)
     np.testing.assert_allclose(before, after, rtol=1e-3, atol=1e-9)
+    ctx.close()
+
+
+@pytest.mark.parametrize("base,net", [
+    ("deep", dict(widths=(64, 256, 256, 256, 256, 10))),
+    ("deep", dict(widths=(64, 512, 512, 512, 512, 10))),
+    ("deep", dict(widths=(64, 1024, 1024, 1024, 10))),
+    ("deepln", dict(widths=(64, 256, 256, 256, 10), layer_norm=False, layer_pick="layer")),
+], ids=["chain", "wide512", "wide1024", "bias"])
+def test_changes_near_the_end_of_fp32(base, net):
+    """First-layer mutations through a second layer with weights of 2^-115: the
+    activation changes that the dense layers take on are of about 2^-122 and keep
+    their relative accuracy.  The errors' rms stays below 2^-24 of the rms size of
+    the changes' first-order terms (each is an average over the samples' roundings:
+    4e-9 to 5e-9 is seen, and 2e-6 to 1e-5 from values split as they are)."""
+    cfg = CONFIGS[base].scaled(name=f"tiny_{base}_{net['widths'][1]}", act="tanh", data="sparse_uniform",
+                               n_samples=150, K=24, delta=0.1, seed_stream=5200, **net)
+    print(f"[gpu] {cfg.name} {cfg.widths}", flush=True)
+    w = mlp_workload(cfg)
+    w["weights"][1] = w["weights"][1] * np.float32(2.0 ** -111)
+    ctx, ref = make_pair(cfg, w, k_max=24)
+    err, size = [], []
+    for t in range(6):
+        _, rc, dls, mags, _, _, _ = _oracle_step(ref, cfg, t, 24, 0.0, 0.0, 0)
+        _, dl = ctx.eval_losses(ctx.propose(t, 24))
+        ctx.rollback()
+        first = [k for k in range(24) if rc[k].layer == 0]
+        err += [dl[k] - dls[k] for k in first]
+        size += [mags[k] for k in first]
+    assert len(err) >= 15 and max(size) < 1e-35
+    ratio = np.sqrt(np.sum(np.square(np.array(err) * 1e38)) / np.sum(np.square(np.array(size) * 1e38)))
+    print(f"[gpu] rms error over rms size {ratio:.2e}", flush=True)
+    assert ratio <= 2.0 ** -24
     ctx.close()
