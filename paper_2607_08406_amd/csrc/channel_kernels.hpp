@@ -13,10 +13,11 @@ inline bool channel_width_ok(int w) { return w == 256 || w == 512 || w == 1024; 
 int channel_segments(int64_t n_samples);
 int channel_tiles(int64_t n_samples, int w);
 
-// The samples whose change goes past the path's units, per channel (k_max * N
-// each): the sample, the changed activation and the path unit's new one, and the
-// layer the change enters; the lists' lengths (two per channel and segment of the
-// samples) and the first tile of each (one more).
+// The samples whose change goes past the path's units, per channel of
+// list_group(), or of the largest batch (N entries each): the sample, the changed
+// activation and the path unit's new one, and the layer the change enters; the
+// lists' lengths (two per channel and segment of the samples) and the first tile of
+// each (one more).
 struct ChannelLists {
   int* rows;
   float* d;

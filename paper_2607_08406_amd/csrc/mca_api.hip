@@ -87,12 +87,11 @@ struct Layout {
   size_t tr_chosen = 0, tr_dl = 0, loop_partials = 0, loop_sync = 0, loop_dls = 0;
   size_t wt = 0, pslab = 0;  // three-layer nets: W_1 transposed, first-layer tile sums
   size_t cols = 0, nnz = 0;  // nonzero entries of layer L-3 candidates' W_{L-2} columns
-  size_t rows = 0, rda = 0, rcnt = 0, pchain = 0;  // deep nets: affected samples, tile sums
+  size_t rows = 0, rda = 0, rcnt = 0, pchain = 0;  // lists of the samples a candidate moves; deep nets' tile sums
   size_t wf = 0;                                    // split copy of the dense layers' weights
   size_t cap = 0, cf = 0, cfirst = 0;               // channel mutations: the listed samples' path units
   size_t chans = 0, pchan = 0;                      // channel mutations: records, tile sums
   size_t pnorm = 0;                                 // nets with biases / normalization: tile sums
-  size_t aug[MCA_MAX_LAYERS] = {};  // the augmented matrices as the host has them
   size_t b[MCA_MAX_LAYERS] = {}, mu[MCA_MAX_LAYERS] = {}, S[MCA_MAX_LAYERS] = {};
   int nchain = 0, nchan = 0, nnorm = 0;
   int nslab = 0;
@@ -348,13 +347,11 @@ Layout make_layout(const mca_net_desc* net, int64_t N, int32_t k_max) {
   };
   const int L = net->n_layers;
   const bool norm = dense_path(net);
+  const size_t k_list = (size_t)std::min<int32_t>(k_max, mca::list_group(N));
   lo.xt = take((size_t)net->widths[0] * lo.Ns * sizeof(float));
   for (int l = 0; l < L; ++l) lo.w[l] = take((size_t)net->widths[l + 1] * net->widths[l] * sizeof(float));
   if (net->biases)
-    for (int l = 0; l < L; ++l) {
-      lo.b[l] = take((size_t)net->widths[l + 1] * sizeof(float));
-      lo.aug[l] = take((size_t)net->widths[l + 1] * (net->widths[l] + 1) * sizeof(float));
-    }
+    for (int l = 0; l < L; ++l) lo.b[l] = take((size_t)net->widths[l + 1] * sizeof(float));
   if (net->layer_norm)
     for (int l = 0; l + 1 < L; ++l) {
       lo.mu[l] = take(lo.Ns * sizeof(float));
@@ -396,20 +393,25 @@ Layout make_layout(const mca_net_desc* net, int64_t N, int32_t k_max) {
   if (norm) {
     lo.nnorm = mca::norm_tiles(N, net->widths[1]);
     lo.pnorm = take((size_t)k_max * lo.nnorm * sizeof(float));
-    lo.rows = take((size_t)k_max * N * sizeof(int32_t));
-    lo.rda = take((size_t)k_max * N * sizeof(float));
-    lo.rcnt = take((size_t)2 * k_max * sizeof(int32_t));
+    // the lists, and between steps one layer's augmented matrix on its way to or
+    // from the host (biased nets)
+    size_t aug = 0;
+    for (int l = 0; net->biases && l < L; ++l)
+      aug = std::max(aug, (size_t)net->widths[l + 1] * (net->widths[l] + 1) * sizeof(float));
+    lo.rows = take(std::max(k_list * N * sizeof(int32_t), aug));
+    lo.rda = take(k_list * N * sizeof(float));
+    lo.rcnt = take(2 * k_list * sizeof(int32_t));
     lo.wf = take((size_t)mca::split_size(net->widths[1], L) * sizeof(uint16_t));
   }
   if (net->mutation != MCA_MUTATE_SINGLE) {
     lo.nchan = mca::channel_tiles(N, net->widths[1]);
     lo.chans = take((size_t)k_max * sizeof(mca_channel));
     lo.pchan = take((size_t)k_max * lo.nchan * sizeof(float));
-    lo.rows = take((size_t)k_max * N * sizeof(int32_t));
-    lo.rda = take((size_t)k_max * N * sizeof(float));
-    lo.cap = take((size_t)k_max * N * sizeof(float));
-    lo.cf = take((size_t)k_max * N * sizeof(int32_t));
-    const size_t lists = (size_t)2 * k_max * mca::channel_segments(N);
+    lo.rows = take(k_list * N * sizeof(int32_t));
+    lo.rda = take(k_list * N * sizeof(float));
+    lo.cap = take(k_list * N * sizeof(float));
+    lo.cf = take(k_list * N * sizeof(int32_t));
+    const size_t lists = 2 * k_list * mca::channel_segments(N);
     lo.rcnt = take(lists * sizeof(int32_t));
     lo.cfirst = take((lists + 1) * sizeof(int32_t));
     lo.wf = take((size_t)mca::split_size(net->widths[1], L) * sizeof(uint16_t));
@@ -462,7 +464,8 @@ struct mca_ctx {
   bool norm = false;             // biases and / or normalized hidden fields (Sec. 2.1)
   mca::NormDev nd{};             // normalization statistics
   float* pnorm = nullptr;        // tile sums of the dense evaluation
-  float* aug[MCA_MAX_LAYERS] = {};  // biased nets: the augmented matrices on their way to or from the host
+  float* aug = nullptr;          // biased nets: a layer's augmented matrix on its way to or from the host,
+                                 // in the lists' place (a commit makes its own list)
   double* dl = nullptr;
   double* bsum = nullptr;
   DevState* st = nullptr;
@@ -656,8 +659,8 @@ int upload_params(mca_ctx* ctx, const float* const* params, const int8_t* const*
     const size_t n = (size_t)d.widths[l + 1] * d.widths[l];
     if (d.biases) {  // the augmented matrix [n_{l+1}][n_l + 1]: weights, then the bias column
       const size_t all = (size_t)d.widths[l + 1] * (d.widths[l] + 1);
-      MCA_HIP(ctx, hipMemcpyAsync(ctx->aug[l], params[l], all * sizeof(float), hipMemcpyHostToDevice, ctx->stream));
-      MCA_HIP(ctx, mca::launch_augment(ctx->aug[l], ctx->net.W[l], ctx->net.B[l], d.widths[l + 1], d.widths[l],
+      MCA_HIP(ctx, hipMemcpyAsync(ctx->aug, params[l], all * sizeof(float), hipMemcpyHostToDevice, ctx->stream));
+      MCA_HIP(ctx, mca::launch_augment(ctx->aug, ctx->net.W[l], ctx->net.B[l], d.widths[l + 1], d.widths[l],
                                        true, ctx->stream));
       continue;
     }
@@ -1157,7 +1160,6 @@ int mca_init(mca_ctx** out, const mca_net_desc* net, const float* const* params,
     nd.offs[l] = off;
     off += (int64_t)net->widths[l + 1] * (net->widths[l] + net->biases);
     nd.B[l] = net->biases ? (float*)(ws + lo.b[l]) : nullptr;
-    ctx->aug[l] = net->biases ? (float*)(ws + lo.aug[l]) : nullptr;
     nd.scales[l] = net->scales[l];
     nd.W[l] = (float*)(ws + lo.w[l]);
     nd.codes[l] = nd.ternary ? (int8_t*)(ws + lo.codes[l]) : nullptr;
@@ -1188,6 +1190,7 @@ int mca_init(mca_ctx** out, const mca_net_desc* net, const float* const* params,
   const bool listed = deep || ctx->norm || ctx->chan;  // kernels that list the samples a candidate moves
   nd.WF = listed ? (uint16_t*)(ws + lo.wf) : nullptr;
   ctx->rows = listed ? (int*)(ws + lo.rows) : nullptr;
+  ctx->aug = net->biases ? (float*)(ws + lo.rows) : nullptr;
   ctx->rda = listed ? (float*)(ws + lo.rda) : nullptr;
   ctx->rcnt = listed ? (int*)(ws + lo.rcnt) : nullptr;
   ctx->pchain = deep ? (float*)(ws + lo.pchain) : nullptr;
@@ -1599,9 +1602,9 @@ int mca_get_params(mca_ctx* ctx, float* const* params_out, int8_t* const* codes_
     if (params_out[l] == nullptr) return fail(ctx, MCA_EINVAL, "a params_out pointer is NULL");
     if (d.biases) {
       const size_t all = (size_t)d.widths[l + 1] * (d.widths[l] + 1);
-      MCA_HIP(ctx, mca::launch_augment(ctx->aug[l], ctx->net.W[l], ctx->net.B[l], d.widths[l + 1], d.widths[l],
+      MCA_HIP(ctx, mca::launch_augment(ctx->aug, ctx->net.W[l], ctx->net.B[l], d.widths[l + 1], d.widths[l],
                                        false, ctx->stream));
-      MCA_HIP(ctx, hipMemcpyAsync(params_out[l], ctx->aug[l], all * sizeof(float), hipMemcpyDeviceToHost, ctx->stream));
+      MCA_HIP(ctx, hipMemcpyAsync(params_out[l], ctx->aug, all * sizeof(float), hipMemcpyDeviceToHost, ctx->stream));
       continue;
     }
     MCA_HIP(ctx, hipMemcpyAsync(params_out[l], ctx->net.W[l], n * sizeof(float), hipMemcpyDeviceToHost, ctx->stream));

@@ -20,6 +20,7 @@
 // normalization starts at layer l+1, with the rank-1 term of the one moved
 // unit.  The commit runs the same arithmetic, stores the moved fields and
 // recomputes each moved sample's statistics from them.
+#include <algorithm>
 #include <type_traits>
 
 #include "dense_tile.hpp"
@@ -57,6 +58,7 @@ __global__ __launch_bounds__(kListThreads) void k_norm_rows(NetDev net_arg, Norm
   const bool commit = k_mode != -2;
   const int k = commit ? ((k_mode >= 0) ? k_mode : st->chosen) : (int)blockIdx.x;
   if (k < 0) return;
+  const int slot = commit ? 0 : k;  // a commit's list is the first
   const mca_cand c = cands[k];
   const int L = net.L, l = c.layer;
   if (!commit && threadIdx.x < 64) {
@@ -64,7 +66,7 @@ __global__ __launch_bounds__(kListThreads) void k_norm_rows(NetDev net_arg, Norm
     if (threadIdx.x == 0) cnt[K + r] = k;
   }
   if (!commit && !aux[k].valid) {  // rejected unevaluated: selection gives +inf
-    if (threadIdx.x == 0) cnt[k] = 0;
+    if (threadIdx.x == 0) cnt[slot] = 0;
     return;
   }
   const float de = aux[k].de;
@@ -73,7 +75,7 @@ __global__ __launch_bounds__(kListThreads) void k_norm_rows(NetDev net_arg, Norm
   const bool unit = !net.ln && l < L - 1;  // lists the unit's activation change
   float* zrow = net.Z[l] + (int64_t)c.j * Ns;
   const int64_t sub0 = subset_start(net, commit ? 0 : st->t);
-  const int n_rows = list_rows(N, rows + (int64_t)k * N, vals + (int64_t)k * N, [&](int64_t n, bool in) {
+  const int n_rows = list_rows(N, rows + (int64_t)slot * N, vals + (int64_t)slot * N, [&](int64_t n, bool in) {
     const float x = is_bias ? 1.0f
                             : (l == 0 ? gload(&net.XT[(int64_t)c.i * Ns + n]) : hidden_act(net, nd, l - 1, c.i, n));
     float v = de * x;
@@ -85,7 +87,7 @@ __global__ __launch_bounds__(kListThreads) void k_norm_rows(NetDev net_arg, Norm
     return (commit || in_subset(net, sub0, n)) ? v : 0.f;
   });
   if (threadIdx.x == 0) {
-    cnt[k] = n_rows;
+    cnt[slot] = n_rows;
     if (commit) {
       const float w = aux[k].w_new;
       if (is_bias) gstore(&net.B[l][c.j], w);
@@ -118,7 +120,8 @@ __global__ __launch_bounds__((Dense<W, commit>::threads), (Dense<W, commit>::blo
   const int tid = threadIdx.x;
   const int k = commit ? ((k_mode >= 0) ? k_mode : st->chosen) : cnt[K + (int)blockIdx.y];
   if (k < 0) return;
-  const int tile = blockIdx.x, n_rows = cnt[k], e0 = tile * T;
+  const int slot = commit ? 0 : k;
+  const int tile = blockIdx.x, n_rows = cnt[slot], e0 = tile * T;
   if (e0 >= n_rows) {
     if (!commit && tid == 0) partial[(int64_t)k * ntiles + tile] = 0.f;
     return;
@@ -129,8 +132,8 @@ __global__ __launch_bounds__((Dense<W, commit>::threads), (Dense<W, commit>::blo
   const int64_t N = net.N, Ns = net.Ns;
   if (tid < T) {
     const int e = e0 + tid;
-    rown[tid] = (e < n_rows) ? gload(&rows[(int64_t)k * N + e]) : -1;
-    rowv[tid] = (e < n_rows) ? gload(&vals[(int64_t)k * N + e]) : 0.f;
+    rown[tid] = (e < n_rows) ? gload(&rows[(int64_t)slot * N + e]) : -1;
+    rowv[tid] = (e < n_rows) ? gload(&vals[(int64_t)slot * N + e]) : 0.f;
   }
   __syncthreads();
   D t;
@@ -141,7 +144,7 @@ __global__ __launch_bounds__((Dense<W, commit>::threads), (Dense<W, commit>::blo
   } else {
     typename D::Acc acc, zc;
     // sum of x over the units of each of this lane's rows
-    int slot = 0;
+    int buf = 0;
     auto row_sums = [&](auto&& x, float (&out)[SB][4]) {
 #pragma unroll
       for (int sb = 0; sb < SB; ++sb)
@@ -153,18 +156,18 @@ __global__ __launch_bounds__((Dense<W, commit>::threads), (Dense<W, commit>::blo
 #pragma unroll
             for (int cb = 0; cb < 4; ++cb) s += x(h, sb, cb, v);
           s = lanes16_sum(s);
-          if (t.li == 0) red[slot][t.wave][16 * sb + 4 * t.q + v] = s;
+          if (t.li == 0) red[buf][t.wave][16 * sb + 4 * t.q + v] = s;
         }
       __syncthreads();
 #pragma unroll
       for (int sb = 0; sb < SB; ++sb) {
-        f32x4 s = *reinterpret_cast<const f32x4*>(&red[slot][0][16 * sb + 4 * t.q]);
+        f32x4 s = *reinterpret_cast<const f32x4*>(&red[buf][0][16 * sb + 4 * t.q]);
 #pragma unroll
-        for (int w = 1; w < NW; ++w) s += *reinterpret_cast<const f32x4*>(&red[slot][w][16 * sb + 4 * t.q]);
+        for (int w = 1; w < NW; ++w) s += *reinterpret_cast<const f32x4*>(&red[buf][w][16 * sb + 4 * t.q]);
 #pragma unroll
         for (int v = 0; v < 4; ++v) out[sb][v] = s[v];
       }
-      slot ^= 1;  // the other buffer next: no wave still reads it two sums later
+      buf ^= 1;  // the other buffer next: no wave still reads it two sums later
     };
     // the layer's changes from its field's change acc, into the tile; `read`:
     // other waves may still read the tile
@@ -412,6 +415,15 @@ hipError_t launch_norm(const NetDev& net, const NormDev& nd, const mca_cand* can
                        const Aux* aux, int K, int* rows, float* vals, int* cnt, float* partial,
                        int ntiles, int k_mode, DevState* st, const double* dL, hipStream_t s) {
   const bool commit = k_mode != -2;
+  const int group = list_group(net.N);
+  if (!commit && K > group) {  // the lists hold `group` candidates: one group after the other
+    for (int g = 0; g < K; g += group) {
+      const hipError_t e = launch_norm(net, nd, cands + g, aux + g, std::min(K - g, group), rows, vals, cnt,
+                                       partial + (int64_t)g * ntiles, ntiles, k_mode, st, dL, s);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
   hipLaunchKernelGGL(k_norm_rows, dim3(commit ? 1 : K), dim3(kListThreads), 0, s, net, nd, cands, aux,
                      k_mode, st, dL, rows, vals, cnt, K);
   hipError_t e = hipGetLastError();

@@ -27,8 +27,8 @@ hipError_t launch_augment(float* aug, float* W, float* B, int rows, int n, bool 
 // k_mode -2: partial[k * ntiles + tile] for every candidate k < K; -1: commit
 // st->chosen (nothing when -1); >= 0: commit that candidate.  A commit moves
 // every cached field and statistic and writes the parameter, the loss and
-// the count.  rows, vals (k_max * N) and cnt (2 k_max) are scratch for the lists
-// of moved samples.
+// the count.  rows, vals (N per list of list_group(), or of the largest batch) and cnt
+// (two per list) are scratch for the lists of moved samples.
 hipError_t launch_norm(const NetDev& net, const NormDev& nd, const mca_cand* cands,
                        const Aux* aux, int K, int* rows, float* vals, int* cnt, float* partial,
                        int ntiles, int k_mode, DevState* st, const double* dL, hipStream_t s);

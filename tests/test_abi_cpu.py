@@ -74,6 +74,31 @@ def test_plan_rejects_bad_descriptions(binding, mutate, code):
     assert code in str(e.value)
 
 
+@pytest.mark.parametrize("widths,kw", [
+    ([784, 256, 256, 256, 10], dict(biases=True, layer_norm=True)),
+    ([784, 512, 512, 512, 10], dict()),
+    ([784, 256, 256, 256, 10], dict(mutation="channel_redraw")),
+])
+def test_plan_bounds_the_lists(binding, widths, kw):
+    """Lists of moved samples are planned for as many candidates as 2^22 entries
+    take (69 of 60000 samples), not for k_max: past those a candidate costs its
+    records, sums and traces (33 to 60 KB), less than a word for every second sample."""
+    N = 60000
+    d = binding.mlp_desc(widths, "relu", delta=0.1, seed=1, stream_tag=1, **kw)
+    size = [binding.mca_plan(d, N, k) for k in (70, 1024)]
+    assert size[1] - size[0] < 954 * 4 * N // 2
+
+
+def test_plan_stages_one_biased_layer(binding):
+    """The augmented matrices of a biased net pass through the lists' memory one
+    layer at a time: another 1024-unit layer takes 10 bytes a weight (fp32 and the
+    bf16 parts) and its fields, not 4 more for an augmented copy."""
+    d = [binding.mlp_desc([784] + [1024] * h + [10], "relu", delta=0.1, seed=1, stream_tag=1, biases=True,
+                          layer_norm=True) for h in (2, 3)]
+    a, b = [binding.mca_plan(x, 64, 1) for x in d]
+    assert b - a < 12 * 1024 * 1024
+
+
 def test_plan_layer_limits(binding):
     """Three-layer MLPs up to a 1024-unit second hidden layer are planned, and
     deeper nets with every hidden layer 256 (or all 512, all 1024) wide;

@@ -72,3 +72,46 @@ def test_changes_near_the_end_of_fp32(base, net):
     print(f"[gpu] rms error over rms size {ratio:.2e}", flush=True)
     assert ratio <= 2.0 ** -24
     ctx.close()
+
+
+@pytest.mark.parametrize("base,net", [
+    ("deepln", dict(widths=(64, 256, 256, 10), layer_pick="layer")),
+    ("deep", dict(widths=(64, 512, 512, 512, 10))),
+    ("channel", dict(widths=(64, 256, 256, 256, 10))),
+], ids=["normalized", "wide", "channel"])
+@pytest.mark.parametrize("N", [130, 65537])
+def test_batch_past_the_lists(base, net, N):
+    """150 candidates at once are scored to the same bits as 50 at a time (lists
+    are held for 64 on 65537 samples), one past the first 64 commits as it does
+    alone, and reading
+    the parameters between evaluation and commit changes nothing (a biased net's
+    pass through the lists' memory)."""
+    K = 150
+    cfg = CONFIGS[base].scaled(name=f"lists_{base}", data="sparse_uniform", n_samples=N, K=K,
+                               delta=0.1, seed_stream=5300, **net)
+    print(f"[gpu] {cfg.name} {cfg.widths}", flush=True)
+    w = mlp_workload(cfg)
+    ctx, _ = make_pair(cfg, w, k_max=K)
+    alone, _ = make_pair(cfg, w, k_max=50)
+    channel = cfg.mutation != "single"
+    cands = ctx.propose_channels(0, K) if channel else ctx.propose(0, K)
+    score = lambda c, r: (c.eval_channels(r) if channel else c.eval_losses(r))[1]
+    parts = []
+    for g in range(0, K, 50):
+        parts.append(score(alone, cands[g:g + 50]))
+        alone.rollback()
+    dl = score(ctx, cands)
+    assert dl.tobytes() == np.concatenate(parts).tobytes()
+    k = 64 + int(np.argmax(np.abs(dl[64:])))
+    assert dl[k] != 0.0
+    before = ctx.params()[0]
+    ctx.commit(k)
+    score(alone, cands[k:k + 1])
+    alone.commit(0)
+    assert ctx.loss()[0] == alone.loss()[0]
+    assert ctx.sample_losses().tobytes() == alone.sample_losses().tobytes()
+    after = ctx.params()[0]
+    assert [a.tobytes() for a in after] == [a.tobytes() for a in alone.params()[0]]
+    assert sum(int((a != b).sum()) for a, b in zip(before, after)) >= 1
+    ctx.close()
+    alone.close()
