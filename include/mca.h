@@ -19,8 +19,10 @@
  *   - Ownership: host arrays passed in are owned by the caller, read during the
  *     call and never retained.  The device workspace is owned by the caller
  *     (e.g. a torch uint8 tensor), must be at least mca_plan() bytes, 256-byte
- *     aligned, and must outlive the context.  The context owns only its host
- *     struct and, once created, a few HIP events.
+ *     aligned, and must outlive the context.  The context owns its host
+ *     struct, a block of pinned host memory (the state read back by
+ *     mca_run_steps, the records and loss changes of the explicit calls) and,
+ *     once created, a few HIP events.
  *   - Stream: all device work is enqueued on the hip_stream given to mca_init
  *     (hipStream_t passed as void*; NULL = the null stream).  Every call that
  *     returns host values synchronises that stream before returning.
@@ -286,12 +288,14 @@ int mca_rollback(mca_ctx* ctx);
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid it): mca_eval_losses
- * without any use of the context's per-call buffers.  The per-call device
- * buffers (the candidates' device copy, prepared values, tile sums, the
- * three-layer and deep nets' affected-sample lists, loss changes) live in one
- * static array per GPU for 8 MiB of them, held until the process ends; a request
- * that needs more (K x (N or tiles) too large) fails with MCA_EINVAL before
- * anything is enqueued.  The call allocates nothing, scores K candidates
+ * without the context's per-call device buffers.  These (the candidates' device
+ * copy, prepared values, tile sums, the three-layer and deep nets'
+ * affected-sample lists, loss changes) live in one static array per GPU, held
+ * until the process ends; a request for more than 8 MiB of it (K x (N or tiles)
+ * too large; the deep nets' tile sums counted per 64 samples) fails with
+ * MCA_EINVAL before anything is enqueued.  Records and results pass through the
+ * context's pinned host block, so calls on one context must not overlap.  The
+ * call allocates no device memory, scores K candidates
  * (1 <= K <= 1024, K not bounded by k_max) against the committed state
  * exactly as mca_eval_losses does (same kernels, same results), leaves no
  * pending batch and touches no pending batch's buffers, and synchronises.

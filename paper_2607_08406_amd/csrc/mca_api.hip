@@ -32,13 +32,17 @@ using mca::NetDev;
 // Per-call buffers of mca_eval_losses_noalloc: one array per GPU, for the
 // process's lifetime.  Host code never uses this name as an address: it is a
 // host-side stand-in; the device address comes from hipGetSymbolAddress.
-// A request is accepted by what it needs with the deep nets' tile sums counted
-// per 64 samples (kScratchLimit); they are kept per kChainT samples, and with
-// the candidates' order, in the margin: rows and rda take 8 bytes per
-// candidate and sample, so at the limit the finer sums and the order add at
-// most 2^20 (4 / 48 - 4 / 64) + 8 * 1024 bytes and their alignment.
+// A request may take kScratchLimit with the deep nets' tile sums counted per 64
+// samples and one count a candidate.  They are kept per kChainT samples, and the
+// candidates' order behind the counts, in the margin: rows and rda take 8 bytes
+// per candidate and sample, so a request within the limit has at most 2^20 of
+// these pairs.
 constexpr size_t kScratchLimit = (size_t)8 << 20;
 constexpr size_t kScratchBytes = kScratchLimit + ((size_t)64 << 10);
+static_assert((kScratchLimit / 8) * 4 * (64 - mca::kChainT) / (64 * mca::kChainT) +  // finer sums
+                      8 * (size_t)mca::kMaxK +  // a part-filled tile, an order entry per candidate
+                      2 * 256 <= kScratchBytes - kScratchLimit,  // alignment
+              "the margin covers what the limit does not count");
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 namespace {
@@ -1389,9 +1393,10 @@ int mca_eval_losses_noalloc(mca_ctx* ctx, const mca_cand* cands_host, int32_t K,
     off_limit = off;
   }
   if (off_limit > kScratchLimit || off > kScratchBytes)
-    return fail(ctx, MCA_EINVAL, "K candidates on this net need " + std::to_string(off_limit) +
-                                     " bytes of scratch, more than the static array's " +
-                                     std::to_string(kScratchLimit));
+    return fail(ctx, MCA_EINVAL, "K candidates on this net take " + std::to_string(off) +
+                                     " bytes of scratch (" + std::to_string(off_limit) +
+                                     " with tile sums per 64 samples, of which " +
+                                     std::to_string(kScratchLimit) + " are allowed)");
   char* base = (char*)ctx->scratch_dev;
   const Bufs b{(mca_cand*)(base + o_cands), (Aux*)(base + o_aux), (uint64_t*)(base + o_cmask),
                (float*)(base + o_partial), (double*)(base + o_dl),
