@@ -305,7 +305,7 @@ int mca_rollback(mca_ctx* ctx);
 int mca_eval_losses_noalloc(mca_ctx* ctx, const mca_cand* cands_host, int32_t K,
                             double* loss_out, double* dloss_out);
 
-/* Tuning options of mca_run_steps (mca_set_option):
+/* Tuning options (mca_set_option), of mca_run_steps unless said otherwise:
  *   MCA_OPT_PERSISTENT_LOOP  1 (default): run eligible nets (mutations reach
  *                            at most the last two layers, K <= 64) in one
  *                            launch per call: one workgroup when the samples
@@ -325,10 +325,15 @@ int mca_eval_losses_noalloc(mca_ctx* ctx, const mca_cand* cands_host, int32_t K,
  *                            workgroup kept out makes the loop's bounded waits
  *                            give up: MCA_EDEVICE, never a hang); 0: a
  *                            cooperative launch, where the runtime guarantees
- *                            it (about 15 us more per call). */
+ *                            it (about 15 us more per call).
+ *   MCA_OPT_PINNED_IO        1 (default): the explicit calls exchange records and
+ *                            loss changes through the context's pinned block,
+ *                            where one could be had; 0: through copies, as they
+ *                            do without one.  The same results. */
 #define MCA_OPT_PERSISTENT_LOOP 1
 #define MCA_OPT_LOOP_TILE 2
 #define MCA_OPT_LOOP_LAUNCH 3
+#define MCA_OPT_PINNED_IO 4
 /* Set a tuning option; MCA_EINVAL for an unknown option or value. */
 int mca_set_option(mca_ctx* ctx, int32_t option, int64_t value);
 

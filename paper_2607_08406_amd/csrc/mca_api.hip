@@ -485,6 +485,7 @@ struct mca_ctx {
   // records, and k_max loss changes with the committed loss behind them.
   void* io_recs = nullptr;
   double* io_dl = nullptr;
+  void* io_blk = nullptr;  // the block they lie in, also while MCA_OPT_PINNED_IO is 0
   bool use_loop = true;
   bool loop_coop = false;    // cooperative launch of the step loop (default: ordinary)
   void* scratch_dev = nullptr;  // this device's static scratch array (no-allocation entry point)
@@ -726,6 +727,18 @@ int check_cands(mca_ctx* ctx, const mca_cand* c, int K) {
   return MCA_OK;
 }
 
+size_t io_records(const mca_ctx* ctx, size_t K) {
+  return align_up(K * (ctx->chan ? sizeof(mca_channel) : sizeof(mca_cand)));
+}
+
+// Has the explicit calls use the pinned block (where there is one) or copies.
+void use_pinned(mca_ctx* ctx, bool on) {
+  const size_t K = (size_t)std::max<int64_t>(ctx->k_max, mca::kMaxK);
+  on = on && ctx->io_blk != nullptr;
+  ctx->io_recs = on ? ctx->io_blk : nullptr;
+  ctx->io_dl = on ? (double*)((char*)ctx->io_blk + io_records(ctx, K)) : nullptr;
+}
+
 // Pinned host memory for the state read-back of every run_steps call and for
 // the explicit calls' records and loss changes (where it cannot be had, plain
 // host buffers and copies take its place).
@@ -735,13 +748,11 @@ void pin_host(mca_ctx* ctx) {
     (void)hipGetLastError();
   }
   const size_t K = (size_t)std::max<int64_t>(ctx->k_max, mca::kMaxK);  // (the no-allocation call takes any K up to kMaxK)
-  const size_t recs = align_up(K * (ctx->chan ? sizeof(mca_channel) : sizeof(mca_cand)));
-  if (hipHostMalloc(&ctx->io_recs, recs + (K + 1) * sizeof(double), hipHostMallocDefault) != hipSuccess) {
-    ctx->io_recs = nullptr;
+  if (hipHostMalloc(&ctx->io_blk, io_records(ctx, K) + (K + 1) * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+    ctx->io_blk = nullptr;
     (void)hipGetLastError();
-  } else {
-    ctx->io_dl = (double*)((char*)ctx->io_recs + recs);
   }
+  use_pinned(ctx, true);
 }
 
 // Where one evaluation's per-call buffers live: the context's workspace, or
@@ -1431,6 +1442,11 @@ int mca_set_option(mca_ctx* ctx, int32_t option, int64_t value) {
     ctx->loop_coop = value == 0;
     return MCA_OK;
   }
+  if (option == MCA_OPT_PINNED_IO) {
+    if (value != 0 && value != 1) return fail(ctx, MCA_EINVAL, "MCA_OPT_PINNED_IO takes 0 or 1");
+    use_pinned(ctx, value != 0);
+    return MCA_OK;
+  }
   if (option == MCA_OPT_LOOP_TILE) {
     if (ctx->tf) return fail(ctx, MCA_EINVAL, "MCA_OPT_LOOP_TILE applies to MLP contexts");
     if (value < kMinLoopTile || value > 64) return fail(ctx, MCA_EINVAL, "MCA_OPT_LOOP_TILE takes 16..64");
@@ -1697,7 +1713,7 @@ void mca_destroy(mca_ctx* ctx) {
   }
   for (auto e : ctx->pool) (void)hipEventDestroy(e);
   if (ctx->host_blk) (void)hipHostFree(ctx->host_blk);
-  if (ctx->io_recs) (void)hipHostFree(ctx->io_recs);
+  if (ctx->io_blk) (void)hipHostFree(ctx->io_blk);
   delete ctx;
 }
 

@@ -29,7 +29,7 @@ MCA_MUTATE_SINGLE, MCA_MUTATE_CHANNEL_REDRAW, MCA_MUTATE_CHANNEL_ZERO = 0, 1, 2
 MCA_WEIGHTS_FP32, MCA_WEIGHTS_TERNARY = 0, 1
 MCA_PICK_WEIGHT, MCA_PICK_LAYER, MCA_PICK_STICKY = 0, 1, 2
 MCA_RULE_GREEDY, MCA_RULE_METROPOLIS = 0, 1
-MCA_OPT_PERSISTENT_LOOP, MCA_OPT_LOOP_TILE, MCA_OPT_LOOP_LAUNCH = 1, 2, 3
+MCA_OPT_PERSISTENT_LOOP, MCA_OPT_LOOP_TILE, MCA_OPT_LOOP_LAUNCH, MCA_OPT_PINNED_IO = 1, 2, 3, 4
 
 STATUS_NAMES = {0: "MCA_OK", -1: "MCA_EINVAL", -2: "MCA_ESTATE", -3: "MCA_ENOSPACE",
                 -4: "MCA_EDEVICE", -5: "MCA_EPOISONED", -6: "MCA_EUNSUPPORTED"}

@@ -10,7 +10,7 @@ import pytest
 import torch
 
 from parity_util import make_pair
-from workloads import CONFIGS, mlp_workload
+from workloads import CONFIGS, mlp_workload, transformer_workload
 
 pytestmark = pytest.mark.gpu
 
@@ -84,3 +84,46 @@ def ctx_propose_free(mca, ctx, cands):
     c = cands.copy()
     c[-1]["d"] = 0.0
     return c
+
+
+PINNED = [CASES[0][1], CASES[1][1], CASES[2][1],
+          CONFIGS["deepln"].scaled(name="io_ln", widths=(784, 256, 256, 10), n_samples=300, layer_pick="layer"),
+          CONFIGS["channel"].scaled(name="io_chan", widths=(784, 256, 256, 10), n_samples=300),
+          CONFIGS["transformer"].scaled(name="io_tf", vocab=20, ctx=16, d_model=32, n_layer=1, n_head=1, d_mlp=64,
+                                        n_seq=4)]
+
+
+@pytest.mark.parametrize("cfg", PINNED, ids=[c.name for c in PINNED])
+def test_explicit_calls_without_the_pinned_block(mca, cfg):
+    """Records and loss changes through copies, as where no pinned memory can be
+    had, are the bits that the pinned exchange gives, call by call."""
+    K, tf = 12, cfg.name == "io_tf"
+    print(f"[gpu] pinned exchange and copies {cfg.name}", flush=True)
+    pair = []
+    for pinned in (1, 0):
+        if tf:
+            w = transformer_workload(cfg)
+            desc = mca.transformer_desc(cfg.vocab, cfg.ctx, cfg.d_model, cfg.n_layer, cfg.n_head, cfg.d_mlp,
+                                        delta=cfg.delta, seed=cfg.seed_stream, stream_tag=cfg.stream_tag)
+            c = mca.TransformerContext(desc, w["params"], w["tokens"], w["targets"], K)
+        else:
+            c, _ = make_pair(cfg, mlp_workload(cfg), k_max=K)
+        c.set_option(mca.MCA_OPT_PINNED_IO, pinned)
+        pair.append(c)
+    channel = cfg.name == "io_chan"
+    for t in range(3):
+        out = []
+        for c in pair:
+            r = c.propose_channels(t, K) if channel else c.propose(t, K)
+            loss, dl = c.eval_channels(r) if channel else c.eval_losses(r)
+            k = int(np.argmin(dl))
+            c.commit(k)
+            out.append((r.tobytes(), loss.tobytes(), dl.tobytes(), k, c.loss()[0]))
+            if cfg in PINNED[:3]:
+                loss, dl = mca.mca_eval_losses_noalloc(c.ctx, c.propose(t + 10, K))
+                out[-1] += (loss.tobytes(), dl.tobytes())
+        assert out[0] == out[1], t
+    with pytest.raises(mca.MCAError, match="EINVAL"):
+        pair[0].set_option(mca.MCA_OPT_PINNED_IO, 2)
+    for c in pair:
+        c.close()
