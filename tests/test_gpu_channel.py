@@ -1,10 +1,11 @@
 """Channel mutation (Sec. 2.3) on the GPU against the fp64 oracle, through the C ABI.
 
-Every width the kernels take (256, 512, 1024: tiles of 64, 32, 16 samples),
-nets of two to five layers (rank-1 only, rank-1 then logits, dense layers in
-between), ReLU and the other transfer functions, both schemes (re-draw with
-the He amplitude, zeroing), a ragged last tile, a weight bound that rejects
-some channels, explicit propose / eval / commit / rollback beside the oracle,
+Every width the kernels take (256, 512, 1024: tiles of 48, 32, 32 listed samples,
+16 in a commit), nets of two to five layers (rank-1 only, rank-1 then logits,
+dense layers in between), ReLU and the other transfer functions, both schemes
+(re-draw with the He amplitude, zeroing), a ragged last tile, sample counts around
+the 2048-sample segments of the listing and its rows of 1024, a weight bound that
+rejects some channels, explicit propose / eval / commit / rollback beside the oracle,
 device runs replayed on the oracle, and the full-size five-layer
 784-1024-1024-1024-10 workload with pooled oracle replicas.
 
@@ -115,6 +116,52 @@ def test_channel_explicit_and_device(mca, widths, act, scheme, N):
     after = ctx.sample_losses()
     np.testing.assert_allclose(before, after, rtol=2e-5, atol=2e-6)
     assert acc + acc2 >= 1 or scheme == "channel_zero"
+    ctx.close()
+
+
+SEGMENTS = [
+    # widths, act, N: the listing's segments of 2048 samples, two rows of 1024 each
+    ((64, 256, 256, 256, 10), "relu", 1025),
+    ((64, 256, 256, 10), "gauss", 2047),
+    ((64, 256, 256, 256, 256, 10), "tanh", 2049),
+    ((64, 1024, 1024, 10), "relu", 2049),
+    ((64, 1024, 1024, 1024, 10), "relu", 3001),
+    ((64, 256, 256, 256, 10), "relu", 5000),
+    ((64, 512, 512, 512, 10), "relu", 5000),
+    ((64, 1024, 1024, 1024, 10), "tanh", 5000),
+]
+
+
+@pytest.mark.parametrize("widths,act,N", SEGMENTS)
+def test_channel_segments(mca, widths, act, N):
+    """Several segments with a part-filled last one (down to one sample), and one
+    whose second row of 1024 is part-filled: explicit steps, a commit of a channel
+    that is not the batch's best, device steps, and the caches against a forward
+    pass."""
+    cfg = cfg_of(widths, act, "channel_redraw", N, K=6, seed=9, data="sparse_uniform",
+                 gamma=0.4 if act == "gauss" else 1.0)
+    banner(f"channel segments {widths} {act} N={N}")
+    w = mlp_workload(cfg)
+    ctx, ref = make_pair(cfg, w, k_max=cfg.K)
+    ps = ParityStats(f"channel {'-'.join(map(str, widths))} {act} N={N}")
+    explicit_channel_steps(ctx, ref, cfg, 0, 3, cfg.K, ps)
+    chans = ctx.propose_channels(3, cfg.K)
+    L_t, rc, dls, mags, th, _, _ = _oracle_step(ref, cfg, 3, cfg.K, 0.0, 0.0, 0)
+    ctx.eval_channels(chans)
+    k = int(np.argmax(np.abs(dls)))
+    ctx.commit(k)
+    ref.commit(rc[k], L_t + dls[k])
+    before = ctx.sample_losses()
+    ctx.refresh()
+    np.testing.assert_allclose(before, ctx.sample_losses(), rtol=2e-5, atol=2e-6)
+    ctx.set_step(4)
+    st, ch, dl = ctx.run_steps(3, cfg.K, trace=True, trace_dloss=True)
+    _, acc = replay_trace(ref, cfg, 4, ch, dl, cfg.K, ps)
+    assert st.accepted == acc
+    assert_state_equal(ctx, ref)
+    before = ctx.sample_losses()
+    ctx.refresh()
+    np.testing.assert_allclose(before, ctx.sample_losses(), rtol=2e-5, atol=2e-6)
     ctx.close()
 
 

@@ -4,7 +4,8 @@ A first-layer mutation moves one unit of the first hidden layer, every unit
 of the second hidden layer for each affected sample (rank-1), and then the
 logits; second- and third-layer mutations are the column cases of the
 two-layer path.  Workloads: reduced ternary Gaussian and tanh nets whose
-sample counts span several 24-sample tiles and a ragged tail, and the full
+sample counts span several 16-sample tiles (12 for class counts other than ten)
+and a ragged tail, and the full
 ternary 784-1024-1024-10 net on 8,192 samples at K = 64.
 """
 import numpy as np
@@ -52,8 +53,8 @@ def layer_counts(ref, cfg, t0, n, K):
 
 
 def test_ternary_three_layer_small(mca):
-    """784-96-80-10 Gaussian ternary net on 333 samples (13 full tiles of 24
-    and a tail of 21): explicit steps, then a device run replayed."""
+    """784-96-80-10 Gaussian ternary net on 333 samples (20 full tiles of 16
+    and a tail of 13): explicit steps, then a device run replayed."""
     cfg = CONFIGS["ternary"].scaled(name="t3_small", widths=(784, 96, 80, 10), n_samples=333,
                                     K=16)
     banner(f"{cfg.name} {cfg.widths} N={cfg.n_samples}")
@@ -122,7 +123,7 @@ def test_tanh_three_layer_continuous(mca):
     ctx.close()
 
 
-@pytest.mark.parametrize("N", [1, 23, 24, 25, 49])
+@pytest.mark.parametrize("N", [1, 15, 16, 17, 23, 24, 25, 49])
 def test_three_layer_tile_edges(mca, N):
     cfg = CONFIGS["ternary"].scaled(name=f"t3_n{N}", widths=(784, 40, 36, 10), n_samples=N, K=8)
     w = mlp_workload(cfg)

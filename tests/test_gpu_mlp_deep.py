@@ -4,7 +4,7 @@ A mutation in layers 0..L-4 moves one unit, every unit of the next layer for
 each affected sample (rank-1), and then every later layer through dense
 products on the matrix cores; layer L-3 and the last two layers take the
 tile and column kernels.  Workloads: reduced tanh nets with 256-unit hidden
-layers whose sample counts span several 64-sample tiles and a ragged tail,
+layers whose sample counts span several 48-sample tiles and a ragged tail,
 sparse image inputs (sparse lists of affected samples), and the full
 784-(24 x 256)-10 net on 4,096 samples at K = 32 with the layer drawn first.
 """
@@ -57,7 +57,7 @@ def small_deep(**kw):
 
 
 def test_deep_small_every_layer_kind(mca):
-    """64-256-256-256-256-10 tanh, 200 samples (3 tiles of 64 + 8), K = 8,
+    """64-256-256-256-256-10 tanh, 200 samples (4 tiles of 48 + 8), K = 8,
     layer drawn first: chain (layers 0, 1), tile (2) and column (3, 4)."""
     cfg = small_deep()
     banner(f"{cfg.name} {cfg.widths} N={cfg.n_samples}")

@@ -1,6 +1,7 @@
 """Deep nets of Sec. 2.1 on the GPU against the fp64 oracle, through the C ABI:
 a bias per unit, hidden fields normalized over their layer, and the
-layer-sticky schedule; widths 256, 512 and 1024 (tiles of 64, 32, 16 samples),
+layer-sticky schedule; widths 256, 512 and 1024 (tiles of 48, 32, 32 listed
+samples, 16 in a commit), sample counts around the listing's chunks of 4096,
 ReLU, tanh and the Gaussian; explicit propose / eval / commit / rollback
 beside the oracle, device runs replayed on it, a candidate forced onto every
 layer's bias, pruning candidates with a minibatch (Sec. 2.2's with-LN runs),
@@ -17,8 +18,8 @@ import torch
 
 from oracle.philox import Candidate
 from oracle_pool import OraclePool
-from parity_util import (ParityStats, assert_state_equal, check_step, explicit_steps, make_pair,
-                         norm_kappa, replay_trace)
+from parity_util import (ParityStats, _oracle_step, assert_state_equal, check_step, explicit_steps,
+                         make_pair, norm_kappa, replay_trace)
 from workloads import CONFIGS, mlp_workload
 
 pytestmark = pytest.mark.gpu
@@ -58,6 +59,50 @@ CASES = [
     ((784, 512, 512, 512, 10), "tanh", False, False, 600, "layer", 0),
     ((784, 1024, 1024, 1024, 10), "relu", False, False, 400, "layer", 0),
 ]
+
+
+CHUNKS = [
+    # widths, act, ln, bias, N: the listing takes 4096 samples at a time
+    ((64, 256, 256, 10), "relu", True, True, 4095),
+    ((64, 256, 256, 10), "relu", False, True, 4097),
+    ((64, 512, 512, 512, 10), "relu", False, False, 5000),
+    ((64, 512, 512, 10), "tanh", True, True, 4097),
+    ((64, 1024, 1024, 10), "relu", True, True, 5000),
+]
+
+
+@pytest.mark.parametrize("widths,act,ln,bias,N", CHUNKS)
+def test_normnet_chunks(mca, widths, act, ln, bias, N):
+    """Lists that go on over the listing's chunks, the last one part-filled (down
+    to one sample): explicit steps, the candidate of the largest change in each
+    layer committed in turn, and the caches against a forward pass."""
+    cfg = cfg_of(widths, act, ln, bias, N, K=10, pick="layer", seed=9, delta=0.05, data="sparse_uniform")
+    banner(f"normnet chunks {widths} {act} ln={ln} bias={bias} N={N}")
+    w = mlp_workload(cfg)
+    ctx, ref = make_pair(cfg, w, k_max=cfg.K)
+    ps = ParityStats(f"normnet {'-'.join(map(str, widths))} {act} ln={int(ln)} N={N}")
+    explicit_steps(ctx, ref, cfg, 0, 3, cfg.K, ps)
+    done = set()
+    for t in range(3, 23):
+        if len(done) == len(widths) - 1:
+            break
+        cands = ctx.propose(t, cfg.K)
+        L_t, rc, dls, _, _, _, _ = _oracle_step(ref, cfg, t, cfg.K, 0.0, 0.0, 0)
+        new = [k for k in range(cfg.K) if rc[k].layer not in done]
+        if not new:
+            continue
+        ctx.eval_losses(cands)
+        k = max(new, key=lambda x: abs(dls[x]))
+        ctx.commit(k)
+        ref.commit(rc[k], L_t + dls[k])
+        done.add(rc[k].layer)
+        before = ctx.sample_losses()
+        ctx.refresh()
+        np.testing.assert_allclose(before, ctx.sample_losses(), rtol=2e-5, atol=2e-6)
+    assert len(done) == len(widths) - 1
+    explicit_steps(ctx, ref, cfg, 30, 2, cfg.K, ps)
+    assert_state_equal(ctx, ref)
+    ctx.close()
 
 
 @pytest.mark.parametrize("widths,act,ln,bias,N,pick,sticky", CASES)

@@ -1,8 +1,10 @@
 """The dense products on bf16 parts, at the edges of their tiles, against the
 fp64 oracle: sample counts around the 48-sample tile of the deep nets' chain,
-with candidates in every layer kind (the longest chains first in the grid),
-commits of every layer (each must leave the split copy of the weights equal to
-the weights: later steps read it), and a resume that rebuilds it."""
+with candidates in every layer kind (the longest chains first in the grid), and a
+resume that rebuilds the split copy of the weights; commits of every layer of
+every net kind, each of which must leave that copy equal to the weights (bit for
+bit against a context made from them); changes near the end of fp32; batches
+larger than the lists of moved samples."""
 import numpy as np
 import pytest
 import torch
@@ -29,7 +31,8 @@ def test_chain_tiles(act, N):
     _, acc = replay_trace(ref, cfg, 0, ch, dl, 13, ps)
     assert st.accepted == acc >= 5
     assert_state_equal(ctx, ref)
-    # the split copy kept through the commits equals one made from the weights
+    # after a resume, which makes the split copy anew, the same candidates score
+    # the same
     cands = ctx.propose(99, 13)
     _, before = ctx.eval_losses(cands)
     ctx.rollback()
@@ -38,6 +41,45 @@ def test_chain_tiles(act, N):
     ctx.rollback()
     # (the caches are recomputed: fields differ in their last bits)
     np.testing.assert_allclose(before, after, rtol=1e-3, atol=1e-9)
+    ctx.close()
+
+
+@pytest.mark.parametrize("base,net", [
+    ("deep", dict(widths=(64, 256, 256, 256, 256, 10))),
+    ("deep", dict(widths=(64, 512, 512, 512, 512, 10))),
+    ("deepln", dict(widths=(64, 256, 256, 256, 10), layer_pick="layer")),
+    ("deepln", dict(widths=(64, 1024, 1024, 1024, 10), layer_pick="layer", layer_norm=False)),
+    ("channel", dict(widths=(64, 256, 256, 256, 10))),
+], ids=["chain", "wide", "normalized", "bias", "channel"])
+def test_split_copy_after_each_commit(base, net):
+    """After a commit in each layer (a channel: in all of them) and a forward pass,
+    candidates score to the same bits as on a context made from the parameters: a
+    split weight that a commit left behind would move every change that passes
+    through it."""
+    K = 40
+    cfg = CONFIGS[base].scaled(name=f"copy_{base}", act="tanh", data="sparse_uniform", n_samples=70, K=K,
+                               delta=0.3, seed_stream=5100, **net)
+    print(f"[gpu] {cfg.name} {cfg.widths}", flush=True)
+    w = mlp_workload(cfg)
+    ctx, _ = make_pair(cfg, w, k_max=K)
+    channel = cfg.mutation != "single"
+    propose = lambda c, t: c.propose_channels(t, K) if channel else c.propose(t, K)
+    score = lambda c, r: (c.eval_channels(r) if channel else c.eval_losses(r))[1]
+    for n, layer in enumerate([None] * 3 if channel else range(cfg.n_layers)):
+        cands = propose(ctx, n)
+        pick = range(K) if channel else np.flatnonzero(cands["layer"] == layer)
+        score(ctx, cands)
+        before = ctx.params()[0]
+        ctx.commit(int(pick[0]))
+        after = ctx.params()[0]
+        moved = [l for l in range(cfg.n_layers) if (before[l] != after[l]).any()]
+        assert moved == (list(range(cfg.n_layers)) if channel else [layer])
+        ctx.refresh()
+        fresh, _ = make_pair(cfg, dict(w, weights=after), k_max=K)
+        cands = propose(ctx, 100 + n)
+        assert score(ctx, cands).tobytes() == score(fresh, cands).tobytes(), layer
+        ctx.rollback()
+        fresh.close()
     ctx.close()
 
 
