@@ -1070,9 +1070,13 @@ hipError_t tf_launch_eval(const TfDev* tf, const TfDev& h, const mca_cand* cands
     else
       hipLaunchKernelGGL(k_tf_stats<4>, srow, dim3(kRowThreads), 0, s, tf, cands, aux, stage, which, ncand);
   };
-  // 128-column tiles, or 64-column ones where those leave fewer columns unused
+  // 128-column tiles, or 64-column ones where those leave fewer columns unused or
+  // the wide ones would not give every CU two blocks (a block's time is a chain of
+  // chunks then: the forward pass over 1540 positions, three blocks, 456 us with
+  // wide tiles and 403 with narrow ones; 16 candidates on 8192 positions, d_model
+  // 256, 1513 us wide, 1605 narrow).  Every output's sum is the same bits in both.
   auto gemm = [&](auto wide_tile, auto narrow_tile, int stage, int nout, int role) {
-    if (tiles(nout, 128) * 2 == tiles(nout, 64))
+    if (tiles(nout, 128) * 2 == tiles(nout, 64) && (int64_t)mt * tiles(nout, 128) * rows >= 512)
       hipLaunchKernelGGL(wide_tile, dim3(mt, tiles(nout, 128), rows), dim3(kGemmThreads), 0, s, tf, stage, role, ncand);
     else
       hipLaunchKernelGGL(narrow_tile, dim3(mt, tiles(nout, 64), rows), dim3(kGemmThreads), 0, s, tf, stage, role, ncand);

@@ -274,3 +274,20 @@ def test_commit_of_every_evaluation_kind(mca):
     ctx.refresh()
     np.testing.assert_allclose(before, ctx.sample_losses(), rtol=1e-5, atol=1e-6)
     ctx.close()
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(n_head=8, d_model=256, d_mlp=640)])
+def test_tile_widths_give_the_same_bits(mca, kw):
+    """A candidate scored alone (few blocks: 64-column tiles) and among 16 on 8192
+    positions (128-column tiles) changes the loss by the same bits."""
+    cfg = CONFIGS["transformer"].scaled(name="tiles", **kw)
+    banner(f"transformer tile widths d {cfg.d_model}")
+    ctx, _, _ = make_pair(mca, cfg, 16)
+    cands = ctx.propose(0, 16)
+    _, together = ctx.eval_losses(cands)
+    ctx.rollback()
+    for k in range(0, 16, 3):
+        _, alone = ctx.eval_losses(cands[k:k + 1])
+        ctx.rollback()
+        assert alone.tobytes() == together[k:k + 1].tobytes(), k
+    ctx.close()
