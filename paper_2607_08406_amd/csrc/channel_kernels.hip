@@ -17,7 +17,8 @@
 // third, and so on.  k_channel_rows walks every sample along the path up to the
 // layer f that first receives a changed activation: layer f moves by the rank-1
 // term of that one unit, and only the layers after it need dense products.
-// Samples whose walk reaches the logits are done there (a rank-1 logit change);
+// Samples whose walk reaches the logits are done there (a rank-1 logit change; in a
+// net of two layers all of them, k_channel_two);
 // the others are listed, those of f = 1 first, and blocks of k_channel take tiles
 // of T of them (dense_tile.hpp).  On 784-1024x3-10 with ReLU a tenth of the
 // samples need the dense layer, a fifth a rank-1 second layer: 16 channels on 8192
@@ -42,6 +43,8 @@ constexpr int kChannelBlocks = 512;
 // most one part-filled tile more, and the walked samples.
 constexpr int kSegU = 2, kSegment = kSegU * kListThreads;
 __host__ __device__ constexpr int segment_slots(int T) { return (kSegment + T - 1) / T + 2; }
+// Samples of a block of k_channel_two: one wave.
+constexpr int kTwo = 64;
 
 // The channel of draw (t, k): 2L + 1 words of the Philox blocks at counters
 // (t, k, 2 + b, 0), four words per block, in order.
@@ -327,6 +330,76 @@ __global__ __launch_bounds__(kListThreads) void k_channel_rows(NetDev net_arg, c
   }
 }
 
+// A net of two layers: every sample's walk ends at the logits and nothing is listed.
+// Block (b, k) (eval) or (b, 0) for the committed channel: 64 samples, their changes'
+// sum the block's one tile sum.  A step of such a net is a chain of short launches,
+// so a sample's loads all leave together and a block is one wave: walked as segments
+// of 2048 samples on one CU each, 380-256-12 with one channel a step on 1585 samples
+// took 37 us a step (24 here), 400-512-10 with 64 channels on 10000 samples 86 (43).
+__global__ __launch_bounds__(kTwo) void k_channel_two(NetDev net_arg, const mca_channel* chans, const Aux* aux,
+                                                      float* partial, int nchan, int k_mode, const DevState* st) {
+  __shared__ NetDev net;
+  stage_net(net, net_arg);
+  __shared__ int units[MCA_MAX_LAYERS + 1];
+  __shared__ float de[MCA_MAX_LAYERS];
+  const int tid = threadIdx.x;
+  const bool commit = k_mode != -2;
+  const int k = commit ? ((k_mode >= 0) ? k_mode : st->chosen) : (int)blockIdx.y;
+  if (k < 0) return;
+  if (!commit && !aux[k].valid) {  // rejected unevaluated: selection gives +inf
+    if (tid == 0) partial[(int64_t)k * nchan + blockIdx.x] = 0.f;
+    return;
+  }
+  load_path(net, chans[k], units, de);
+  const int C = net.C, act = net.act, cls = units[2];
+  const float gamma = net.gamma;
+  const int64_t N = net.N, Ns = net.Ns, at = (int64_t)blockIdx.x * kTwo + tid, n = at < N ? at : N - 1;
+  float* zp = net.Z[0] + (int64_t)units[1] * Ns + n;
+  const float* WL = net.W[1] + units[1];
+  const float x = gload(&net.XT[(int64_t)units[0] * Ns + n]), z0 = gload(zp);
+  const int y = gload(&net.y[n]);
+  float p[kCMax], w[kCMax];
+#pragma unroll
+  for (int c = 0; c < kCMax; ++c) {
+    p[c] = (c < C) ? gload(&net.prob[(int64_t)c * Ns + n]) : 0.f;
+    w[c] = (c < C) ? gload(&WL[(int64_t)c * net.widths[1]]) : 0.f;
+  }
+  const float dz0 = de[0] * x, d = dphi(z0, dz0, act, gamma), ap = act_fn(z0 + dz0, act, gamma);
+  float change = 0.f;
+  if (at < N && (d != 0.f || de[1] * ap != 0.f)) {
+    float dz[kCMax], dzy = 0.f;
+#pragma unroll
+    for (int c = 0; c < kCMax; ++c) {
+      dz[c] = d * w[c];
+      if (c == cls) dz[c] = fmaf(de[1], ap, dz[c]);
+      dzy = (c == y) ? dz[c] : dzy;
+    }
+    change = ce_change<kCMax>(p, dz, C, dzy);
+    if (commit) {
+      float* ZL = net.Z[1];
+      float z[kCMax], pn[kCMax];
+#pragma unroll
+      for (int c = 0; c < kCMax; ++c) z[c] = (c < C) ? gload(&ZL[(int64_t)c * Ns + n]) + dz[c] : 0.f;
+      const float ln = softmax_ce<kCMax>(z, C, y, pn);
+#pragma unroll
+      for (int c = 0; c < kCMax; ++c)
+        if (c < C) {
+          gstore(&ZL[(int64_t)c * Ns + n], z[c]);
+          gstore(&net.prob[(int64_t)c * Ns + n], pn[c]);
+        }
+      gstore(&net.ell[n], ln);
+    }
+  }
+  if (commit) {
+    if (at < N && dz0 != 0.f) gstore(zp, z0 + dz0);
+    return;
+  }
+  double sum = (double)change;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+  if (tid == 0) partial[(int64_t)k * nchan + blockIdx.x] = (float)sum;
+}
+
 // Tiles of the lists, shared out to the grid's blocks in list order.
 template <int W, int ACT, bool commit>
 __global__ __launch_bounds__((Dense<W, commit>::threads), (Dense<W, commit>::blocks_per_cu)) void k_channel(
@@ -478,7 +551,8 @@ __global__ __launch_bounds__((Dense<W, commit>::threads), (Dense<W, commit>::blo
 
 int channel_segments(int64_t n_samples) { return (int)((n_samples + kSegment - 1) / kSegment); }
 
-int channel_tiles(int64_t n_samples, int w) {
+int channel_tiles(int64_t n_samples, int w, int n_layers) {
+  if (n_layers == 2) return (int)((n_samples + kTwo - 1) / kTwo);
   const int T = w == 256 ? Dense<256, false>::T : (w == 512 ? Dense<512, false>::T : Dense<1024, false>::T);
   return channel_segments(n_samples) * segment_slots(T);
 }
@@ -534,11 +608,14 @@ hipError_t launch_channel(const NetDev& net, const mca_channel* ch, const Aux* a
     constexpr int W = decltype(w)::value, ACT = decltype(act)::value;
     auto run = [&](auto com) {
       typedef Dense<W, decltype(com)::value> D;
+      if (net.L == 2) {
+        hipLaunchKernelGGL(k_channel_two, dim3((unsigned)((net.N + kTwo - 1) / kTwo), commit ? 1u : (unsigned)K),
+                           dim3(kTwo), 0, s, net, ch, aux, partial, nchan, k_mode, st);
+        return;
+      }
       const int S = channel_segments(net.N);
       hipLaunchKernelGGL(k_channel_rows, dim3(S, commit ? 1 : K), dim3(kListThreads), 0, s, net, ch, aux, lists,
                          partial, nchan, D::T, K, k_mode, st);
-      // nets of two layers have no layer between the walk and the logits
-      if (net.L < 3) return;
       const int64_t tiles = (int64_t)S * segment_slots(D::T) * (commit ? 1 : K);
       const int64_t most = kChannelBlocks * D::blocks_per_cu;
       hipLaunchKernelGGL((k_channel<W, ACT, decltype(com)::value>), dim3((unsigned)(tiles < most ? tiles : most)),

@@ -11,7 +11,7 @@ namespace mca {
 inline bool channel_width_ok(int w) { return w == 256 || w == 512 || w == 1024; }
 // Segments of the samples, listed apart, and tile sums per channel.
 int channel_segments(int64_t n_samples);
-int channel_tiles(int64_t n_samples, int w);
+int channel_tiles(int64_t n_samples, int w, int n_layers);
 
 // The samples whose change goes past the path's units, per channel of
 // list_group(), or of the largest batch (N entries each): the sample, the changed

@@ -408,16 +408,18 @@ Layout make_layout(const mca_net_desc* net, int64_t N, int32_t k_max) {
     lo.wf = take((size_t)mca::split_size(net->widths[1], L) * sizeof(uint16_t));
   }
   if (net->mutation != MCA_MUTATE_SINGLE) {
-    lo.nchan = mca::channel_tiles(N, net->widths[1]);
+    lo.nchan = mca::channel_tiles(N, net->widths[1], L);
     lo.chans = take((size_t)k_max * sizeof(mca_channel));
     lo.pchan = take((size_t)k_max * lo.nchan * sizeof(float));
-    lo.rows = take(k_list * N * sizeof(int32_t));
-    lo.rda = take(k_list * N * sizeof(float));
-    lo.cap = take(k_list * N * sizeof(float));
-    lo.cf = take(k_list * N * sizeof(int32_t));
-    const size_t lists = 2 * k_list * mca::channel_segments(N);
-    lo.rcnt = take(lists * sizeof(int32_t));
-    lo.cfirst = take((lists + 1) * sizeof(int32_t));
+    if (L > 2) {  // (a net of two layers lists nothing)
+      lo.rows = take(k_list * N * sizeof(int32_t));
+      lo.rda = take(k_list * N * sizeof(float));
+      lo.cap = take(k_list * N * sizeof(float));
+      lo.cf = take(k_list * N * sizeof(int32_t));
+      const size_t lists = 2 * k_list * mca::channel_segments(N);
+      lo.rcnt = take(lists * sizeof(int32_t));
+      lo.cfirst = take((lists + 1) * sizeof(int32_t));
+    }
     lo.wf = take((size_t)mca::split_size(net->widths[1], L) * sizeof(uint16_t));
   }
   // persistent loop: tiles of T samples (16..64), one workgroup each; the

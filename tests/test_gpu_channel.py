@@ -121,6 +121,9 @@ def test_channel_explicit_and_device(mca, widths, act, scheme, N):
 
 SEGMENTS = [
     # widths, act, N: the listing's segments of 2048 samples, two rows of 1024 each
+    ((64, 256, 10), "relu", 64),  # two layers: blocks of 64 samples, no lists
+    ((64, 1024, 16), "gauss", 65),
+    ((64, 512, 3), "tanh", 2111),
     ((64, 256, 256, 256, 10), "relu", 1025),
     ((64, 256, 256, 10), "gauss", 2047),
     ((64, 256, 256, 256, 256, 10), "tanh", 2049),
