@@ -13,12 +13,14 @@
 // samples.  It stages their second-hidden-layer local fields ([n_2][T],
 // unit-major as in HBM, rows padded to T+1 floats), the logit-layer weights
 // transposed ([n_2][C]) and the tile's logits, softmax and labels in LDS, lists
-// every affected (candidate, sample) pair, and scores them with a wave for each
-// two of a candidate: lane g adds the list entries g, g+64, ... in order (the
-// next entries are requested while the current ones are used), then the lane
-// sums meet in a fixed butterfly.  The commit runs the same expressions in the same order for
-// the chosen candidate, so the caches hold exactly the values that were
-// scored.
+// every affected (candidate, sample) pair, and scores them with a wave (or half of
+// one) for each two of a candidate: lane g adds the list entries g, g+64, ... (g+32,
+// ...) in order (the next entries are requested while the current ones are used),
+// then the lane sums meet in a fixed butterfly.  The commit runs the same expressions
+// in the same order for the chosen candidate, so the caches hold exactly the values
+// that were scored.
+#include <type_traits>
+
 #include "device_common.hpp"
 #include "slab_kernels.hpp"
 #include "split_mma.hpp"
@@ -29,8 +31,8 @@ namespace {
 
 constexpr int kSlabThreads = 1024;
 constexpr int kGroupK = 64;  // candidate slots listed at a time
-constexpr int kWaves = kSlabThreads / 64;
-constexpr int kPairChunk = 2;        // pairs of one candidate that a wave scores together
+constexpr int kHalfEntries = 192;    // columns of at most these are scored by half a wave
+constexpr int kPairChunk = 2;        // pairs of one candidate scored together
 constexpr int kChunk = 2;    // list entries a lane loads at once (two batches in flight)
 constexpr int kStageU = 8;   // tile elements a thread loads at once
 constexpr int kStage4 = 4;   // the same in four samples each
@@ -47,33 +49,34 @@ template <int kCtrl>
 __device__ __forceinline__ float dpp_mov(float x) {
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), kCtrl, 0xF, 0xF, true));
 }
-// Sum over the wave in one fixed order, the same bits in every lane: DPP
-// within rows of 16 (lane ^ 1, ^ 2, then the mirrored partners), then the
-// other rows.
-__device__ __forceinline__ float wave_sum(float v) {
+// Sum over LANES (a wave, or each half of one) in one fixed order, the same bits in
+// every lane: DPP within rows of 16 (lane ^ 1, ^ 2, then the mirrored partners),
+// then the other rows.
+template <int LANES>
+__device__ __forceinline__ float lanes_sum(float v) {
   v += dpp_mov<0xB1>(v);   // quad_perm [1,0,3,2]
   v += dpp_mov<0x4E>(v);   // quad_perm [2,3,0,1]
   v += dpp_mov<0x141>(v);  // row_half_mirror
   v += dpp_mov<0x140>(v);  // row_mirror
   v += __shfl_xor(v, 16, 64);
-  return v + __shfl_xor(v, 32, 64);
+  return LANES == 32 ? v : v + __shfl_xor(v, 32, 64);
 }
 
 // Logit changes of up to kPairChunk pairs of one candidate (samples tp[p],
 // activation changes dp[p] of its first-hidden-layer unit, p < np, all uniform
-// over the wave): lane g takes the list entries g, g+64, ... in order, reads
-// each entry's logit-layer weights once for all the pairs, and the lane sums
-// meet in wave_sum().  zt: the block's tile (row stride TS); w2: [n2][CM]; col:
-// the candidate's nnz column entries (m in the low word, the bits of W_1[m, j]
-// in the high word).  With STORE each lane writes its units' new local fields
-// into the tile.
-template <int CM, int ACT, int TS, bool STORE>
+// over the LANES that share them): lane g takes the list entries g, g+LANES, ...
+// in order, reads each entry's logit-layer weights once for all the pairs, and
+// the lane sums meet in lanes_sum().  zt: the block's tile (row stride TS); w2:
+// [n2][CM]; col: the candidate's nnz column entries (m in the low word, the bits
+// of W_1[m, j] in the high word).  With STORE each lane writes its units' new
+// local fields into the tile.  All 64 lanes of the wave must call this.
+template <int CM, int ACT, int TS, int LANES, bool STORE>
 __device__ __forceinline__ void chunk_logit_delta(float* zt, const float* w2, const uint64_t* col,
                                                   int nnz, const int (&tp)[kPairChunk],
                                                   const float (&dp)[kPairChunk], int np,
                                                   float gamma,
                                                   float (&acc)[kPairChunk][CM]) {
-  const int g = threadIdx.x & 63;
+  const int g = threadIdx.x & (LANES - 1);
 #pragma unroll
   for (int p = 0; p < kPairChunk; ++p)
 #pragma unroll
@@ -85,14 +88,14 @@ __device__ __forceinline__ void chunk_logit_delta(float* zt, const float* w2, co
   auto fetch = [&](int e0, uint64_t (&ent)[kChunk]) {
 #pragma unroll
     for (int u = 0; u < kChunk; ++u) {
-      const int e = e0 + 64 * u;
+      const int e = e0 + LANES * u;
       ent[u] = gload(&col[e < nnz ? e : 0]);
     }
   };
   auto use = [&](int e0, const uint64_t (&ent)[kChunk]) {
 #pragma unroll
     for (int u = 0; u < kChunk; ++u) {
-      const int e = e0 + 64 * u;
+      const int e = e0 + LANES * u;
       if (e < nnz) {
         const int m = (int)(uint32_t)ent[u];
         const float w = __uint_as_float((uint32_t)(ent[u] >> 32));
@@ -114,7 +117,7 @@ __device__ __forceinline__ void chunk_logit_delta(float* zt, const float* w2, co
     }
   };
   if (nnz > 0) {
-    constexpr int kStride = 64 * kChunk;
+    constexpr int kStride = LANES * kChunk;
     uint64_t ea[kChunk], eb[kChunk];
     fetch(g, ea);
 #pragma unroll 1
@@ -129,7 +132,7 @@ __device__ __forceinline__ void chunk_logit_delta(float* zt, const float* w2, co
   for (int p = 0; p < kPairChunk; ++p)
 #pragma unroll
     for (int c = 0; c < CM; ++c)
-      if (p < np) acc[p][c] = wave_sum(acc[p][c]);
+      if (LANES == 32 || p < np) acc[p][c] = lanes_sum<LANES>(acc[p][c]);
 }
 
 }  // namespace
@@ -212,7 +215,7 @@ __global__ __launch_bounds__(kSlabThreads) void k_propose_columns(
 // candidate of layer L-3, and with `columns` also one of the last two layers
 // (the column commit, as k_commit_column); others are no-ops here.  ACT is
 // the net's transfer function (MCA_ACT_*), fixed at compile time.
-template <int CM, int ACT>
+template <int CM, int ACT, int LANES>
 __global__ __launch_bounds__(kSlabThreads) void k_slab(NetDev net_arg, const mca_cand* cands,
                                                        const Aux* aux, int K, const uint64_t* cols,
                                                        const int* nnz, float* partial, int nblk,
@@ -450,13 +453,24 @@ __global__ __launch_bounds__(kSlabThreads) void k_slab(NetDev net_arg, const mca
       stage_listed(cols + (int64_t)kc * n2, nnz[kc]);
       __syncthreads();
     }
-    // 4. score: wave w takes items w, w + kWaves, ... (a whole wave an item: at
-    // 47 items a block, the ternary net's, 32 half-waves would take two rounds
-    // at three quarters of their lanes)
-    for (int it = wave; it < ni; it += kWaves) {
-      const int code = __builtin_amdgcn_readfirstlane(items[it]);
+    // 4. score: LANES lanes take items w, w + 1024 / LANES, ...  A whole wave has its
+    // control flow in scalars and is the better one where columns are long (47 items a
+    // block on the 784-1024-1024-10 ternary net are two rounds of half-waves at three
+    // quarters of their lanes) or items few (300-300-230-10 ReLU, 8 candidates on 5000
+    // samples, 40 steps: 2.20 ms against 2.28); half a wave where a short column leaves
+    // a whole one idle (300-300-120-10, 63 candidates: 2.82 -> 2.55 ms; 300-300-32-10
+    // tanh, 64 candidates on 9000 samples: 5.15 -> 3.97).  The line follows the column's
+    // entries, half of the units in a ternary net.  Every wave runs the same rounds.
+    constexpr int kUnits = kSlabThreads / LANES;
+    auto uniform = [](int v) { return LANES == 64 ? __builtin_amdgcn_readfirstlane(v) : v; };
+    const int g = tid & (LANES - 1);
+    for (int i0 = 0; i0 < ni; i0 += kUnits) {
+      const int it = i0 + tid / LANES;
+      if (LANES == 64 && it >= ni) break;
+      const bool active = it < ni;
+      const int code = uniform(active ? items[it] : 0);
       const int s = code >> 4, ch = code & 15;
-      uint32_t pm = __builtin_amdgcn_readfirstlane(pmask[s]);
+      uint32_t pm = uniform(active ? pmask[s] : 0u);
       for (int r = 0; r < kPairChunk * ch; ++r) pm &= pm - 1u;  // the earlier chunks' samples
       int tp[kPairChunk];
       float dp[kPairChunk];
@@ -473,23 +487,23 @@ __global__ __launch_bounds__(kSlabThreads) void k_slab(NetDev net_arg, const mca
           np = p + 1;
         }
       }
-      const uint64_t* col = cols + (int64_t)__builtin_amdgcn_readfirstlane(gk[s]) * n2;
-      const int cnt = __builtin_amdgcn_readfirstlane(gnnz[s]);
+      const uint64_t* col = cols + (int64_t)uniform(gk[s]) * n2;
+      const int cnt = uniform(active ? gnnz[s] : 0);
       float acc[kPairChunk][CM];
       if (commit)  // the commit also writes the new fields into the tile
-        chunk_logit_delta<CM, ACT, TS, true>(zt, w2, col, cnt, tp, dp, np, gamma, acc);
+        chunk_logit_delta<CM, ACT, TS, LANES, true>(zt, w2, col, cnt, tp, dp, np, gamma, acc);
       else
-        chunk_logit_delta<CM, ACT, TS, false>(zt, w2, col, cnt, tp, dp, np, gamma, acc);
-      if (lane < np) {  // lane p finishes pair p
+        chunk_logit_delta<CM, ACT, TS, LANES, false>(zt, w2, col, cnt, tp, dp, np, gamma, acc);
+      if (g < np) {  // lane p finishes pair p
         int t = tp[0];
         float pr[CM], dz[CM];
 #pragma unroll
         for (int c = 0; c < CM; ++c) dz[c] = acc[0][c];
 #pragma unroll
         for (int p = 1; p < kPairChunk; ++p) {
-          t = lane == p ? tp[p] : t;
+          t = g == p ? tp[p] : t;
 #pragma unroll
-          for (int c = 0; c < CM; ++c) dz[c] = lane == p ? acc[p][c] : dz[c];
+          for (int c = 0; c < CM; ++c) dz[c] = g == p ? acc[p][c] : dz[c];
         }
         const int64_t n = n0 + t;
         const int y = yt[t];
@@ -589,13 +603,19 @@ hipError_t launch_slab(const NetDev& net, const mca_cand* cands, const Aux* aux,
     hipLaunchKernelGGL(kernel, dim3(nblk), dim3(kSlabThreads), 0, s, net, cands, aux, K, cols,
                        nnz, partial, nblk, k_mode, st, dL, columns ? 1 : 0);
   };
-  const bool small = net.C == 10;  // the ten-class kernels take exactly ten
-  if (net.act == MCA_ACT_TANH)
-    small ? go(k_slab<10, MCA_ACT_TANH>) : go(k_slab<kCMax, MCA_ACT_TANH>);
-  else if (net.act == MCA_ACT_RELU)
-    small ? go(k_slab<10, MCA_ACT_RELU>) : go(k_slab<kCMax, MCA_ACT_RELU>);
-  else
-    small ? go(k_slab<10, MCA_ACT_GAUSS>) : go(k_slab<kCMax, MCA_ACT_GAUSS>);
+  auto by_act = [&](auto cm, auto lanes) {
+    constexpr int CM = decltype(cm)::value, LANES = decltype(lanes)::value;
+    if (net.act == MCA_ACT_TANH) go(k_slab<CM, MCA_ACT_TANH, LANES>);
+    else if (net.act == MCA_ACT_RELU) go(k_slab<CM, MCA_ACT_RELU, LANES>);
+    else go(k_slab<CM, MCA_ACT_GAUSS, LANES>);
+  };
+  auto by_units = [&](auto cm) {
+    if (net.widths[net.L - 1] <= kHalfEntries * (net.ternary ? 2 : 1)) by_act(cm, std::integral_constant<int, 32>{});
+    else by_act(cm, std::integral_constant<int, 64>{});
+  };
+  // (the ten-class kernels take exactly ten)
+  if (net.C == 10) by_units(std::integral_constant<int, 10>{});
+  else by_units(std::integral_constant<int, kCMax>{});
   return hipGetLastError();
 }
 

@@ -134,6 +134,25 @@ def test_three_layer_tile_edges(mca, N):
     ctx.close()
 
 
+@pytest.mark.parametrize("n2,ternary", [(192, False), (193, False), (384, True), (385, True)])
+def test_three_layer_lanes_per_pair(mca, n2, ternary):
+    """Columns at the line between half a wave and a whole one for a pair of samples
+    (192 entries, half of a ternary net's units)."""
+    base = CONFIGS["ternary"] if ternary else CONFIGS["tiny"]
+    cfg = base.scaled(name=f"t3_lanes{n2}", widths=(64, 48, n2, 10), data="sparse_uniform", n_samples=150, K=12)
+    banner(f"{cfg.name} {cfg.widths}")
+    w = mlp_workload(cfg)
+    ctx, ref = make_pair(cfg, w, k_max=12)
+    ps = ParityStats(f"three layers, {n2} units, ternary {int(ternary)}")
+    explicit_steps(ctx, ref, cfg, 0, 20, 12, ps)
+    ctx.set_step(20)
+    _, ch, dl = ctx.run_steps(20, 12, trace=True, trace_dloss=True)
+    replay_trace(ref, cfg, 20, ch, dl, 12, ps)
+    assert_state_equal(ctx, ref)
+    assert_caches_match(ctx, ref)
+    ctx.close()
+
+
 def test_rollback_three_layer_is_byte_identical(mca):
     cfg = CONFIGS["ternary"].scaled(name="t3_rb", widths=(784, 64, 48, 10), n_samples=200, K=16)
     w = mlp_workload(cfg)
