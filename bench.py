@@ -119,25 +119,69 @@ def candidate_flops(cfg, w, cands, params):
     return total
 
 
-def dense_path_flops(cfg, cands, channel: bool):
-    """Algorithmic flops of one step on the channel-mutation net (Sec. 2.3) or
-    the deep net with biases and normalization (Sec. 2.1), an FMA counting 2.
-    Counted for every sample, as the definition has it (the kernels skip the
-    samples and layers that a change does not reach, so the rate is one of
-    definition work).  A channel: its first-layer column (2 N), the
-    rank-1 term into the second layer (2 N W), a dense product per later
-    hidden layer (2 N W^2) and the logits (2 N W C).  A single mutation in
-    layer l below the logits: a dense product per later hidden layer
-    (2 N W^2) and the logits (2 N W C); in the logit layer: 2 N."""
+def committed_fields(cfg, w, params):
+    """Hidden activations a_0 = X .. a_{L-1} and fields z_0 .. z_{L-2} of the
+    committed parameters, [samples][units] on the GPU."""
+    import torch
+    a, z = [torch.from_numpy(w["X"]).cuda()], []
+    for l in range(cfg.n_layers - 1):
+        W = torch.from_numpy(params[l]).cuda()
+        f = a[l] @ W[:, :cfg.widths[l]].T
+        if cfg.biases:
+            f = f + W[:, -1]
+        z.append(f)
+        if cfg.layer_norm:
+            f = torch.nn.functional.layer_norm(f, (f.shape[1],), eps=cfg.ln_eps)
+        a.append(transfer(cfg, f))
+    return a, z
+
+
+def transfer(cfg, z):
+    import torch
+    if cfg.act == "tanh":
+        return torch.tanh(z)
+    return z.clamp_min(0) if cfg.act == "relu" else torch.exp(-cfg.gamma * z * z)
+
+
+def dense_path_flops(cfg, cands, fields, params):
+    """Algorithmic flops of one step on the deep net with biases and
+    normalization (Sec. 2.1), an FMA counting 2, over the samples whose input of
+    the mutated parameter is not zero (all of them for a bias): a dense product
+    per hidden layer after the mutated one (2 W^2 a sample) and the logits
+    (2 W C); 2 in the logit layer."""
+    import torch
     L, C, N, W = cfg.n_layers, cfg.n_classes, cfg.n_samples, cfg.widths[1]
     total = 0.0
     for c in cands:
-        if channel:
-            total += 2 * N + (2 * N * W if L >= 3 else 2 * N * C) + \
-                max(0, L - 3) * 2 * N * W * W + (2 * N * W * C if L >= 3 else 0)
-        else:
-            l = int(c["layer"])
-            total += 2 * N if l == L - 1 else (L - 2 - l) * 2 * N * W * W + 2 * N * W * C
+        l, i = int(c["layer"]), int(c["i"])
+        rows = float(N if i == cfg.widths[l] else torch.count_nonzero(fields[0][l][:, i]))
+        total += rows * (2 if l == L - 1 else (L - 2 - l) * 2 * W * W + 2 * W * C)
+    return total
+
+
+def channel_flops(cfg, chans, fields, params):
+    """Algorithmic flops of one step's channels (Sec. 2.3), an FMA counting 2: the
+    first-layer column (2 a sample); from the first layer f that a changed
+    activation enters (the path's units are walked up to it), a rank-1 term
+    (2 W), a dense product per later hidden layer (2 W^2) and the logits (2 W C);
+    2 C where the walk reaches the logits."""
+    import torch
+    L, C, N, W = cfg.n_layers, cfg.n_classes, cfg.n_samples, cfg.widths[1]
+    a, z = fields
+    total = 0.0
+    for ch in chans:
+        u = [int(v) for v in ch["units"][:L + 1]]
+        de = [float(ch["w_new"][m]) - float(params[m][u[m + 1], u[m]]) for m in range(L)]
+        total += 2 * N
+        inp, walking = a[0][:, u[0]], torch.ones(N, dtype=torch.bool, device=a[0].device)
+        for m in range(L - 1):
+            old = z[m][:, u[m + 1]]
+            new = transfer(cfg, old + de[m] * inp)
+            moved = walking & (new != transfer(cfg, old))
+            n, f = int(moved.sum()), m + 1
+            total += n * (2 * C if f == L - 1 else 2 * W + (L - 2 - f) * 2 * W * W + 2 * W * C)
+            walking, inp = walking & ~moved, new
+        total += int(walking.sum()) * 2 * C
     return total
 
 
@@ -367,9 +411,12 @@ def measure(cfg, w, steps, warmup, args, eval_batch=0):
                 "flops_per_launch": per_step}
     elif cfg.mutation != "single" or cfg.biases or cfg.layer_norm:
         channel = cfg.mutation != "single"
+        params = ctx.params()[0]
+        fields = committed_fields(cfg, w, params)
         per_step = float(np.mean([
-            dense_path_flops(cfg, ctx.propose_channels(t_first + n, cfg.K) if channel
-                             else ctx.propose(t_first + n, cfg.K), channel) for n in sample]))
+            channel_flops(cfg, ctx.propose_channels(t_first + n, cfg.K), fields, params) if channel
+            else dense_path_flops(cfg, ctx.propose(t_first + n, cfg.K), fields, params)
+            for n in sample]))
         achieved = per_step / avg_s / 1e12
         roof = {"bound": "mfma", "kernel": "eval phase (k_channel)" if channel
                 else "eval phase (k_norm)", "achieved": achieved, "peak": MFMA_SPLIT_PEAK_TFS,

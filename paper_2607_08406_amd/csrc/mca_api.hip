@@ -540,7 +540,7 @@ int device_fail(mca_ctx* ctx, hipError_t e, const char* what) {
 // microseconds (a 20-step call after 50 us of idle: 178 us blocking, 149
 // polling).  The explicit calls block: their few kernels end sooner, and each
 // query of a busy stream delays them (four explicit steps on 37-23-5: 329 us
-// polling, 226 blocking).
+// polling, 226 blocking).  A traced call has blocked for its traces' copies before.
 hipError_t wait_stream(hipStream_t s) {
   const auto t0 = std::chrono::steady_clock::now();
   while (true) {

@@ -10,7 +10,7 @@
 //     dh = e / sqrt(S + dS) - c dS / (sqrt S sqrt(S + dS) (sqrt S + sqrt(S + dS))),
 //   so that h + dh = (z' - mu') / sqrt(S') with no difference of near-equal
 //   values; then da = phi(h + dh) - phi(h) (dphi), and the next field's change
-//   W_m da on the matrix cores (v_mfma_f32_16x16x4f32); the logits' change
+//   W_m da as six products of bf16 parts (split_mma.hpp); the logits' change
 //   gives each sample's loss change with the cached softmax (ce_change).
 // k_norm_rows lists, per candidate and in sample order, the samples the change
 // moves (a first-layer weight's input is zero on most: about 81 % of the images)

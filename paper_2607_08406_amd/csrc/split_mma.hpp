@@ -17,7 +17,8 @@
 // and their products' sums taken times 2^-24, both exact.  Changes of 2^104 and
 // more overflow that way, far past the logit change of 88 at which a sample's loss
 // change is lost anyway.  Weights, inputs and ReLU activations are split as they
-// are.
+// are: below 2^-103 they lose their lowest bits, above 3.39e38 (bf16's largest) they
+// become infinite.
 //
 // Hidden-layer weights are kept split beside their fp32 values (NetDev::WF), in
 // the order the kernels read them: for each block of 16 output units and each

@@ -24,8 +24,9 @@
 // The model (pre-LN blocks, learned positions, erf GELU, final LayerNorm,
 // untied output layer with bias; linear layers y = x W^T + b) is the reading
 // of the paper fixed for the oracle.  The dense products run on the matrix
-// cores (v_mfma_f32_16x16x4f32) with each LayerNorm folded into the product
-// that reads it; attention, GELU and the loss run in fp32 on the vector units.
+// cores as six products of bf16 parts (split_mma.hpp) with each LayerNorm folded
+// into the product that reads it; attention's products take fp32 instructions
+// (v_mfma_f32_16x16x4f32), its softmax, GELU and the loss the vector units.
 #include <algorithm>
 
 #include "split_mma.hpp"
